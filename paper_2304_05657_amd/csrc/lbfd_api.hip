@@ -122,6 +122,8 @@ struct lbfd_ctx {
     double *btw = nullptr;
     unsigned long long *bcode_pull = nullptr, *bcode_st = nullptr;  // compact codes of the same descriptors
     double *face_Td = nullptr;                                         // face_T in device memory
+    ulonglong2 *cell_code = nullptr;  // [N] the codes by cell (D3Q27)
+    int *bslot = nullptr;             // [N] position in the boundary list (D3Q27 with curved walls)
     char chem_msg[512] = "";  // which chemistry kernel runs, or why the specialised one does not
     int nblocks_interior = 0;
     double *wall_T = nullptr;
@@ -163,7 +165,7 @@ static void free_ctx(lbfd_ctx *c)
                     c->btw, c->wall_T, c->outlet, c->outlet_un, c->inflow_u, c->inflow_du, c->bq,
                     c->bimg, c->img_rng, c->img_idx, c->img_w, c->img_val, c->sup_idx, c->sup_val,
                     c->fields, c->partials, c->diag_dev, c->bad_dev, c->rx_dev, c->rxk_dev, c->fluid,
-                    c->chem_order, c->chem_heavy, c->chem_count, c->bcode_pull, c->bcode_st, c->face_Td};
+                    c->chem_order, c->chem_heavy, c->chem_count, c->bcode_pull, c->bcode_st, c->face_Td, c->cell_code, c->bslot};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
     delete c;
@@ -463,10 +465,16 @@ static int build_descriptors(lbfd_ctx *c)
     HIP_TRY(hipMemcpy(c->bcode_pull, pcode.data(), pcode.size() * sizeof(unsigned long long), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(c->bcode_st, scode.data(), scode.size() * sizeof(unsigned long long), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(c->face_Td, p.face_T, sizeof(p.face_T), hipMemcpyHostToDevice));
+    c->bwk_host = wk;
+    if (D == 3) {
+        // 3-D tiles read the codes by cell
+        HIP_TRY(launch_cell_codes(c->boundary, c->bcode_pull, c->bcode_st, nb, c->cell_code, c->stream));
+        HIP_TRY(hipStreamSynchronize(c->stream));
+        return LBFD_OK;
+    }
     HIP_TRY(hipMemcpy(c->bsrc, src.data(), src.size() * sizeof(int), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(c->bpt, pt.data(), pt.size() * sizeof(int), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(c->bwk, wk.data(), wk.size(), hipMemcpyHostToDevice));
-    c->bwk_host = wk;
     HIP_TRY(hipMemcpy(c->btw, tw.data(), tw.size() * sizeof(double), hipMemcpyHostToDevice));
     return LBFD_OK;
 }
@@ -502,6 +510,8 @@ static KParams make_kparams(const lbfd_ctx *c)
     k.bcode_pull = c->bcode_pull;
     k.bcode_st = c->bcode_st;
     k.face_Td = c->face_Td;
+    k.cell_code = c->cell_code;
+    k.bslot = c->bslot;
     k.periodic_bits = periodic_bits(c->p);
     k.bpt = c->bpt;
     k.bwk = c->bwk;
@@ -667,7 +677,8 @@ int lbfd_init(const lbfd_params *p, const uint8_t *mask, const double *wall_T, c
     c->nblocks_interior = c->grid.x * c->grid.y * c->grid.z;
     // boundary blocks padded to a multiple of 8 (one per XCD in turn), so
     // that the interior tiles after them start on XCD 0
-    c->nblocks = c->nblocks_interior + (int)(((c->n_boundary + kBlock - 1) / kBlock + 7) / 8 * 8);
+    // (3-D tiles cover every fluid cell: no boundary blocks)
+    c->nblocks = c->nblocks_interior + (c->D == 2 ? (int)(((c->n_boundary + kBlock - 1) / kBlock + 7) / 8 * 8) : 0);
 
 #define ALLOC(ptr, bytes)                                                                   \
     do {                                                                                    \
@@ -687,10 +698,14 @@ int lbfd_init(const lbfd_params *p, const uint8_t *mask, const double *wall_T, c
     ALLOC(c->boundary, sizeof(int) * (boundary.empty() ? 1 : boundary.size()));
     {
         const size_t nbd = boundary.empty() ? 1 : boundary.size();
-        ALLOC(c->bsrc, sizeof(int) * c->Q * nbd);
-        ALLOC(c->bpt, sizeof(int) * 12 * nbd);
-        ALLOC(c->bwk, 12 * nbd);
-        ALLOC(c->btw, sizeof(double) * 12 * nbd);
+        if (c->D == 2) {
+            ALLOC(c->bsrc, sizeof(int) * c->Q * nbd);
+            ALLOC(c->bpt, sizeof(int) * 12 * nbd);
+            ALLOC(c->bwk, 12 * nbd);
+            ALLOC(c->btw, sizeof(double) * 12 * nbd);
+        } else {
+            ALLOC(c->cell_code, sizeof(ulonglong2) * (size_t)N);
+        }
         ALLOC(c->bcode_pull, sizeof(unsigned long long) * nbd);
         ALLOC(c->bcode_st, sizeof(unsigned long long) * nbd);
         ALLOC(c->face_Td, sizeof(double) * 6);
@@ -966,6 +981,25 @@ int lbfd_diagnostics(lbfd_ctx *c, lbfd_diag *d)
     return LBFD_OK;
 }
 
+// The boundary-list position of every cell on the device (3-D contexts with
+// curved walls; the list does not change over a context's life).
+static int upload_slots(lbfd_ctx *c, const std::vector<int> &slot)
+{
+    if (c->D == 2 || c->bslot) return LBFD_OK;
+    if (hipMalloc((void **)&c->bslot, slot.size() * sizeof(int)) != hipSuccess) {
+        c->bslot = nullptr;
+        return fail(LBFD_ENOMEM, "hipMalloc of the boundary positions failed");
+    }
+    const hipError_t e = hipMemcpy(c->bslot, slot.data(), slot.size() * sizeof(int), hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+        (void)hipFree(c->bslot);
+        c->bslot = nullptr;
+        return fail(LBFD_EDEVICE, "upload of the boundary positions failed: %s", hipGetErrorString(e));
+    }
+    c->base.bslot = c->bslot;
+    return LBFD_OK;
+}
+
 int lbfd_set_wall_links(lbfd_ctx *c, int64_t n, const int64_t *cell, const int32_t *dir, const double *q)
 {
     if (!c || n < 0 || (n > 0 && (!cell || !dir || !q))) return fail(LBFD_EINVAL, "bad arguments");
@@ -996,6 +1030,7 @@ int lbfd_set_wall_links(lbfd_ctx *c, int64_t n, const int64_t *cell, const int32
             return fail(LBFD_EINVAL, "wall link %lld does not end at a wall", (long long)k);
         h[(size_t)(Q - 1 - d) * nb + slot[i]] = (float)q[k];  // stored by the entering direction
     }
+    if (const int rs = upload_slots(c, slot)) return rs;
     if (!c->bq && hipMalloc((void **)&c->bq, h.size() * sizeof(float)) != hipSuccess) {
         c->bq = nullptr;
         return fail(LBFD_ENOMEM, "hipMalloc of the wall-distance table failed");
@@ -1181,6 +1216,7 @@ int lbfd_set_image_points(lbfd_ctx *c, int64_t n, const int64_t *cell, const int
     } catch (const std::bad_alloc &) {
         return fail(LBFD_ENOMEM, "host memory for the Shepard support exhausted");
     }
+    if (const int rs = upload_slots(c, pos)) return rs;
     // everything checked: the new set replaces the previous one
     clear_image_points(c);
     if (hipMalloc((void **)&c->sup_idx, sup.size() * sizeof(int)) != hipSuccess ||

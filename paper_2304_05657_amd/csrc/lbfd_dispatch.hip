@@ -124,6 +124,23 @@ hipError_t launch_finalize(const double *partials, int nblocks, double *out, lon
     return hipGetLastError();
 }
 
+__global__ void __launch_bounds__(kBlock) cell_code_kernel(const int *boundary, const unsigned long long *pull,
+                                                           const unsigned long long *st, long long n,
+                                                           ulonglong2 *cell_code)
+{
+    const long long t = (long long)blockIdx.x * kBlock + threadIdx.x;
+    if (t < n) cell_code[boundary[t]] = make_ulonglong2(pull[t], st[t]);
+}
+
+hipError_t launch_cell_codes(const int *boundary, const unsigned long long *pull, const unsigned long long *st,
+                             long long n, ulonglong2 *cell_code, hipStream_t s)
+{
+    if (n == 0) return hipSuccess;
+    cell_code_kernel<<<dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s>>>(boundary, pull, st, n,
+                                                                                          cell_code);
+    return hipGetLastError();
+}
+
 // Widening copy of single-precision scalars into caller double buffers.
 __global__ void __launch_bounds__(kBlock) widen_kernel(const float *src, double *dst, size_t n)
 {

@@ -137,6 +137,8 @@ struct KParams {
     const double *btw;          // [3*4][nb] wall temperature of isothermal ghost walls
     const unsigned long long *bcode_pull;  // [nb] compact pull codes (decode_pull_kind below)
     const unsigned long long *bcode_st;    // [nb] compact stencil codes (decode_point below)
+    const ulonglong2 *cell_code;  // [N] {pull, stencil} codes of boundary cells (D3Q27)
+    const int *bslot;           // [N] position in the boundary-cell list (D3Q27 with curved walls)
     const double *face_Td;      // [6] face_T in device memory (read at a computed face index)
     unsigned periodic_bits;     // bit f: face f periodic
     const float *bq;            // [Q][nb] wall distance of the bounced link of population I, NaN: half-way
@@ -191,23 +193,21 @@ struct KParams {
 // state written).
 enum { kModeStep = 0, kModeStepDiag = 1, kModeFields = 2 };
 
-// D2Q9 steps are one launch over boundary blocks and interior tiles;
-// D3Q27 steps launch them separately (one kernel holding both paths slows
-// the 3-D interior tiles), plus the outlet update with an outflow face.
-constexpr bool fused_step(int Q) { return Q == 9; }
-
+// A step is one launch (boundary blocks and tiles), plus the outlet update
+// for D3Q27 with an outflow face, the chemistry and the image points.
 inline int step_launches(int Q, int nsp, const KParams &kp)
 {
     const int images = kp.bimg != nullptr && kp.n_img > 0 ? 2 : 0;
     const int chem = chem_pass(nsp) && kp.n_fluid > 0 ? 3 : 0;  // counter clear, ordering, sources
-    if (fused_step(Q)) return (kp.boundary_blocks + kp.interior_blocks > 0 ? 1 : 0) + images + chem;
-    const bool outlet = kp.n_boundary > 0 && (kp.face[0] == LBFD_FACE_OUTFLOW || kp.face[1] == LBFD_FACE_OUTFLOW);
-    return (kp.boundary_blocks > 0) + (kp.interior_blocks > 0) + (outlet ? 1 : 0) + images + chem;
+    const bool outlet = Q == 27 && kp.n_boundary > 0 &&
+                        (kp.face[0] == LBFD_FACE_OUTFLOW || kp.face[1] == LBFD_FACE_OUTFLOW);
+    return (kp.boundary_blocks + kp.interior_blocks > 0 ? 1 : 0) + (outlet ? 1 : 0) + images + chem;
 }
 
 // Where a step is launched: the context stream, and which launches (0: all;
-// for per-part timing 1: interior tiles only, 2: boundary blocks, image
-// points and outlet, 3: the chemistry launch only).
+// for per-part timing 1: the tiles (D2Q9: interior cells; D3Q27: every cell,
+// with the image points), 2: D2Q9 boundary blocks with the image points,
+// D3Q27 outlet, 3: the chemistry launch only).
 struct Streams {
     hipStream_t main;
     int part;
@@ -245,6 +245,9 @@ hipError_t launch_adjoint(int Q, int nsp, const KParams &kp, const double *lam_p
 hipError_t launch_tangent(int Q, int nsp, const KParams &kp, const double *dpop, const double *dsc,
                           const double *dwallT, const double *dparam, double *dpop_out, double *dsc_out, double *dq,
                           int obj_kind, double obj_w, hipStream_t s);
+// cell_code[boundary[t]] = {pull[t], st[t]} for t < n.
+hipError_t launch_cell_codes(const int *boundary, const unsigned long long *pull, const unsigned long long *st,
+                             long long n, ulonglong2 *cell_code, hipStream_t s);
 // dst[i] = src[i] for i < n (float to double, on the stream).
 hipError_t launch_widen(const float *src, double *dst, size_t n, hipStream_t s);
 // dst[i] = v for i < n (a fill kernel, so that callers capturing a graph

@@ -245,6 +245,16 @@ __device__ __forceinline__ C density(const KParams &P, C T, const C *Y)
     return (C)P.T_ref_over_W_ref * rcp(T * s);
 }
 
+// The density over its constant factor T_ref / W_ref.
+template <int NSP, class C>
+__device__ __forceinline__ C density_rcp(const KParams &P, C T, const C *Y)
+{
+    C s = 0;
+#pragma unroll
+    for (int k = 0; k < NSP; ++k) s += Y[k] * (C)P.invW[k];
+    return rcp(T * s);
+}
+
 template <int NSP, int PREC>
 __device__ __forceinline__ void load_point(const KParams &P, long long idx, Pt<NSP, typename Prec<PREC>::calc> &o)
 {
@@ -942,6 +952,263 @@ __device__ __forceinline__ void finish_cell(const KParams &P, long long idx, con
     }
 }
 
+// ------------------------------------------------------------ 3-D tiles
+// The pull of one cell of a 3-D tile.  The rows of the 3 x 3 neighbour lines
+// are the same for a wave (its lanes differ in x only), so an interior wave
+// loads each population at a scalar base plus one of three lane offsets.
+// Where the wave holds a boundary cell, a lane whose source is no fluid cell
+// takes its own cell's opposite population by selecting the address (no
+// branch and no wait between the 27 loads); inlet, outlet and interpolated
+// walls, which few waves hold, follow in passes of their own.
+// m: the momentum sums.  In the mixed forms an interior cell's sum takes the
+// stored value and its scale in one fused multiply-add, a boundary cell's the
+// scaled population (one factor per lane and lattice weight tells them apart).
+template <int Q, int PREC, bool CW>
+__device__ __forceinline__ void tile_pull(const KParams &P, int x, int y, int z, long long tb, bool bnd,
+                                          unsigned long long pcode, typename Prec<PREC>::calc (&g)[Q],
+                                          typename Prec<PREC>::calc (&m)[3])
+{
+    using C = typename Prec<PREC>::calc;
+    using T = typename Prec<PREC>::pop;
+    using L = Lat<Q>;
+    // wrapped neighbour coordinates (a wrapped source beyond a face that is
+    // not periodic is never read: its code is not kPullFluid)
+    const int xs[3] = {x == 0 ? P.nx - 1 : x - 1, x, x == P.nx - 1 ? 0 : x + 1};
+    const int ys[3] = {y == 0 ? P.ny - 1 : y - 1, y, y == P.ny - 1 ? 0 : y + 1};
+    const int zs[3] = {z == 0 ? P.nz - 1 : z - 1, z, z == P.nz - 1 ? 0 : z + 1};
+    // population i of the cell at neighbour offset (ox, oy, oz), as stored
+    auto at = [&](int i, int ox, int oy, int oz) -> const T * {
+        const long long row = ((long long)zs[1 + oz] * P.ny + ys[1 + oy]) * P.nx;
+        return (const T *)P.pop_in + ((long long)i * P.N + row) + (uint32_t)xs[1 + ox];
+    };
+    auto raw = [](T v) -> C {
+        if constexpr (PREC == LBFD_MIXED_FP16)
+            return __half2float(v);
+        else
+            return v;
+    };
+    auto scale = [](auto I) -> C {
+        return PREC == LBFD_FP64 ? (C)1 : (C)(float)(L::w(decltype(I)::value) * kCs2);
+    };
+    auto widen = [&](T v, auto I) -> C {
+        if constexpr (PREC == LBFD_FP64)
+            return v;
+        else
+            return raw(v) * scale(I);
+    };
+    // sum of c v s over the populations (v with its scale s)
+    auto momentum = [&](auto &&v, auto &&sc) {
+        m[0] = m[1] = m[2] = 0;
+        sfor<0, Q>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            auto add = [&](C &acc, auto sign) {
+                if constexpr (PREC == LBFD_FP64)
+                    acc += (C)decltype(sign)::value * v(I);
+                else
+                    acc = fma(v(I), (C)decltype(sign)::value * sc(I), acc);
+            };
+            if constexpr (L::cx(i) != 0) add(m[0], std::integral_constant<int, L::cx(i)>{});
+            if constexpr (L::cy(i) != 0) add(m[1], std::integral_constant<int, L::cy(i)>{});
+            if constexpr (L::cz(i) != 0) add(m[2], std::integral_constant<int, L::cz(i)>{});
+        });
+    };
+    C v[Q];
+    if (!__any(bnd)) {
+        sfor<0, Q>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            v[i] = raw(*at(i, -L::cx(i), -L::cy(i), -L::cz(i)));
+            g[i] = PREC == LBFD_FP64 ? v[i] : v[i] * scale(I);
+        });
+        momentum([&](auto I) { return v[decltype(I)::value]; }, scale);
+        return;
+    }
+    sfor<0, Q>([&](auto I) {
+        constexpr int i = decltype(I)::value;
+        const T *src = at(i, -L::cx(i), -L::cy(i), -L::cz(i));
+        const T *own = at(Q - 1 - i, 0, 0, 0);
+        v[i] = raw(*(decode_pull_kind(pcode, i) == kPullFluid ? src : own));
+        g[i] = PREC == LBFD_FP64 ? v[i] : v[i] * scale(I);
+    });
+    if (__any((pcode & 0xaaaaaaaaaaaaaaaaull) != 0)) {
+        // inlets (Eq. 31: + 2 w_I rho_in c_I.u_in; an x face carries the
+        // per-cell profile indexed by the cell's (y, z)) and outlets (the
+        // value kept in the outlet buffer)
+        const long long s3 = (long long)P.ny * P.nz;
+        sfor<0, Q>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            if constexpr (i != (Q - 1) / 2) {
+                constexpr int cx = L::cx(i), cy = L::cy(i), cz = L::cz(i);
+                const int kind = decode_pull_kind(pcode, i);
+                const bool inflow = kind == kPullInflow, outlet = kind == kPullOutlet;
+                if (__any(inflow)) {
+                    const int f = (cx == 1 && x == 0 && P.face[0] == LBFD_FACE_INFLOW)               ? 0
+                                  : (cx == -1 && x == P.nx - 1 && P.face[1] == LBFD_FACE_INFLOW) ? 1
+                                                                                                 : -1;
+                    const bool prof = inflow && f >= 0;
+                    const double *ub = prof ? P.inflow_u : kZeroEntry;
+                    const long long o = prof ? 3 * s3 * f + (long long)z * P.ny + y : 0;
+                    const double ux = ub[o], uy = ub[prof ? o + s3 : 0], uz = ub[prof ? o + 2 * s3 : 0];
+                    const double cu =
+                        prof ? cx * ux + cy * uy + cz * uz : cx * P.u_in[0] + cy * P.u_in[1] + cz * P.u_in[2];
+                    g[i] = inflow ? g[i] + (C)(2.0 * L::w(i) * P.rho_in * cu) : g[i];
+                }
+                if (__any(outlet)) {
+                    const double *ob = outlet ? P.outlet : kZeroEntry;
+                    const C ov = (C)ob[outlet ? outlet_index(P, cx < 0 ? 1 : 0, i, Q, y, z) : 0];
+                    g[i] = outlet ? ov : g[i];
+                }
+            }
+        });
+    }
+    if constexpr (CW) {
+        // linearly interpolated bounce-back (post-collision form) for a
+        // wall met at the fraction q of the link toward it (direction OPP)
+        if (P.bq != nullptr) {
+            sfor<0, Q>([&](auto I) {
+                constexpr int i = decltype(I)::value;
+                constexpr int opp = Q - 1 - i;
+                if constexpr (i != opp) {
+                    const bool wall = decode_pull_kind(pcode, i) == kPullBounce;
+                    const float qraw = P.bq[i * P.n_boundary + tb];
+                    const float qs = wall ? qraw : __builtin_nanf("");
+                    const bool interp = qs == qs;
+                    if (__any(interp)) {
+                        const C q2 = (C)2 * (C)qs;  // weights in the arithmetic precision
+                        // q < 1/2: the far node r + c_I is the pull source of
+                        // direction OPP (when it is a fluid cell)
+                        const bool near_half = qs < 0.5f;
+                        const bool use_far = interp && near_half && decode_pull_kind(pcode, opp) == kPullFluid;
+                        const T *far = at(opp, L::cx(i), L::cy(i), L::cz(i)), *own = at(opp, 0, 0, 0);
+                        const C gfar = widen(*(use_far ? far : own), I);
+                        const C gown = widen(*at(i, 0, 0, 0), I);
+                        const C lo = q2 * g[i] + ((C)1 - q2) * gfar;
+                        const C iq = (C)1 / (interp && !near_half ? q2 : (C)1);
+                        const C hi = g[i] * iq + (q2 - (C)1) * iq * gown;
+                        g[i] = use_far ? lo : (interp && !near_half) ? hi : g[i];
+                    }
+                }
+            });
+        }
+    }
+    if constexpr (PREC == LBFD_FP64) {
+        momentum([&](auto I) { return g[decltype(I)::value]; }, scale);
+    } else {
+        // one factor per squared speed
+        const C f[4] = {bnd ? (C)1 : scale(std::integral_constant<int, 13>{}),
+                        bnd ? (C)1 : scale(std::integral_constant<int, 12>{}),
+                        bnd ? (C)1 : scale(std::integral_constant<int, 9>{}),
+                        bnd ? (C)1 : scale(std::integral_constant<int, 0>{})};
+        sfor<0, Q>([&](auto I) { v[decltype(I)::value] = bnd ? g[decltype(I)::value] : v[decltype(I)::value]; });
+        momentum([&](auto I) { return v[decltype(I)::value]; },
+                 [&](auto I) {
+                     constexpr int i = decltype(I)::value;
+                     return f[L::cx(i) * L::cx(i) + L::cy(i) * L::cy(i) + L::cz(i) * L::cz(i)];
+                 });
+    }
+}
+
+// The stencil points m = -2, -1, 1, 2 of one cell of a 3-D tile along axis d
+// (T, rho, Y_k), ghosts included; near: some point lies behind a wall.  A
+// ghost's image is a cell of the same line (the point itself, the cell, a
+// first neighbour), so boundary lanes select their four cells and the loads
+// are those of interior lanes; ghost values are formed by selection where a
+// lane of the wave has one on this axis.  The two points of a side share
+// their wall, hence one wall temperature a side.
+// d1r: the density's first derivative (d1).  An interior cell leaves the
+// constant factor of the first point's density to the difference that takes
+// it (one rounding less); the select keeps that form beside the boundary
+// cells' formed densities.
+template <int NSP, int PREC, bool DIAG, bool CW>
+__device__ __forceinline__ void tile_stencil(const KParams &P, int d, int x, int y, int z, long long idx,
+                                             long long tb, bool bnd, unsigned long long scode,
+                                             const Pt<NSP, typename Prec<PREC>::calc> &ctr,
+                                             Pt<NSP, typename Prec<PREC>::calc> (&pv)[4], bool &near,
+                                             typename Prec<PREC>::calc &d1r, double &wallq)
+{
+    using C = typename Prec<PREC>::calc;
+    const int c = d == 0 ? x : d == 1 ? y : z, n = d == 0 ? P.nx : d == 1 ? P.ny : P.nz;
+    const int stride = d == 0 ? 1 : d == 1 ? P.nx : P.nx * P.ny;
+    int off[4];  // cell offsets of m = -2, -1, 1, 2 along the (wrapped) axis
+#pragma unroll
+    for (int j = 0; j < 4; ++j) off[j] = (wrap_once(c + slot_offset(j), n) - c) * stride;
+    const unsigned s20 = (unsigned)(scode >> (20 * d)) & 0xfffffu;  // this axis' four slots of five bits
+    int at[4] = {off[0], off[1], off[2], off[3]};
+    if (__any(s20 != 0)) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int img = (int)(s20 >> (5 * j + 3)) & 3;
+            const int same = off[j < 2 ? 1 : 2], mirror = off[j < 2 ? 2 : 1];
+            at[j] = img == kImgSelf ? off[j] : img == kImgMirror ? mirror : img == kImgSame ? same : 0;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) load_point<NSP, PREC>(P, idx + at[j], pv[j]);
+    const C r0 = density_rcp<NSP>(P, pv[0].T, pv[0].Y);
+    const unsigned kinds = s20 & 0x39ce7u;  // the kinds of the four slots
+    near = kinds != 0;
+    if (__any(near)) {
+        if constexpr (CW) {
+            if (P.bimg != nullptr) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int li = near ? P.bimg[(d * 4 + j) * P.n_boundary + tb] : -1;
+                    if (__any(li >= 0)) {
+                        Pt<NSP, C> iv;
+                        image_value<NSP>(P, li >= 0 ? li : 0, iv);
+                        pv[j].T = li >= 0 ? iv.T : pv[j].T;
+                        pv[j].rho = li >= 0 ? iv.rho : pv[j].rho;
+#pragma unroll
+                        for (int k = 0; k < NSP; ++k) pv[j].Y[k] = li >= 0 ? iv.Y[k] : pv[j].Y[k];
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int side = 0; side < 2; ++side) {
+            const int j1 = side ? 2 : 1, j2 = side ? 3 : 0;
+            const int k1 = (int)(s20 >> (5 * j1)) & 7, k2 = (int)(s20 >> (5 * j2)) & 7;
+            // the side's wall: the first non-fluid point from the cell (the
+            // kinds of both slots are its kind when it is the first neighbour)
+            const bool iso1 = k1 == kIso, iso2 = k2 == kIso;
+            if (__any(iso2)) {
+                const bool second = k1 == kFluid;
+                const int mw = (side ? 1 : -1) * (second ? 2 : 1);
+                const bool out = (unsigned)(c + mw) >= (unsigned)n && !((P.periodic_bits >> (2 * d + side)) & 1u);
+                const double *tw = out ? P.face_Td + (2 * d + side) : P.wall_T + (idx + off[second ? j2 : j1]);
+                const C Tw = (C)*(iso2 ? tw : P.face_Td);
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const int j = q ? j2 : j1;
+                    const bool iso = q ? iso2 : iso1;
+                    const C rb = density<NSP>(P, Tw, pv[j].Y);
+                    pv[j].rho = iso ? (C)2 * rb - pv[j].rho : pv[j].rho;
+                    pv[j].T = iso ? (C)2 * Tw - pv[j].T : pv[j].T;
+                }
+                if constexpr (DIAG) {
+                    const double q = 2.0 * P.alpha * (double)density<NSP>(P, Tw, ctr.Y) * ((double)ctr.T - (double)Tw);
+                    wallq += iso1 ? q : 0.0;
+                }
+            }
+            const bool in1 = k1 == kInflow, in2 = k2 == kInflow;
+            if (__any(in2)) {
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const int j = q ? j2 : j1;
+                    const bool in = q ? in2 : in1;
+                    pv[j].rho = in ? (C)2 * (C)P.rho_in - pv[j].rho : pv[j].rho;
+                    pv[j].T = in ? (C)2 * (C)P.T_in - pv[j].T : pv[j].T;
+#pragma unroll
+                    for (int k = 0; k < NSP; ++k)
+                        pv[j].Y[k] = in ? (C)2 * (C)P.Y_in[k] - pv[j].Y[k] : pv[j].Y[k];
+                }
+            }
+        }
+    }
+    const C f0 = bnd ? (C)1 : (C)P.T_ref_over_W_ref, ra = bnd ? pv[0].rho : r0;
+    const C lo = fma(f0, ra, -((C)8 * pv[1].rho)), hi = (C)8 * pv[2].rho - pv[3].rho;
+    d1r = (lo + hi) * (C)(1.0 / 12.0);
+}
+
 // Interior tile of one 256-thread block: 64 x 4 cells in 2-D, 64 x 2 x 2
 // in 3-D.
 template <int D> struct TileShape {
@@ -949,12 +1216,21 @@ template <int D> struct TileShape {
 };
 
 // One block of the step.
-// FAST = true: an interior tile (bx, by, bz) of the box whose threads work
+// FAST = true, 2-D: an interior tile (bx, by) of the box whose threads work
 // only on interior fluid cells (every pull source and every finite-difference
 // point in the box and fluid), with plain offset loads.
-// FAST = false: block bx of the list of the other fluid cells (boundary
+// FAST = false (2-D): block bx of the list of the other fluid cells (boundary
 // cells), with the general geometry logic.
-// (tx, ty, tz): the thread's place in the tile (FAST) or tx in 0..255.
+// 3-D (FAST = true): a tile (bx, by, bz) whose threads work on every fluid
+// cell.  A boundary cell differs from an interior one in its addresses and in
+// ghost values, both selected per lane from the cell's two 64-bit codes under
+// wave-uniform conditions (some lane of the wave is a boundary cell), so that
+// the cache lines that interior and boundary cells share are fetched and
+// written once.  What bounded the two separate launches was that traffic:
+// interior tiles then listed boundary cells moved 53 GB a step on a 512 x 256
+// x 256 packing with 9 species, 2.6 times what the cells need.
+// (tx, ty, tz): the thread's place in the tile (FAST; ty and tz the same for
+// a wave) or tx in 0..255.
 // slot: the block's row of the diagnostics partials.
 // CW: boundary cells apply the curved-wall treatments when listed: the
 // interpolated bounce-back of P.bq and the Shepard image points of P.bimg (a
@@ -968,18 +1244,30 @@ __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int
     using C = typename Prec<PREC>::calc;
     constexpr int D = L::D;
     constexpr bool DIAG = MODE != kModeStep;
+    constexpr bool ALL = D == 3;  // every fluid cell of the tile
     using TS = TileShape<D>;
+    static_assert(FAST || D == 2, "3-D blocks are tiles");
     int x, y, z;
     long long idx, tb = 0;
     unsigned long long pcode = 0, scode = 0;  // a boundary cell's compact codes
-    bool active, inbox;
+    bool active, inbox, bnd = !FAST;
     if constexpr (FAST) {
         x = bx * TS::X + tx;
         y = by * TS::Y + ty;
         z = bz * TS::Z + tz;
         inbox = x < P.nx && y < P.ny && z < P.nz;
         idx = inbox ? ((long long)z * P.ny + y) * P.nx + x : 0;
-        active = inbox && P.code[idx] == kCodeInterior;
+        const int code = inbox ? (int)P.code[idx] : (int)kCodeSolid;
+        active = ALL ? code != kCodeSolid : code == kCodeInterior;
+        if constexpr (ALL) {
+            bnd = code == kCodeBoundary;
+            if (bnd) {
+                const ulonglong2 cc = P.cell_code[idx];
+                pcode = cc.x;
+                scode = cc.y;
+                if constexpr (CW) tb = P.bslot[idx];
+            }
+        }
     } else {
         tb = (long long)bx * kBlock + tx;
         inbox = false;
@@ -993,7 +1281,7 @@ __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int
         y = (int)((idx / P.nx) % P.ny);
         z = (int)(idx / ((long long)P.nx * P.ny));
     }
-    const long long sy = P.nx, sz = (long long)P.nx * P.ny;
+    const long long sy = P.nx;
     double acc[kNDiag];
     if constexpr (DIAG) diag_identity(acc);
 
@@ -1049,14 +1337,14 @@ __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int
     };
 
     if (active) {
+        C m[3] = {0, 0, 0};
         // streaming with boundary conditions (pull; already issued for tiles)
-        if constexpr (!TILE)
+        if constexpr (ALL)
+            tile_pull<Q, PREC, CW>(P, x, y, z, tb, bnd, pcode, g, m);
+        else if constexpr (!TILE)
             sfor<0, Q>([&](auto I) {
                 constexpr int i = decltype(I)::value;
-                if constexpr (FAST)
-                    g[i] = pop_load<Q, PREC, i>(P.pop_in, P.N, idx - (L::cx(i) + sy * L::cy(i) + sz * L::cz(i)));
-                else
-                    g[i] = desc_pull<Q, PREC, i, CW>(P, tb, P.n_boundary, idx, x, y, z, pcode);
+                g[i] = desc_pull<Q, PREC, i, CW>(P, tb, P.n_boundary, idx, x, y, z, pcode);
             });
         Pt<NSP, C> ctr;
         if constexpr (TILE)
@@ -1065,17 +1353,17 @@ __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int
             load_point<NSP, PREC>(P, idx, ctr);
         const C rho = ctr.rho;
 
-        // moments: sum g and sum c g (Eq. 13)
-        C sg = 0, m[3] = {0, 0, 0};
+        // moments: sum g and sum c g (Eq. 13; in 3-D formed with the pull)
+        C sg = 0;
         sfor<0, Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
             sg += g[i];
-            if constexpr (L::cx(i) == 1) m[0] += g[i];
-            if constexpr (L::cx(i) == -1) m[0] -= g[i];
-            if constexpr (L::cy(i) == 1) m[1] += g[i];
-            if constexpr (L::cy(i) == -1) m[1] -= g[i];
-            if constexpr (L::cz(i) == 1) m[2] += g[i];
-            if constexpr (L::cz(i) == -1) m[2] -= g[i];
+            if constexpr (!ALL) {
+                if constexpr (L::cx(i) == 1) m[0] += g[i];
+                if constexpr (L::cx(i) == -1) m[0] -= g[i];
+                if constexpr (L::cy(i) == 1) m[1] += g[i];
+                if constexpr (L::cy(i) == -1) m[1] -= g[i];
+            }
         });
         const C inv_rho = rcp(rho);
         const C inv_rc = (C)3 * inv_rho;  // 1 / (rho cs^2)
@@ -1099,9 +1387,9 @@ __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int
             }
         }
         const C inv_M = LE ? rcp(Mc) : (C)0, inv_cp = LE ? rcp(cpc) : (C)0;
-        auto axis_terms = [&](auto &&val, const C (&r5)[5], bool near, C ud) -> C {
-            // val(f, m): field f (0 = T, 2 + k = Y_k) at offset m = -2..2
-            const C d1r = d1(r5[0], r5[1], r5[2], r5[3], r5[4]);
+        auto axis_terms = [&](auto &&val, C d1r, bool near, C ud) {
+            // val(f, m): field f (0 = T, 2 + k = Y_k) at offset m = -2..2;
+            // d1r: the derivative of rho
             const C uh = (C)0.5 * ud;  // the conv2 values are twice the derivatives
             C t1, t2;
             {
@@ -1151,7 +1439,6 @@ __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int
             // mass-conserving correction of the convection (Eq. 26)
 #pragma unroll
             for (int k = 0; k < NSP; ++k) CY[k] += uh * (cY[k] - ctr.Y[k] * sumc);
-            return d1r;
         };
 #pragma unroll 1
         for (int d = 0; d < D; ++d) {
@@ -1163,99 +1450,28 @@ __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int
                 C r5[5];
 #pragma unroll
                 for (int m = 0; m < 5; ++m) r5[m] = tile[kNP + ic + (m - 2) * sd];
-                d1r = axis_terms([&](int f, int m) -> C { return tile[f * kNP + ic + m * sd]; }, r5, false, ud);
-            } else if constexpr (FAST) {
-                // the four points' T and Y, read once for their densities and
-                // kept for the finite differences
-                const long long sd = d == 0 ? 1 : d == 1 ? sy : sz;
-                Pt<NSP, C> pv[4];
-                C r5[5];
-                r5[2] = rho;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    load_point<NSP, PREC>(P, idx + (j < 2 ? j - 2 : j - 1) * sd, pv[j]);
-                    r5[j < 2 ? j : j + 1] = pv[j].rho;
-                }
-                d1r = axis_terms(
-                    [&](int f, int m) -> C {
-                        const int j = m < 0 ? m + 2 : m + 1;
-                        return f == 0 ? pv[j].T : pv[j].Y[f - 2];
-                    },
-                    r5, false, ud);
+                d1r = d1(r5[0], r5[1], r5[2], r5[3], r5[4]);
+                axis_terms([&](int f, int m) -> C { return tile[f * kNP + ic + m * sd]; }, d1r, false, ud);
             } else if constexpr (D == 2) {
                 // boundary cell (2-D): whole stencil points from the descriptors
                 Pt<NSP, C> st[5];
                 bool near = false;
                 desc_stencil<NSP, PREC, DIAG, CW>(P, tb, P.n_boundary, d, ctr, st, near, wallq);
-                C r5[5] = {st[0].rho, st[1].rho, st[2].rho, st[3].rho, st[4].rho};
-                d1r = axis_terms(
-                    [&](int f, int m) -> C { return f == 0 ? st[m + 2].T : st[m + 2].Y[f - 2]; }, r5, near, ud);
+                d1r = d1(st[0].rho, st[1].rho, st[2].rho, st[3].rho, st[4].rho);
+                axis_terms([&](int f, int m) -> C { return f == 0 ? st[m + 2].T : st[m + 2].Y[f - 2]; }, d1r, near, ud);
             } else {
-                // boundary cell (3-D): per offset m = -2, -1, 1, 2 the descriptor
-                // gives the point holding the value (or the ghost's image)
-                // and the kind of the wall behind a ghost (Sec. III.B)
-                // (or the listed image point of a curved wall)
-                const long long nbd = P.n_boundary;
-                int pts[4], wks[4], lis[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    if constexpr (CW) {
-                        pts[j] = P.bpt[(d * 4 + j) * nbd + tb];
-                        wks[j] = P.bwk[(d * 4 + j) * nbd + tb];
-                        lis[j] = P.bimg != nullptr ? P.bimg[(d * 4 + j) * nbd + tb] : -1;
-                    } else {
-                        pts[j] = (int)decode_point(scode, d, j, idx, x, y, z, P.nx, P.ny, P.nz);
-                        wks[j] = decode_kind(scode, d, j);
-                        lis[j] = -1;
-                    }
-                }
-                // the wall temperature behind an isothermal ghost at slot j
-                auto wall_temp = [&](int j) -> double {
-                    if constexpr (CW)
-                        return P.btw[(d * 4 + j) * nbd + tb];
-                    else
-                        return decode_wall_T(scode, d, j, x, y, z, P.nx, P.ny, P.nz, P.periodic_bits, P.face_Td,
-                                             P.wall_T);
-                };
-                const bool near = (wks[0] | wks[1] | wks[2] | wks[3]) != kFluid;
-                C r5[5];
-                r5[2] = rho;
-                Pt<NSP, C> pv[4];  // the points' (or images') values, kept for the differences
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int slot = j < 2 ? j : j + 1;
-                    Pt<NSP, C> &pt = pv[j];
-                    if (CW && lis[j] >= 0)
-                        image_value<NSP>(P, lis[j], pt);
-                    else
-                        load_point<NSP, PREC>(P, pts[j], pt);
-                    r5[slot] = pt.rho;
-                    if (wks[j] == kIso) {
-                        const C Tw = (C)wall_temp(j);
-                        r5[slot] = (C)2 * density<NSP>(P, Tw, pt.Y) - pt.rho;
-                        if constexpr (DIAG) {
-                            if (j == 1 || j == 2)
-                                wallq += 2.0 * P.alpha * (double)density<NSP>(P, Tw, ctr.Y) *
-                                         ((double)ctr.T - (double)Tw);
-                        }
-                    } else if (wks[j] == kInflow) {
-                        r5[slot] = (C)2 * (C)P.rho_in - pt.rho;
-                    }
-                }
-                d1r = axis_terms(
+                // 3-D: the four points' T and Y, read once for their densities
+                // and kept for the finite differences; behind a wall a point
+                // is the ghost formed from its image (Sec. III.B)
+                Pt<NSP, C> pv[4];
+                bool near = false;
+                tile_stencil<NSP, PREC, DIAG, CW>(P, d, x, y, z, idx, tb, bnd, scode, ctr, pv, near, d1r, wallq);
+                axis_terms(
                     [&](int f, int m) -> C {
                         const int j = m < 0 ? m + 2 : m + 1;
-                        const C v = f == 0 ? pv[j].T : pv[j].Y[f - 2];
-                        if (wks[j] == kFluid) return v;
-                        if (f == 0) {
-                            if (wks[j] == kIso) return (C)2 * (C)wall_temp(j) - v;
-                            if (wks[j] == kInflow) return (C)2 * (C)P.T_in - v;
-                            return v;
-                        }
-                        if (wks[j] == kInflow) return (C)2 * (C)P.Y_in[f - 2] - v;
-                        return v;
+                        return f == 0 ? pv[j].T : pv[j].Y[f - 2];
                     },
-                    r5, near, ud);
+                    d1r, near, ud);
             }
             grad[0] = d == 0 ? d1r : grad[0];
             grad[1] = d == 1 ? d1r : grad[1];
@@ -1298,7 +1514,7 @@ __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int
                         }
                     });
                 }
-            } else if constexpr (!FAST) {
+            } else if constexpr (D == 3) {
                 // 3-D: outlet cells hand their outward normal velocity to
                 // outlet_kernel, which applies the same update (keeps the
                 // nine extra gathers out of this kernel's registers)
@@ -1322,10 +1538,7 @@ __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int
 // kernel (measured on MI355X).  2-D with up to 4 species: three waves
 // (168 VGPRs) in FP64 and four (128) in the mixed forms -- the boundary
 // path, which needs more, spills instead of lowering the tiles' occupancy.
-// 3-D FP64: two waves (256 VGPRs) for boundary cells with up to 4 species
-// and for both parts with 9 species (spills of 132 and 208 bytes per lane;
-// the 9-species interior tiles 3 % and boundary cells 13 % faster than at
-// the free allocator's one wave).  Otherwise the allocator is left free
+// 3-D FP64: two waves (256 VGPRs).  Otherwise the allocator is left free
 // (1): for the launches with diagnostics or fields (MODE != kModeStep),
 // which run once per check or read, and for the curved-wall and
 // mixture-transport instantiations (CW, LE).  The 2-D FP64 fields launch
@@ -1333,51 +1546,46 @@ __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int
 // velocities at the three-wave budget (spilling) and exact ones without it;
 // the assembly check of the build finds no one-sided copy in it, so the
 // budget stays off on those paths.
-template <int Q, int NSP, int PREC, int PART, int MODE = kModeStep, bool CWLE = false> struct StepWaves {
-    static constexpr int value = (MODE != kModeStep || CWLE)                               ? 1
-                                 : (Q == 9 && NSP <= 4)                                     ? (PREC == LBFD_FP64 ? 3 : 4)
-                                 : (Q == 27 && NSP <= 4 && PART == 2 && PREC == LBFD_FP64) ? 2
-                                 : (Q == 27 && NSP == 9 && PREC == LBFD_FP64)              ? 2
-                                                                                           : 1;
+template <int Q, int NSP, int PREC, int MODE = kModeStep, bool CWLE = false> struct StepWaves {
+    static constexpr int value = (MODE != kModeStep || CWLE)           ? 1
+                                 : (Q == 9 && NSP <= 4)                 ? (PREC == LBFD_FP64 ? 3 : 4)
+                                 : (Q == 27 && PREC == LBFD_FP64)       ? 2
+                                                                        : 1;
 };
 
 // The step over the block range [block_begin, block_begin + gridDim.x) of
-// the list (boundary blocks, then interior tiles).  PART 0: one launch
-// covers both kinds -- boundary blocks first, so that their long dependent
-// chains of descriptor and neighbour loads start with the launch and the
-// interior tiles fill the remaining wave slots (D2Q9).  PART 2 / PART 1:
-// boundary blocks / interior tiles only, two launches in stream order
-// (D3Q27, where one kernel holding both paths slows the interior tiles).
-// Consecutive blocks go to the 8 XCDs in turn, so the interior tiles are
-// renumbered to give each XCD one contiguous band of the box;
-// boundary_blocks is a multiple of 8, which keeps the XCD of a tile block
-// equal to its index modulo 8.
-template <int Q, int NSP, int PREC, int MODE, int PART, bool CW = false, bool LE = false>
+// the list (boundary blocks, then tiles).  D2Q9: boundary blocks first, so
+// that their long dependent chains of descriptor and neighbour loads start
+// with the launch and the interior tiles fill the remaining wave slots.
+// D3Q27: no boundary blocks, the tiles cover every fluid cell.
+// Consecutive blocks go to the 8 XCDs in turn, so the tiles are renumbered
+// to give each XCD one contiguous band of the box; boundary_blocks is a
+// multiple of 8, which keeps the XCD of a tile block equal to its index
+// modulo 8.
+template <int Q, int NSP, int PREC, int MODE, bool CW = false, bool LE = false>
 __global__ void __launch_bounds__(kBlock)
-__attribute__((amdgpu_waves_per_eu(StepWaves<Q, NSP, PREC, PART, MODE, CW || LE>::value))) step_kernel(const KParams P)
+__attribute__((amdgpu_waves_per_eu(StepWaves<Q, NSP, PREC, MODE, CW || LE>::value))) step_kernel(const KParams P)
 {
     using TS = TileShape<Lat<Q>::D>;
     const long long b = (long long)blockIdx.x + P.block_begin;
-    if constexpr (PART != 1) {
+    if constexpr (Lat<Q>::D == 2) {
         if (b < P.boundary_blocks) {
             step_block<Q, NSP, PREC, MODE, false, CW, LE>(P, (int)b, 0, 0, (int)threadIdx.x, 0, 0,
                                                   P.interior_blocks + b);
             return;
         }
     }
-    if constexpr (PART != 2) {
-        const long long t = b - P.boundary_blocks;
-        const long long n = P.interior_blocks, q = n >> 3;
-        const int xcd = (int)(t & 7), r = (int)(n & 7);
-        const long long tile = xcd * q + (xcd < r ? xcd : r) + (t >> 3);
-        const int bx = (int)(tile % P.tiles_x);
-        const int by = (int)((tile / P.tiles_x) % P.tiles_y);
-        const int bz = (int)(tile / ((long long)P.tiles_x * P.tiles_y));
-        const int tx = (int)threadIdx.x % TS::X;
-        const int ty = ((int)threadIdx.x / TS::X) % TS::Y;
-        const int tz = (int)threadIdx.x / (TS::X * TS::Y);
-        step_block<Q, NSP, PREC, MODE, true, false, LE>(P, bx, by, bz, tx, ty, tz, tile);
-    }
+    const long long t = b - P.boundary_blocks;
+    const long long n = P.interior_blocks, q = n >> 3;
+    const int xcd = (int)(t & 7), r = (int)(n & 7);
+    const long long tile = xcd * q + (xcd < r ? xcd : r) + (t >> 3);
+    const int bx = (int)(tile % P.tiles_x);
+    const int by = (int)((tile / P.tiles_x) % P.tiles_y);
+    const int bz = (int)(tile / ((long long)P.tiles_x * P.tiles_y));
+    const int tx = (int)threadIdx.x % TS::X;
+    // a wave is one row of the tile: its y and z are scalars
+    const int row = Lat<Q>::D == 3 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / TS::X) : (int)threadIdx.x / TS::X;
+    step_block<Q, NSP, PREC, MODE, true, CW && Lat<Q>::D == 3, LE>(P, bx, by, bz, tx, row % TS::Y, row / TS::Y, tile);
 }
 
 // ------------------------------------------------------------ image points
@@ -1688,24 +1896,21 @@ __global__ void __launch_bounds__(kBlock) init_kernel(const KParams P, const dou
 // ------------------------------------------------------------ launchers
 // Instantiated once per configuration in inst/*.hip (explicit
 // instantiation), declared extern in the dispatcher.
-// One step: the boundary blocks and the interior tiles (both read level n
-// and write disjoint cells of level n+1), on the context stream, then for
-// D3Q27 the outlet update.
-template <int Q, int NSP, int PREC, int MODE, int PART, bool LE>
+// One step: the boundary blocks (D2Q9) and the tiles (both read level n and
+// write disjoint cells of level n+1) in one launch on the context stream,
+// then for D3Q27 the outlet update.
+template <int Q, int NSP, int PREC, int MODE, bool LE>
 hipError_t launch_range_t(const KParams &kp, long long count, hipStream_t s)
 {
-    if constexpr (PART != 1) {
-        // boundary cells with curved-wall links or image points
-        if (kp.bq != nullptr || kp.bimg != nullptr) {
-            step_kernel<Q, NSP, PREC, MODE, PART, true, LE><<<dim3((unsigned)count), dim3(kBlock), 0, s>>>(kp);
-            return hipGetLastError();
-        }
-    }
-    step_kernel<Q, NSP, PREC, MODE, PART, false, LE><<<dim3((unsigned)count), dim3(kBlock), 0, s>>>(kp);
+    // boundary cells with curved-wall links or image points
+    if (kp.bq != nullptr || kp.bimg != nullptr)
+        step_kernel<Q, NSP, PREC, MODE, true, LE><<<dim3((unsigned)count), dim3(kBlock), 0, s>>>(kp);
+    else
+        step_kernel<Q, NSP, PREC, MODE, false, LE><<<dim3((unsigned)count), dim3(kBlock), 0, s>>>(kp);
     return hipGetLastError();
 }
 
-template <int Q, int NSP, int PREC, int MODE, int PART>
+template <int Q, int NSP, int PREC, int MODE>
 hipError_t launch_range(const KParams &kp0, long long begin, long long count, hipStream_t s)
 {
     if (count <= 0) return hipSuccess;
@@ -1713,15 +1918,16 @@ hipError_t launch_range(const KParams &kp0, long long begin, long long count, hi
     kp.block_begin = begin;
     // the mixture-averaged transport is a separate instantiation, so that
     // unity-Lewis steps keep their registers
-    if (kp.transport == LBFD_MIXTURE_AVERAGED) return launch_range_t<Q, NSP, PREC, MODE, PART, true>(kp, count, s);
-    return launch_range_t<Q, NSP, PREC, MODE, PART, false>(kp, count, s);
+    if (kp.transport == LBFD_MIXTURE_AVERAGED) return launch_range_t<Q, NSP, PREC, MODE, true>(kp, count, s);
+    return launch_range_t<Q, NSP, PREC, MODE, false>(kp, count, s);
 }
 
 template <int Q, int NSP, int PREC, int MODE>
 hipError_t launch_pair(const KParams &kp, const Streams &st)
 {
-    // st.part 0: every launch; 1: interior tiles only; 2: boundary blocks,
-    // image points and outlet; 3: the chemistry launch only
+    // st.part 0: every launch; 1: the tiles; 2: the boundary blocks (D2Q9)
+    // and the outlet; the image points run with the launch that reads them;
+    // 3: the chemistry launch only
     const long long nbb = kp.boundary_blocks, nti = kp.interior_blocks;
     hipError_t e = hipSuccess;
     if constexpr (chem_pass(NSP)) {
@@ -1729,18 +1935,11 @@ hipError_t launch_pair(const KParams &kp, const Streams &st)
             return e;
     }
     if (st.part == 3) return hipSuccess;
-    if (kp.bimg != nullptr && kp.n_img > 0 && st.part != 1)
+    if (kp.bimg != nullptr && kp.n_img > 0 && st.part != (Lat<Q>::D == 2 ? 1 : 2))
         if ((e = launch_images<NSP, PREC>(kp, st.main)) != hipSuccess) return e;
-    if constexpr (fused_step(Q)) {
-        const long long begin = st.part == 1 ? nbb : 0;
-        const long long count = st.part == 1 ? nti : st.part == 2 ? nbb : nbb + nti;
-        if ((e = launch_range<Q, NSP, PREC, MODE, 0>(kp, begin, count, st.main)) != hipSuccess) return e;
-    } else {
-        if (st.part != 1 && (e = launch_range<Q, NSP, PREC, MODE, 2>(kp, 0, nbb, st.main)) != hipSuccess)
-            return e;
-        if (st.part != 2 && (e = launch_range<Q, NSP, PREC, MODE, 1>(kp, nbb, nti, st.main)) != hipSuccess)
-            return e;
-    }
+    const long long begin = st.part == 1 ? nbb : 0;
+    const long long count = st.part == 1 ? nti : st.part == 2 ? nbb : nbb + nti;
+    if ((e = launch_range<Q, NSP, PREC, MODE>(kp, begin, count, st.main)) != hipSuccess) return e;
     if (Lat<Q>::D == 3 && MODE != kModeFields && st.part != 1 && kp.n_boundary > 0 &&
         (kp.face[0] == LBFD_FACE_OUTFLOW || kp.face[1] == LBFD_FACE_OUTFLOW)) {
         const unsigned no = (unsigned)((2LL * kp.ny * kp.nz + kBlock - 1) / kBlock);
