@@ -158,7 +158,8 @@ struct KParams {
     // of 256 boundary cells, then interior_blocks tiles of tiles_x x tiles_y
     // x (nz / tile depth); a launch covers blocks [block_begin, + gridDim.x)
     long long boundary_blocks, interior_blocks, block_begin;
-    int tiles_x, tiles_y;
+    int tiles_x, tiles_y, tiles_z;
+    int tile_band;        // D3Q27: tiles in y of a band of the tile order
     const double *wall_T;
     const void *pop_in;   // post-collision populations of the previous level
     void *pop_out;        // post-collision populations of this level
