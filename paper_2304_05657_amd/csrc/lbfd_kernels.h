@@ -67,6 +67,42 @@ __device__ __forceinline__ void sto(void *base, uint32_t byte_off, T v)
     *(T *)((char *)base + byte_off) = v;
 }
 
+// A uniform base address in scalar registers that steps from plane to plane
+// of a field (one field of a structure of arrays after another).  step() and
+// the empty asm keep the planes' addresses from being formed all at once: left
+// to itself the compiler holds the 27 populations' 64-bit bases (three times
+// over, for the interior, boundary and curved-wall pulls) in scalar registers,
+// spills them into vector lanes -- 850 of the 7,200 vector instructions of the
+// 3-D FP64 step -- and, in one instantiation, gave a spilled base's register to
+// another value before it was stored.
+template <class T> struct PlanePtr {
+    typedef __attribute__((address_space(1))) T G;
+    G *p;
+    __device__ __forceinline__ PlanePtr(const void *base, long long planes, long long N)
+        : p((G *)base + planes * N)
+    {
+        asm volatile("" : "+s"(p));
+    }
+    __device__ __forceinline__ void step(long long n)
+    {
+        p += n;
+        asm volatile("" : "+s"(p));
+    }
+    // the element at a 32-bit byte offset
+    __device__ __forceinline__ G *at(uint32_t byte_off) const
+    {
+        return (G *)((__attribute__((address_space(1))) char *)p + byte_off);
+    }
+};
+template <bool STREAM, class G>
+__device__ __forceinline__ auto load_global(const G *p)
+{
+    if constexpr (STREAM)
+        return __builtin_nontemporal_load(p);
+    else
+        return *p;
+}
+
 // Populations in 3-D pass through L2 without displacing the scalars, whose
 // stencil rows and planes are read again: each population is read by one cell
 // and written once, so its loads and stores are marked nontemporal.  In half
@@ -75,15 +111,6 @@ __device__ __forceinline__ void sto(void *base, uint32_t byte_off, T v)
 // 256 x 256 x 128 packing, FP64, 1888 -> 1847 us a step; 256 x 128 x 128 with
 // 9 species, FP64, 1404 -> 1378 us; 161 x 99 x 83, half, 179 -> 184 us.
 template <int Q, int PREC> constexpr bool pop_stream() { return Q == 27 && PREC != LBFD_MIXED_FP16; }
-template <bool STREAM, class T>
-__device__ __forceinline__ T load_pop(const T *p)
-{
-    if constexpr (STREAM)
-        return __builtin_nontemporal_load(p);
-    else
-        return *p;
-}
-
 // Populations: FP64 stores g; mixed stores g / (w_i cs^2) (deviation from
 // the lattice weights, scaled to comparable magnitude across directions).
 template <int Q, int PREC, int I>
@@ -107,14 +134,32 @@ template <int Q, int PREC, int I>
 __device__ __forceinline__ void pop_store(void *base, long long N, uint32_t idx, typename Prec<PREC>::calc v)
 {
     using T = typename Prec<PREC>::pop;
-    T *p = (T *)((char *)base + (size_t)I * (size_t)N * sizeof(T)) + idx;
+    char *b = (char *)base + (size_t)I * (size_t)N * sizeof(T);
+    const uint32_t off = idx * (uint32_t)sizeof(T);
+    if constexpr (PREC == LBFD_FP64) {
+        sto<double>(b, off, v);
+    } else if constexpr (PREC == LBFD_MIXED_FP32) {
+        constexpr float s = (float)(1.0 / (Lat<Q>::w(I) * kCs2));
+        sto<float>(b, off, v * s);
+    } else {
+        constexpr float s = (float)(1.0 / (Lat<Q>::w(I) * kCs2));
+        sto<__half>(b, off, __float2half_rn(v * s));
+    }
+}
+
+// Population I of a cell stored at q, scaled (pop_store on a plane).
+template <int Q, int PREC, int I>
+__device__ __forceinline__ void plane_store(__attribute__((address_space(1))) typename Prec<PREC>::pop *q,
+                                            typename Prec<PREC>::calc v)
+{
+    using T = typename Prec<PREC>::pop;
     constexpr float s = (float)(1.0 / (Lat<Q>::w(I) * kCs2));
     if constexpr (PREC == LBFD_MIXED_FP16)
-        *p = __float2half_rn(v * s);
+        *(__attribute__((address_space(1))) unsigned short *)q = __builtin_bit_cast(unsigned short, __float2half_rn(v * s));
     else if constexpr (pop_stream<Q, PREC>())
-        __builtin_nontemporal_store(PREC == LBFD_FP64 ? (T)v : (T)(v * s), p);
+        __builtin_nontemporal_store(PREC == LBFD_FP64 ? (T)v : (T)(v * s), q);
     else
-        *p = PREC == LBFD_FP64 ? (T)v : (T)(v * s);
+        *q = PREC == LBFD_FP64 ? (T)v : (T)(v * s);
 }
 
 // compile-time loop
@@ -950,13 +995,31 @@ __device__ __forceinline__ void finish_cell(const KParams &P, long long idx, con
     }
 
     if constexpr (MODE != kModeFields) {
-        sfor<0, Q>([&](auto I) { pop_store<Q, PREC, decltype(I)::value>(P.pop_out, P.N, idx, h[decltype(I)::value]); });
-        char *so = (char *)P.sc_out;
-        const size_t fstride = (size_t)P.N * sizeof(S);
         const uint32_t off = (uint32_t)idx * (uint32_t)sizeof(S);
-        sto<S>(so, off, (S)Tn);
+        if constexpr (L::D == 3) {
+            using T = typename Prec<PREC>::pop;
+            PlanePtr<T> pl(P.pop_out, 0, P.N);
+            sfor<0, Q>([&](auto I) {
+                constexpr int i = decltype(I)::value;
+                plane_store<Q, PREC, i>(pl.at((uint32_t)idx * (uint32_t)sizeof(T)), h[i]);
+                pl.step(P.N);
+            });
+            PlanePtr<S> ps(P.sc_out, 0, P.N);
+            *ps.at(off) = (S)Tn;
 #pragma unroll
-        for (int k = 0; k < NSP; ++k) sto<S>(so + (size_t)(1 + k) * fstride, off, (S)Yn[k]);
+            for (int k = 0; k < NSP; ++k) {
+                ps.step(P.N);
+                *ps.at(off) = (S)Yn[k];
+            }
+        } else {
+            sfor<0, Q>(
+                [&](auto I) { pop_store<Q, PREC, decltype(I)::value>(P.pop_out, P.N, idx, h[decltype(I)::value]); });
+            char *so = (char *)P.sc_out;
+            const size_t fstride = (size_t)P.N * sizeof(S);
+            sto<S>(so, off, (S)Tn);
+#pragma unroll
+            for (int k = 0; k < NSP; ++k) sto<S>(so + (size_t)(1 + k) * fstride, off, (S)Yn[k]);
+        }
     } else {
         P.fields[idx] = (double)rho;
         P.fields[P.N + idx] = (double)u[0];
@@ -986,26 +1049,29 @@ __device__ __forceinline__ void tile_pull(const KParams &P, int x, int y, int z,
     using T = typename Prec<PREC>::pop;
     using L = Lat<Q>;
     constexpr bool kStream = pop_stream<Q, PREC>();
+    using R = std::conditional_t<PREC == LBFD_MIXED_FP16, unsigned short, T>;  // as loaded
     // wrapped neighbour coordinates (a wrapped source beyond a face that is
-    // not periodic is never read: its code is not kPullFluid)
-    const int xs[3] = {x == 0 ? P.nx - 1 : x - 1, x, x == P.nx - 1 ? 0 : x + 1};
+    // not periodic is never read: its code is not kPullFluid), as byte offsets
+    // in a population's plane: three along the lane's row, nine rows
+    constexpr uint32_t kB = sizeof(T);
+    const uint32_t xs[3] = {kB * (uint32_t)(x == 0 ? P.nx - 1 : x - 1), kB * (uint32_t)x,
+                            kB * (uint32_t)(x == P.nx - 1 ? 0 : x + 1)};
     const int ys[3] = {y == 0 ? P.ny - 1 : y - 1, y, y == P.ny - 1 ? 0 : y + 1};
     const int zs[3] = {z == 0 ? P.nz - 1 : z - 1, z, z == P.nz - 1 ? 0 : z + 1};
-    // population i of the cell at neighbour offset (ox, oy, oz), as stored
-    auto at = [&](int i, int ox, int oy, int oz) -> const T * {
-        const long long row = ((long long)zs[1 + oz] * P.ny + ys[1 + oy]) * P.nx;
-        return (const T *)P.pop_in + ((long long)i * P.N + row) + (uint32_t)xs[1 + ox];
+    auto off = [&](int ox, int oy, int oz) -> uint32_t {
+        return (uint32_t)((zs[1 + oz] * P.ny + ys[1 + oy]) * P.nx) * kB + xs[1 + ox];
     };
-    auto raw = [](T v) -> C {
+    const uint32_t own = off(0, 0, 0);
+    auto raw = [](R v) -> C {
         if constexpr (PREC == LBFD_MIXED_FP16)
-            return __half2float(v);
+            return __half2float(__builtin_bit_cast(__half, v));
         else
             return v;
     };
     auto scale = [](auto I) -> C {
         return PREC == LBFD_FP64 ? (C)1 : (C)(float)(L::w(decltype(I)::value) * kCs2);
     };
-    auto widen = [&](T v, auto I) -> C {
+    auto widen = [&](R v, auto I) -> C {
         if constexpr (PREC == LBFD_FP64)
             return v;
         else
@@ -1029,48 +1095,58 @@ __device__ __forceinline__ void tile_pull(const KParams &P, int x, int y, int z,
     };
     C v[Q];
     if (!__any(bnd)) {
+        PlanePtr<const R> pl(P.pop_in, 0, P.N);
         sfor<0, Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
-            v[i] = raw(load_pop<kStream>(at(i, -L::cx(i), -L::cy(i), -L::cz(i))));
+            v[i] = raw(load_global<kStream>(pl.at(off(-L::cx(i), -L::cy(i), -L::cz(i)))));
             g[i] = PREC == LBFD_FP64 ? v[i] : v[i] * scale(I);
+            pl.step(P.N);
         });
         momentum([&](auto I) { return v[decltype(I)::value]; }, scale);
         return;
     }
-    sfor<0, Q>([&](auto I) {
-        constexpr int i = decltype(I)::value;
-        const T *src = at(i, -L::cx(i), -L::cy(i), -L::cz(i));
-        const T *own = at(Q - 1 - i, 0, 0, 0);
-        v[i] = raw(load_pop<kStream>(decode_pull_kind(pcode, i) == kPullFluid ? src : own));
-        g[i] = PREC == LBFD_FP64 ? v[i] : v[i] * scale(I);
-    });
+    {
+        PlanePtr<const R> pl(P.pop_in, 0, P.N), po(P.pop_in, Q - 1, P.N);  // directions i and opposite
+        sfor<0, Q>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            const auto *src = pl.at(off(-L::cx(i), -L::cy(i), -L::cz(i))), *opp = po.at(own);
+            v[i] = raw(load_global<kStream>(decode_pull_kind(pcode, i) == kPullFluid ? src : opp));
+            g[i] = PREC == LBFD_FP64 ? v[i] : v[i] * scale(I);
+            pl.step(P.N);
+            po.step(-P.N);
+        });
+    }
     if (__any((pcode & 0xaaaaaaaaaaaaaaaaull) != 0)) {
         // inlets (Eq. 31: + 2 w_I rho_in c_I.u_in; an x face carries the
-        // per-cell profile indexed by the cell's (y, z)) and outlets (the
-        // value kept in the outlet buffer)
-        const long long s3 = (long long)P.ny * P.nz;
+        // per-cell profile indexed by the cell's (y, z), the same for a wave)
+        // and outlets (the value kept in the outlet buffer)
+        const long long s3 = (long long)P.ny * P.nz, o = (long long)z * P.ny + y;
+        const bool in0 = x == 0 && P.face[0] == LBFD_FACE_INFLOW, in1 = x == P.nx - 1 && P.face[1] == LBFD_FACE_INFLOW;
+        double p0[3], p1[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            p0[d] = P.inflow_u[d * s3 + o];
+            p1[d] = P.inflow_u[(3 + d) * s3 + o];
+        }
         sfor<0, Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
             if constexpr (i != (Q - 1) / 2) {
                 constexpr int cx = L::cx(i), cy = L::cy(i), cz = L::cz(i);
                 const int kind = decode_pull_kind(pcode, i);
-                const bool inflow = kind == kPullInflow, outlet = kind == kPullOutlet;
+                const bool inflow = kind == kPullInflow;
                 if (__any(inflow)) {
-                    const int f = (cx == 1 && x == 0 && P.face[0] == LBFD_FACE_INFLOW)               ? 0
-                                  : (cx == -1 && x == P.nx - 1 && P.face[1] == LBFD_FACE_INFLOW) ? 1
-                                                                                                 : -1;
-                    const bool prof = inflow && f >= 0;
-                    const double *ub = prof ? P.inflow_u : kZeroEntry;
-                    const long long o = prof ? 3 * s3 * f + (long long)z * P.ny + y : 0;
-                    const double ux = ub[o], uy = ub[prof ? o + s3 : 0], uz = ub[prof ? o + 2 * s3 : 0];
-                    const double cu =
-                        prof ? cx * ux + cy * uy + cz * uz : cx * P.u_in[0] + cy * P.u_in[1] + cz * P.u_in[2];
+                    const double cu0 = cx * p0[0] + cy * p0[1] + cz * p0[2], cu1 = cx * p1[0] + cy * p1[1] + cz * p1[2];
+                    double cu = cx * P.u_in[0] + cy * P.u_in[1] + cz * P.u_in[2];
+                    if constexpr (cx == 1) cu = in0 ? cu0 : cu;
+                    if constexpr (cx == -1) cu = in1 ? cu1 : cu;
                     g[i] = inflow ? g[i] + (C)(2.0 * L::w(i) * P.rho_in * cu) : g[i];
                 }
-                if (__any(outlet)) {
-                    const double *ob = outlet ? P.outlet : kZeroEntry;
-                    const C ov = (C)ob[outlet ? outlet_index(P, cx < 0 ? 1 : 0, i, Q, y, z) : 0];
-                    g[i] = outlet ? ov : g[i];
+                if constexpr (cx != 0) {
+                    const bool outlet = kind == kPullOutlet;
+                    if (__any(outlet)) {
+                        const C ov = (C)P.outlet[outlet_index(P, cx < 0 ? 1 : 0, i, Q, y, z)];
+                        g[i] = outlet ? ov : g[i];
+                    }
                 }
             }
         });
@@ -1079,13 +1155,15 @@ __device__ __forceinline__ void tile_pull(const KParams &P, int x, int y, int z,
         // linearly interpolated bounce-back (post-collision form) for a
         // wall met at the fraction q of the link toward it (direction OPP)
         if (P.bq != nullptr) {
+            PlanePtr<const R> pl(P.pop_in, 0, P.N), po(P.pop_in, Q - 1, P.N);
+            PlanePtr<const float> pq(P.bq, 0, P.n_boundary);
+            const uint32_t tq = (uint32_t)tb * (uint32_t)sizeof(float);
             sfor<0, Q>([&](auto I) {
                 constexpr int i = decltype(I)::value;
                 constexpr int opp = Q - 1 - i;
                 if constexpr (i != opp) {
-                    const bool wall = decode_pull_kind(pcode, i) == kPullBounce;
-                    const float qraw = P.bq[i * P.n_boundary + tb];
-                    const float qs = wall ? qraw : __builtin_nanf("");
+                    const float qraw = *pq.at(tq);
+                    const float qs = decode_pull_kind(pcode, i) == kPullBounce ? qraw : __builtin_nanf("");
                     const bool interp = qs == qs;
                     if (__any(interp)) {
                         const C q2 = (C)2 * (C)qs;  // weights in the arithmetic precision
@@ -1093,15 +1171,18 @@ __device__ __forceinline__ void tile_pull(const KParams &P, int x, int y, int z,
                         // direction OPP (when it is a fluid cell)
                         const bool near_half = qs < 0.5f;
                         const bool use_far = interp && near_half && decode_pull_kind(pcode, opp) == kPullFluid;
-                        const T *far = at(opp, L::cx(i), L::cy(i), L::cz(i)), *own = at(opp, 0, 0, 0);
-                        const C gfar = widen(*(use_far ? far : own), I);
-                        const C gown = widen(*at(i, 0, 0, 0), I);
+                        const uint32_t far = off(L::cx(i), L::cy(i), L::cz(i));
+                        const C gfar = widen(*po.at(use_far ? far : own), I);
+                        const C gown = widen(*pl.at(own), I);
                         const C lo = q2 * g[i] + ((C)1 - q2) * gfar;
                         const C iq = (C)1 / (interp && !near_half ? q2 : (C)1);
                         const C hi = g[i] * iq + (q2 - (C)1) * iq * gown;
                         g[i] = use_far ? lo : (interp && !near_half) ? hi : g[i];
                     }
                 }
+                pl.step(P.N);
+                po.step(-P.N);
+                pq.step(P.n_boundary);
             });
         }
     }
@@ -1151,13 +1232,30 @@ __device__ __forceinline__ void tile_stencil(const KParams &P, int d, int x, int
     if (__any(s20 != 0)) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int img = (int)(s20 >> (5 * j + 3)) & 3;
+            // the two bits of the image: self, cell, mirror, same
+            const bool b0 = (s20 >> (5 * j + 3)) & 1u, b1 = (s20 >> (5 * j + 4)) & 1u;
             const int same = off[j < 2 ? 1 : 2], mirror = off[j < 2 ? 2 : 1];
-            at[j] = img == kImgSelf ? off[j] : img == kImgMirror ? mirror : img == kImgSame ? same : 0;
+            const int lo = b0 ? 0 : off[j], hi = b0 ? same : mirror;
+            at[j] = b1 ? hi : lo;
         }
     }
+    {
+        using S = typename Prec<PREC>::scal;
+        uint32_t bo[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) load_point<NSP, PREC>(P, idx + at[j], pv[j]);
+        for (int j = 0; j < 4; ++j) bo[j] = (uint32_t)((int)idx + at[j]) * (uint32_t)sizeof(S);
+        PlanePtr<const S> pl(P.sc_in, 0, P.N);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) pv[j].T = *pl.at(bo[j]);
+#pragma unroll
+        for (int k = 0; k < NSP; ++k) {
+            pl.step(P.N);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) pv[j].Y[k] = *pl.at(bo[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) pv[j].rho = density<NSP>(P, pv[j].T, pv[j].Y);
+    }
     const C r0 = density_rcp<NSP>(P, pv[0].T, pv[0].Y);
     const unsigned kinds = s20 & 0x39ce7u;  // the kinds of the four slots
     near = kinds != 0;
