@@ -97,6 +97,7 @@ struct lbfd_ctx {
     lbfd_params p;
     lbfd_reaction rx[LBFD_MAX_REACTIONS];
     int Q, D, nsp, prec;
+    int device = 0;  // the GPU the context lives on
     long long N;
     hipStream_t stream;
     Streams streams = {nullptr, 0};
@@ -540,7 +541,6 @@ static KParams make_kparams(const lbfd_ctx *c)
     k.n_sup = c->n_sup;
     k.sup_idx = c->sup_idx;
     k.sup_val = c->sup_val;
-    k.fields = c->fields;
     k.partials = c->partials;
     k.rx = c->rx_dev;
     k.rxk = c->rxk_dev;
@@ -792,6 +792,7 @@ int lbfd_init(const lbfd_params *p, const uint8_t *mask, const double *wall_T, c
     TRY_OR_FREE(upload_scalars(c, c->sc[0], T0, Y0));
     TRY_OR_FREE(upload_scalars(c, c->sc[1], T0, Y0));
 
+    HIP_OR_FREE(hipGetDevice(&c->device));
     c->streams.main = c->stream;
     c->base = make_kparams(c);
     TRY_OR_FREE(upload_reactions(c));
@@ -896,35 +897,62 @@ int lbfd_sync(lbfd_ctx *c)
 
 int64_t lbfd_level(const lbfd_ctx *c) { return c ? c->level : -1; }
 
-// Evaluate the current level without advancing it: fields and diagnostics.
-static int evaluate(lbfd_ctx *c)
+// The launch parameters that evaluate the current level without advancing it.
+static KParams level_params(const lbfd_ctx *c)
 {
-    if (!c->fields) {
-        if (hipMalloc((void **)&c->fields, (size_t)5 * c->N * sizeof(double)) != hipSuccess) {
-            c->fields = nullptr;
-            return fail(LBFD_ENOMEM, "hipMalloc of the field buffer failed");
-        }
-        c->base.fields = c->fields;
-    }
     KParams k = c->base;
     k.pop_in = c->pop[c->cur];
     k.sc_in = c->sc[c->cur];
     // the next level's scalar buffer holds the chemistry launch's source
     // (it is overwritten by the next step)
     k.sc_out = c->sc[1 - c->cur];
-    HIP_TRY(launch_step(c->Q, c->nsp, c->prec, kModeFields, k, c->streams));
-    HIP_TRY(launch_finalize(c->partials, c->nblocks, c->diag_dev, nullptr, c->level, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    return LBFD_OK;
+    return k;
+}
+
+// A caller's buffer that the fields kernel can write itself: aligned device
+// memory of the context's GPU (other memory the copy engine can reach is
+// filled from the context's own buffer).
+static bool writable_here(const lbfd_ctx *c, const double *p)
+{
+    if (!p) return true;
+    hipPointerAttribute_t a;
+    if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return a.type == hipMemoryTypeDevice && a.device == c->device && ((uintptr_t)p & 7) == 0;
 }
 
 // Fields of the current level into host (dev = false) or device buffers.
+// Device buffers are written by the fields launch itself; a first version
+// evaluated rho, u and P_h with the level's reductions into a buffer of the
+// context and copied five arrays out of it.
 static int read_fields(lbfd_ctx *c, double *rho, double *u, double *T, double *Y, double *Ph, bool dev)
 {
     if (!c) return fail(LBFD_EINVAL, "null context");
-    int rc = evaluate(c);
-    if (rc) return rc;
     const long long N = c->N;
+    const bool direct = dev && writable_here(c, rho) && writable_here(c, u) && writable_here(c, T) &&
+                        writable_here(c, Y) && writable_here(c, Ph);
+    KParams k = level_params(c);
+    if (direct) {
+        k.f_rho = rho;
+        k.f_u = u;
+        k.f_T = T;
+        k.f_Y = Y;
+        k.f_Ph = Ph;
+        HIP_TRY(launch_step(c->Q, c->nsp, c->prec, kModeFields, k, c->streams));
+        HIP_TRY(hipStreamSynchronize(c->stream));
+        return LBFD_OK;
+    }
+    if (!c->fields && hipMalloc((void **)&c->fields, (size_t)5 * N * sizeof(double)) != hipSuccess) {
+        c->fields = nullptr;
+        return fail(LBFD_ENOMEM, "hipMalloc of the field buffer failed");
+    }
+    k.f_rho = c->fields;
+    k.f_u = c->fields + N;
+    k.f_Ph = c->fields + 4 * N;
+    HIP_TRY(launch_step(c->Q, c->nsp, c->prec, kModeFields, k, c->streams));
+    HIP_TRY(hipStreamSynchronize(c->stream));
     const hipMemcpyKind kind = dev ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
     if (rho) HIP_TRY(hipMemcpyAsync(rho, c->fields, N * sizeof(double), kind, c->stream));
     if (u) HIP_TRY(hipMemcpyAsync(u, c->fields + N, (size_t)c->D * N * sizeof(double), kind, c->stream));
@@ -967,8 +995,9 @@ int lbfd_read_fields_dev(lbfd_ctx *c, double *rho, double *u, double *T, double 
 int lbfd_diagnostics(lbfd_ctx *c, lbfd_diag *d)
 {
     if (!c || !d) return fail(LBFD_EINVAL, "null argument");
-    int rc = evaluate(c);
-    if (rc) return rc;
+    HIP_TRY(launch_step(c->Q, c->nsp, c->prec, kModeDiag, level_params(c), c->streams));
+    HIP_TRY(launch_finalize(c->partials, c->nblocks, c->diag_dev, nullptr, c->level, c->stream));
+    HIP_TRY(hipStreamSynchronize(c->stream));
     double a[kNDiag];
     HIP_TRY(hipMemcpy(a, c->diag_dev, sizeof(a), hipMemcpyDeviceToHost));
     d->sum_g = a[kSumG];

@@ -167,7 +167,9 @@ struct KParams {
     void *sc_out;
     double *outlet;       // [2 x faces][Q][ny*nz] post-streaming outlet populations
     double *outlet_un;    // [2 x faces][ny*nz] outward normal velocity of the face cells (this level)
-    double *fields;       // [5][N]: rho, u_x, u_y, u_z, P_h  (fields mode)
+    // fields mode: rho [N], u [dim][N], T [N], Y [n_species][N], P_h [N]
+    // (nullptr: not asked for)
+    double *f_rho, *f_u, *f_T, *f_Y, *f_Ph;
     double *partials;     // [interior_blocks + boundary_blocks][kNDiag]  (diagnostics modes)
     const lbfd_reaction *rx;
     const ChemRx *rxk;  // the same reactions as the chemistry reads them
@@ -190,9 +192,11 @@ struct KParams {
 };
 
 // Launch modes: the step; the step with the reductions of the level; the
-// evaluation of the current level (fields and reductions, nothing of the
-// state written).
-enum { kModeStep = 0, kModeStepDiag = 1, kModeFields = 2 };
+// reductions of the current level; the fields of the current level (neither
+// of the last two writes anything of the state).
+enum { kModeStep = 0, kModeStepDiag = 1, kModeDiag = 2, kModeFields = 3 };
+constexpr bool mode_reduces(int mode) { return mode == kModeStepDiag || mode == kModeDiag; }
+constexpr bool mode_advances(int mode) { return mode == kModeStep || mode == kModeStepDiag; }
 
 // A step is one launch (boundary blocks and tiles), plus the outlet update
 // for D3Q27 with an outflow face, the chemistry and the image points.

@@ -899,7 +899,7 @@ __device__ __forceinline__ void finish_cell(const KParams &P, long long idx, con
     using L = Lat<Q>;
     using C = typename Prec<PREC>::calc;
     using S = typename Prec<PREC>::scal;
-    constexpr bool DIAG = MODE != kModeStep;
+    constexpr bool DIAG = mode_reduces(MODE);
     const C rho = ctr.rho;
     // Arrhenius source (double): computed here, or read back from this
     // step's output scalars where the chemistry launch left it
@@ -935,6 +935,19 @@ __device__ __forceinline__ void finish_cell(const KParams &P, long long idx, con
 #pragma unroll
     for (int k = 0; k < NSP; ++k) Yn[k] = ctr.Y[k] - CY[k] + DtY[k];
     const C Ph = sg + (C)0.5 * rho * (C)kCs2 * Lam;
+
+    if constexpr (MODE == kModeFields) {
+        if (P.f_rho) P.f_rho[idx] = (double)rho;
+        if (P.f_u)
+#pragma unroll
+            for (int d = 0; d < L::D; ++d) P.f_u[d * P.N + idx] = (double)u[d];
+        if (P.f_Ph) P.f_Ph[idx] = (double)Ph;
+        if (P.f_T) P.f_T[idx] = (double)ctr.T;
+        if (P.f_Y)
+#pragma unroll
+            for (int k = 0; k < NSP; ++k) P.f_Y[k * P.N + idx] = (double)ctr.Y[k];
+        return;
+    }
 
     // source Xi_i (Eq. 9) and pre-conditioned populations (Eq. 19)
     const C uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
@@ -994,7 +1007,7 @@ __device__ __forceinline__ void finish_cell(const KParams &P, long long idx, con
         }
     }
 
-    if constexpr (MODE != kModeFields) {
+    if constexpr (mode_advances(MODE)) {
         const uint32_t off = (uint32_t)idx * (uint32_t)sizeof(S);
         if constexpr (L::D == 3) {
             using T = typename Prec<PREC>::pop;
@@ -1020,12 +1033,6 @@ __device__ __forceinline__ void finish_cell(const KParams &P, long long idx, con
 #pragma unroll
             for (int k = 0; k < NSP; ++k) sto<S>(so + (size_t)(1 + k) * fstride, off, (S)Yn[k]);
         }
-    } else {
-        P.fields[idx] = (double)rho;
-        P.fields[P.N + idx] = (double)u[0];
-        P.fields[2 * P.N + idx] = (double)u[1];
-        P.fields[3 * P.N + idx] = (double)u[2];
-        P.fields[4 * P.N + idx] = (double)Ph;
     }
 }
 
@@ -1356,7 +1363,7 @@ __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int
     using L = Lat<Q>;
     using C = typename Prec<PREC>::calc;
     constexpr int D = L::D;
-    constexpr bool DIAG = MODE != kModeStep;
+    constexpr bool DIAG = mode_reduces(MODE);
     constexpr bool ALL = D == 3;  // every fluid cell of the tile
     using TS = TileShape<D>;
     static_assert(FAST || D == 2, "3-D blocks are tiles");
@@ -1600,7 +1607,7 @@ __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int
         for (int k = 0; k < NSP; ++k) diffY[k] *= alpha;
 
         finish_cell<Q, NSP, PREC, MODE, LE>(P, idx, g, ctr, u, m, sg, inv_rc, diffT, diffY, CT, CY, grad, wallq, acc);
-        if constexpr (MODE != kModeFields) {
+        if constexpr (mode_advances(MODE)) {
             if constexpr (!FAST && D == 2) {
                 // outlet (Eq. 32): g_i(r) <- g_i(r-n)(cs - u.n) + g_i(r)(1 - cs + u.n)
                 // for the populations entering through the face, with the
@@ -1639,9 +1646,20 @@ __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int
             }
         }
     } else if constexpr (MODE == kModeFields && FAST) {
-        if (inbox && P.code[idx] == kCodeSolid)
+        // solid cells: their stored T and Y, no flow
+        if (inbox && P.code[idx] == kCodeSolid) {
+            if (P.f_rho) P.f_rho[idx] = 0.0;
+            if (P.f_u)
 #pragma unroll
-            for (int c = 0; c < 5; ++c) P.fields[c * P.N + idx] = 0.0;
+                for (int d = 0; d < D; ++d) P.f_u[d * P.N + idx] = 0.0;
+            if (P.f_Ph) P.f_Ph[idx] = 0.0;
+            using S = typename Prec<PREC>::scal;
+            if (P.f_T) P.f_T[idx] = (double)((const S *)P.sc_in)[idx];
+            if (P.f_Y)
+#pragma unroll
+                for (int k = 0; k < NSP; ++k)
+                    P.f_Y[k * P.N + idx] = (double)((const S *)P.sc_in)[(1 + k) * P.N + idx];
+        }
     }
 
     if constexpr (DIAG) block_reduce_diag(acc, P.partials + slot * kNDiag);
@@ -2066,7 +2084,7 @@ hipError_t launch_pair(const KParams &kp, const Streams &st)
     const long long begin = st.part == 1 ? nbb : 0;
     const long long count = st.part == 1 ? nti : st.part == 2 ? nbb : nbb + nti;
     if ((e = launch_range<Q, NSP, PREC, MODE>(kp, begin, count, st.main)) != hipSuccess) return e;
-    if (Lat<Q>::D == 3 && MODE != kModeFields && st.part != 1 && kp.n_boundary > 0 &&
+    if (Lat<Q>::D == 3 && mode_advances(MODE) && st.part != 1 && kp.n_boundary > 0 &&
         (kp.face[0] == LBFD_FACE_OUTFLOW || kp.face[1] == LBFD_FACE_OUTFLOW)) {
         const unsigned no = (unsigned)((2LL * kp.ny * kp.nz + kBlock - 1) / kBlock);
         outlet_kernel<Q, PREC><<<dim3(no), dim3(kBlock), 0, st.main>>>(kp);
@@ -2081,6 +2099,7 @@ hipError_t launch_step_t(int mode, const KParams &kp, const Streams &st)
     switch (mode) {
     case kModeStep: return launch_pair<Q, NSP, PREC, kModeStep>(kp, st);
     case kModeStepDiag: return launch_pair<Q, NSP, PREC, kModeStepDiag>(kp, st);
+    case kModeDiag: return launch_pair<Q, NSP, PREC, kModeDiag>(kp, st);
     default: return launch_pair<Q, NSP, PREC, kModeFields>(kp, st);
     }
 }

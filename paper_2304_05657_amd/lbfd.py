@@ -363,12 +363,14 @@ class Solver:
         N = self.N
         if device:
             import torch
+            # (u holds three components; the library writes the first dim of them)
             out = {k: torch.empty(n * N, dtype=torch.float64, device="cuda")
-                   for k, n in (("rho", 1), ("u", self.dim), ("T", 1), ("Y", self.nsp), ("Ph", 1))}
+                   for k, n in (("rho", 1), ("u", 3), ("T", 1), ("Y", self.nsp), ("Ph", 1))}
             _check(self._lib, self._lib.lbfd_read_fields_dev(self._h, *(C.c_void_p(out[k].data_ptr())
                                                                       for k in ("rho", "u", "T", "Y", "Ph"))))
-            u3 = torch.zeros((3,) + shp, dtype=torch.float64, device="cuda")
-            u3[: self.dim] = out["u"].reshape((self.dim,) + shp)
+            u3 = out["u"].reshape((3,) + shp)
+            if self.dim < 3:
+                u3[self.dim:] = 0.0
             return {"rho": out["rho"].reshape(shp), "u": u3, "T": out["T"].reshape(shp),
                     "Y": out["Y"].reshape((self.nsp,) + shp), "Ph": out["Ph"].reshape(shp)}
         rho, T, Ph = np.empty(N), np.empty(N), np.empty(N)
