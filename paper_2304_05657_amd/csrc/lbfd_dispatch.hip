@@ -11,31 +11,52 @@ namespace lbfd {
 LBFD_FOR_CONFIGS(X)
 #undef X
 
-// Deterministic final reduction of the block partials (one block); records
-// the first level whose check saw a non-finite value and, with acc, adds
-// coef * out[slot] + shift to *acc.  (A 1024-thread block with wave
-// butterflies measured slower: 13.6 against 7.9 us for 1024 partials.)
-__global__ void __launch_bounds__(kBlock) finalize_kernel(const double *partials, int nblocks, double *out,
-                                                          long long *first_bad, long long level, double *acc,
-                                                          int slot, double coef, double shift)
+// Combine `count` rows of partials, `stride` rows apart from `first` on, in
+// one block (a fixed order, so the result is deterministic); thread 0 holds
+// the result in red[0].
+__device__ __forceinline__ void reduce_rows(const double *first, int count, long long stride,
+                                            double (&red)[kBlock][kNDiag])
 {
-    __shared__ double red[kBlock][kNDiag];
     double a[kNDiag];
     diag_identity(a);
-    for (int b = threadIdx.x; b < nblocks; b += blockDim.x) diag_combine(a, partials + (long long)b * kNDiag);
+    for (int b = threadIdx.x; b < count; b += blockDim.x) diag_combine(a, first + b * stride * kNDiag);
 #pragma unroll
     for (int s = 0; s < kNDiag; ++s) red[threadIdx.x][s] = a[s];
     __syncthreads();
-    for (int stride = blockDim.x / 2; stride >= 1; stride >>= 1) {
-        if ((int)threadIdx.x < stride) {
+    for (int stride2 = blockDim.x / 2; stride2 >= 1; stride2 >>= 1) {
+        if ((int)threadIdx.x < stride2) {
 #pragma unroll
             for (int s = 0; s < kNDiag; ++s) a[s] = red[threadIdx.x][s];
-            diag_combine(a, red[threadIdx.x + stride]);
+            diag_combine(a, red[threadIdx.x + stride2]);
 #pragma unroll
             for (int s = 0; s < kNDiag; ++s) red[threadIdx.x][s] = a[s];
         }
         __syncthreads();
     }
+}
+
+// First stage for many partials: every block reduces kRowsPerGroup rows into
+// the first of them (which only this block reads).
+constexpr int kRowsPerGroup = 256;
+__global__ void __launch_bounds__(kBlock) reduce_partials_kernel(double *partials, int nblocks)
+{
+    __shared__ double red[kBlock][kNDiag];
+    const long long r0 = (long long)blockIdx.x * kRowsPerGroup;
+    double *first = partials + r0 * kNDiag;
+    reduce_rows(first, (int)(nblocks - r0 < kRowsPerGroup ? nblocks - r0 : kRowsPerGroup), 1, red);
+    if (threadIdx.x < kNDiag) first[threadIdx.x] = red[0][threadIdx.x];
+}
+
+// Final reduction of `count` rows of partials, `stride` apart (one block);
+// records the first level whose check saw a non-finite value and, with acc,
+// adds coef * out[slot] + shift to *acc.  (A 1024-thread block with wave
+// butterflies measured slower: 13.6 against 7.9 us for 1024 partials.)
+__global__ void __launch_bounds__(kBlock) finalize_kernel(const double *partials, int count, long long stride,
+                                                          double *out, long long *first_bad, long long level,
+                                                          double *acc, int slot, double coef, double shift)
+{
+    __shared__ double red[kBlock][kNDiag];
+    reduce_rows(partials, count, stride, red);
     if (threadIdx.x == 0) {
 #pragma unroll
         for (int s = 0; s < kNDiag; ++s) out[s] = red[0][s];
@@ -117,10 +138,25 @@ hipError_t launch_inflow_shift(int Q, int prec, const KParams &kp, int face, con
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_finalize(const double *partials, int nblocks, double *out, long long *first_bad,
-                           long long level, hipStream_t s, double *acc, int slot, double a, double b)
+// One block over all rows is bound by its serial walk (155 us for the 32,768
+// rows of a 256 x 256 x 128 box); past kOneStageRows the rows are first
+// reduced in groups (two launches, 6.3 + 4.9 us there; near 2,048 rows one
+// launch takes 10.1 us and the two 5.4 + 4.7).
+constexpr int kOneStageRows = 2048;
+
+hipError_t launch_finalize(double *partials, int nblocks, double *out, long long *first_bad, long long level,
+                           hipStream_t s, double *acc, int slot, double a, double b)
 {
-    finalize_kernel<<<1, kBlock, 0, s>>>(partials, nblocks, out, first_bad, level, acc, slot, a, b);
+    int count = nblocks;
+    long long stride = 1;
+    if (nblocks > kOneStageRows) {
+        count = (nblocks + kRowsPerGroup - 1) / kRowsPerGroup;
+        stride = kRowsPerGroup;
+        reduce_partials_kernel<<<count, kBlock, 0, s>>>(partials, nblocks);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    finalize_kernel<<<1, kBlock, 0, s>>>(partials, count, stride, out, first_bad, level, acc, slot, a, b);
     return hipGetLastError();
 }
 

@@ -225,9 +225,9 @@ hipError_t launch_init(int Q, int nsp, int prec, const KParams &kp, const double
 // Keep the populations entering through inflow face `face` at the current
 // level when its profile changes by -du (lbfd_dispatch.hip).
 hipError_t launch_inflow_shift(int Q, int prec, const KParams &kp, int face, const double *du, hipStream_t s);
-// The final diagnostics from the per-block partials (one block); with acc,
-// also *acc += a * out[slot] + b (an objective's term).
-hipError_t launch_finalize(const double *partials, int nblocks, double *out,
+// The final diagnostics from the per-block partials (whose rows it may
+// overwrite); with acc, also *acc += a * out[slot] + b (an objective's term).
+hipError_t launch_finalize(double *partials, int nblocks, double *out,
                            long long *first_bad, long long level, hipStream_t s, double *acc = nullptr,
                            int slot = 0, double a = 0.0, double b = 0.0);
 bool supported(int Q, int nsp, int prec);

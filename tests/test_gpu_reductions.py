@@ -1,0 +1,29 @@
+"""The diagnostics' final reduction on both sides of its two-stage line
+(2,048 block partials) and with a ragged last group, against the oracle.
+
+Tolerance: sums of up to 1.1e6 positive terms in another order, 1e-16 each
+in a balanced tree, and two steps of rounding: 1e-12 relative."""
+import pytest
+
+from paper_2304_05657_amd import workloads as W
+
+from .gpu_util import need_gpu, oracle_threads, say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("nx,ny", [(1024, 470), (1024, 512), (1000, 1101)])
+def test_diagnostics_of_many_blocks(nx, ny):
+    import oracle
+    from paper_2304_05657_amd.lbfd import Solver
+    need_gpu()
+    p = W.channel_flame(nx=nx, ny=ny, front_x=nx / 3.0)
+    say("diagnostics %dx%d: %d tiles" % (nx, ny, -(-nx // 64) * -(-ny // 4)))
+    g, o = Solver(p), oracle.Oracle(p, threads=oracle_threads())
+    g.step(2)
+    o.step(2)
+    dg, do = g.diagnostics(), o.diagnostics()
+    for k in ("sum_theta", "wall_q", "fuel_rate"):
+        assert abs(dg[k] - do[k]) <= 1e-12 * abs(do[k]), (k, dg[k], do[k])
+    assert dg["nonfinite"] == 0 and dg["max_sumY_err"] < 1e-13
+    assert abs(dg["hrr_max"] - do["hrr_max"]) <= 1e-12 * do["hrr_max"]
