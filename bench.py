@@ -47,7 +47,7 @@ HBM_PEAK_GBS = 8000.0
 VALU_PEAK_TFLOPS = 256 * 4 * 16 * 2 * 2.4e9 / 1e12
 RIDGE = VALU_PEAK_TFLOPS * 1e12 / (HBM_PEAK_GBS * 1e9)  # flop per byte
 # sources that fix what the launches read and write (device code, the
-# host-side launch plan and the boundary-cell list)
+# host-side launch plan and the boundary cells' codes)
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2304_05657_amd", "csrc", f)
                   for f in ("lbfd_kernels.h", "lbfd_internal.h", "lbfd_api.hip", "lbfd_math.h", "lbfd_chemjit.hip")]
 # HBM bytes per launch of a kernel on a workload, from two rocprofv3 --pmc
@@ -208,7 +208,7 @@ def run_gpu(prob, precision: str, steps: int, warmup: int, check_every: int, lin
     # each launch alone, serialised and bracketed by HIP events on the
     # solver's stream (after the timed region; the state advances)
     n_fluid, _ = s.cell_counts()
-    kms_i, kms_b, kms_c = s.time_kernels(steps)
+    kms_i, _, kms_c = s.time_kernels(steps)
     launches = s.step_launches()
     per_fluid = step_bytes_per_fluid(prob, precision)
     sfl = step_flops_per_cell(prob)
@@ -227,12 +227,8 @@ def run_gpu(prob, precision: str, steps: int, warmup: int, check_every: int, lin
         step_fl = sfl
     else:
         step_fl = sfl + cfl
-    if prob.lattice == 9:
-        kernels.append(kernel_record("step_kernel (one launch: boundary and interior cells)", n_fluid,
-                                     (kms_i + kms_b) / steps, n_fluid * step_fl, float(n_fluid * per_fluid + prob.N)))
-    else:
-        kernels.append(kernel_record("step_kernel (tiles, every fluid cell)", n_fluid, kms_i / steps,
-                                     n_fluid * step_fl, float(n_fluid * per_fluid + prob.N)))
+    kernels.append(kernel_record("step_kernel (tiles, every fluid cell)", n_fluid, kms_i / steps,
+                                 n_fluid * step_fl, float(n_fluid * per_fluid + prob.N)))
     dominant = max(kernels, key=lambda k: k["ms_per_launch"])
     f = s.fields()
     fluid = prob.mask == 0

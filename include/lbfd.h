@@ -421,24 +421,21 @@ int lbfd_step_adjoint(lbfd_ctx *c, const double *lam_pop, const double *lam_sc, 
 /* Per-part timing: queue nsteps steps with their parts launched separately
  * on the context stream, each bracketed by HIP events -- the chemistry
  * launch (mechanisms of more than four species; 0 otherwise), the tiles
- * (D2Q9: interior cells; D3Q27: every cell, with the image-point launches)
- * in ms_interior, and D2Q9's boundary cells (with the image-point launches)
- * or D3Q27's outlet launch in ms_boundary -- wait and return their summed
- * durations in milliseconds (ms_chemistry may be NULL).  The state advances
- * exactly as with lbfd_step. */
+ * (every fluid cell, with the image-point launches) in ms_interior, and
+ * D3Q27's outlet launch (0 in D2Q9) in ms_boundary -- wait and return their
+ * summed durations in milliseconds (ms_chemistry may be NULL).  The state
+ * advances exactly as with lbfd_step. */
 int lbfd_time_kernels(lbfd_ctx *c, int64_t nsteps, double *ms_interior, double *ms_boundary,
                       double *ms_chemistry);
 
 /* Cell counts of the context's geometry: fluid cells, and the fluid cells
- * handled by the boundary-cell path (every other fluid cell is interior: all
- * of its pull sources and finite-difference points are fluid cells inside
+ * that are boundary cells (every other fluid cell is interior: all of its pull sources and finite-difference points are fluid cells inside
  * the box). */
 int lbfd_cell_counts(const lbfd_ctx *c, int64_t *n_fluid, int64_t *n_boundary);
 
 /* Kernel launches queued by one lbfd_step level without diagnostics: 1 for
- * the step (one launch covers boundary and interior cells), for D3Q27 with
- * an outflow face one more for the outlet update (Eq. 32); plus three for
- * the chemistry of a
+ * the step (tiles of every fluid cell), for D3Q27 with an outflow face one
+ * more for the outlet update (Eq. 32); plus three for the chemistry of a
  * mechanism of more than four species (clearing the ordering's counters,
  * ordering the fluid cells by their previous sub-step count, the sources),
  * and two for image points.

@@ -109,7 +109,6 @@ struct lbfd_ctx {
     int cur = 0;
     uint8_t *mask = nullptr;
     uint8_t *code = nullptr;
-    int *boundary = nullptr;
     long long n_boundary = 0;
     int *fluid = nullptr;               // fluid-cell list (contexts with a chemistry launch)
     int *chem_order = nullptr;          // its per-step order for the chemistry launch
@@ -118,15 +117,10 @@ struct lbfd_ctx {
     std::vector<int> boundary_host;
     std::vector<uint8_t> mask_host;
     std::vector<double> wall_T_host;
-    int *bsrc = nullptr, *bpt = nullptr;
-    uint8_t *bwk = nullptr;
-    double *btw = nullptr;
-    unsigned long long *bcode_pull = nullptr, *bcode_st = nullptr;  // compact codes of the same descriptors
     double *face_Td = nullptr;                                         // face_T in device memory
-    ulonglong2 *cell_code = nullptr;  // [N] the codes by cell (D3Q27)
-    int *bslot = nullptr;             // [N] position in the boundary list (D3Q27 with curved walls)
+    ulonglong2 *cell_code = nullptr;  // [N] the boundary cells' pull and stencil codes
+    int *bslot = nullptr;             // [N] position in the boundary list (with curved walls)
     char chem_msg[512] = "";  // which chemistry kernel runs, or why the specialised one does not
-    int nblocks_interior = 0;
     double *wall_T = nullptr;
     double *outlet = nullptr;
     double *outlet_un = nullptr;
@@ -162,11 +156,10 @@ struct lbfd_ctx {
 static void free_ctx(lbfd_ctx *c)
 {
     if (!c) return;
-    void *ptrs[] = {c->pop[0], c->pop[1], c->sc[0], c->sc[1], c->mask, c->code, c->boundary, c->bsrc, c->bpt, c->bwk,
-                    c->btw, c->wall_T, c->outlet, c->outlet_un, c->inflow_u, c->inflow_du, c->bq,
-                    c->bimg, c->img_rng, c->img_idx, c->img_w, c->img_val, c->sup_idx, c->sup_val,
+    void *ptrs[] = {c->pop[0], c->pop[1], c->sc[0], c->sc[1], c->mask, c->code, c->wall_T, c->outlet, c->outlet_un,
+                    c->inflow_u, c->inflow_du, c->bq, c->bimg, c->img_rng, c->img_idx, c->img_w, c->img_val, c->sup_idx, c->sup_val,
                     c->fields, c->partials, c->diag_dev, c->bad_dev, c->rx_dev, c->rxk_dev, c->fluid,
-                    c->chem_order, c->chem_heavy, c->chem_count, c->bcode_pull, c->bcode_st, c->face_Td, c->cell_code, c->bslot};
+                    c->chem_order, c->chem_heavy, c->chem_count, c->face_Td, c->cell_code, c->bslot};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
     delete c;
@@ -241,16 +234,10 @@ static int validate(const lbfd_params *p, const uint8_t *mask, const double *T0,
     return LBFD_OK;
 }
 
-// Brick shape of the boundary-cell list order (x, y[, z]); 0: cell index
-// order.  Measured on MI355X: 16 x 16 bricks shorten the 2-D boundary part,
-// 3-D bricks lengthen it.
-constexpr int kBrick2D[2] = {16, 16};
-constexpr int kBrick3D[3] = {0, 0, 0};
-
 // Cell codes: solid; interior fluid when every pull source (the 3^D - 1
 // neighbours) and every finite-difference point (+-1, +-2 along each axis)
 // lies inside the box without wrapping and is fluid; boundary fluid
-// otherwise.  Returns the boundary cells in the brick order above.
+// otherwise.  Returns the boundary cells in index order.
 static void classify_cells(const lbfd_params &p, const uint8_t *mask, std::vector<uint8_t> &code,
                            std::vector<int> &boundary)
 {
@@ -291,19 +278,6 @@ static void classify_cells(const lbfd_params &p, const uint8_t *mask, std::vecto
                 code[i] = interior ? kCodeInterior : kCodeBoundary;
                 if (!interior) boundary.push_back((int)i);
             }
-    // Order of the boundary-cell list (the cell each thread takes): by
-    // bricks of the box, cell index within a brick, so that the neighbour
-    // gathers of one wave stay in a compact region.  (0: cell index order.)
-    const int bx = D == 2 ? kBrick2D[0] : kBrick3D[0], by = D == 2 ? kBrick2D[1] : kBrick3D[1],
-              bz = D == 2 ? 1 : kBrick3D[2];
-    if (bx > 0) {
-        const long long nbx = (p.nx + bx - 1) / bx, nby = (p.ny + by - 1) / by;
-        auto brick = [&](int i) {
-            const long long x = i % p.nx, y = (i / p.nx) % p.ny, z = i / sz;
-            return ((z / bz) * nby + y / by) * nbx + x / bx;
-        };
-        std::stable_sort(boundary.begin(), boundary.end(), [&](int a, int b) { return brick(a) < brick(b); });
-    }
 }
 
 // Host copy of the kernels' neighbour rule: periodic faces wrap; outside
@@ -349,18 +323,41 @@ static HostNb host_classify(const lbfd_params &p, const uint8_t *mask, const dou
     return r;
 }
 
+// Special pull sources of boundary cells.
+enum { kSrcBounce = -1, kSrcInflow = -2, kSrcOutlet = -3 };
+
 // Per boundary cell: pull source of every direction and, per axis and
 // offset m = -2, -1, 1, 2, the index of the value point (or of the ghost's
 // image: the cell itself for m = +-1 behind a first-neighbour wall, the
 // cell on the other side for m = +-2, clamped to the cell when not fluid,
 // or the first neighbour when the wall is the second), the kind of the wall
-// behind a ghost and its temperature.
+// behind a ghost and its temperature; from these the two compact codes that
+// the kernels read by cell.
 // bit f set for a periodic face f
 static unsigned periodic_bits(const lbfd_params &p)
 {
     unsigned b = 0;
     for (int f = 0; f < 6; ++f) b |= p.face[f] == LBFD_FACE_PERIODIC ? 1u << f : 0u;
     return b;
+}
+
+// The boundary cells' codes to their cells on the device.
+static int upload_codes(lbfd_ctx *c, const std::vector<unsigned long long> &pull,
+                        const std::vector<unsigned long long> &st)
+{
+    const size_t nb = pull.size(), b = nb * sizeof(unsigned long long);
+    char *tmp = nullptr;
+    if (hipMalloc((void **)&tmp, 2 * b + nb * sizeof(int)) != hipSuccess)
+        return fail(LBFD_ENOMEM, "hipMalloc of the boundary codes failed");
+    unsigned long long *dp = (unsigned long long *)tmp, *ds = dp + nb;
+    int *db = (int *)(ds + nb);
+    hipError_t e = hipMemcpy(dp, pull.data(), b, hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(ds, st.data(), b, hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(db, c->boundary_host.data(), nb * sizeof(int), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = launch_cell_codes(db, dp, ds, (long long)nb, c->cell_code, c->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    (void)hipFree(tmp);
+    return e == hipSuccess ? LBFD_OK : fail(LBFD_EDEVICE, "upload of the boundary codes failed: %s", hipGetErrorString(e));
 }
 
 static int build_descriptors(lbfd_ctx *c)
@@ -422,8 +419,8 @@ static int build_descriptors(lbfd_ctx *c)
             }
         }
     }
-    // the compact codes of the same descriptors (what the kernels without
-    // curved-wall links read), each decoded entry checked against them
+    // the compact codes of the same descriptors, each decoded entry checked
+    // against them
     std::vector<unsigned long long> pcode((size_t)nb, 0ull), scode((size_t)nb, 0ull);
     for (long long t = 0; t < nb; ++t) {
         const long long idx = c->boundary_host[t];
@@ -463,21 +460,9 @@ static int build_descriptors(lbfd_ctx *c)
         pcode[t] = pc;
         scode[t] = sc;
     }
-    HIP_TRY(hipMemcpy(c->bcode_pull, pcode.data(), pcode.size() * sizeof(unsigned long long), hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(c->bcode_st, scode.data(), scode.size() * sizeof(unsigned long long), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(c->face_Td, p.face_T, sizeof(p.face_T), hipMemcpyHostToDevice));
     c->bwk_host = wk;
-    if (D == 3) {
-        // 3-D tiles read the codes by cell
-        HIP_TRY(launch_cell_codes(c->boundary, c->bcode_pull, c->bcode_st, nb, c->cell_code, c->stream));
-        HIP_TRY(hipStreamSynchronize(c->stream));
-        return LBFD_OK;
-    }
-    HIP_TRY(hipMemcpy(c->bsrc, src.data(), src.size() * sizeof(int), hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(c->bpt, pt.data(), pt.size() * sizeof(int), hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(c->bwk, wk.data(), wk.size(), hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(c->btw, tw.data(), tw.size() * sizeof(double), hipMemcpyHostToDevice));
-    return LBFD_OK;
+    return upload_codes(c, pcode, scode);
 }
 
 static KParams make_kparams(const lbfd_ctx *c)
@@ -495,16 +480,13 @@ static KParams make_kparams(const lbfd_ctx *c)
     }
     k.mask = c->mask;
     k.code = c->code;
-    k.boundary = c->boundary;
     k.n_boundary = c->n_boundary;
     k.fluid = c->fluid;
     k.n_fluid = c->n_fluid;
     k.chem_order = c->chem_order;
     k.chem_heavy = c->chem_heavy;
     k.chem_count = c->chem_count;
-    k.boundary_blocks = c->nblocks - c->nblocks_interior;
-    k.interior_blocks = c->nblocks_interior;
-    k.block_begin = 0;
+    k.nblocks = c->nblocks;
     k.tiles_x = (int)c->grid.x;
     k.tiles_y = (int)c->grid.y;
     k.tiles_z = (int)c->grid.z;
@@ -516,16 +498,10 @@ static KParams make_kparams(const lbfd_ctx *c)
     // 1404 / 1430 us.
     const long long band_row = 7LL * 2 * p.nx * (1 + c->nsp) * (long long)sc_elem_size(c->prec);
     k.tile_band = (int)std::min<long long>(16, std::max<long long>(1, (2LL << 20) / band_row));
-    k.bsrc = c->bsrc;
-    k.bcode_pull = c->bcode_pull;
-    k.bcode_st = c->bcode_st;
     k.face_Td = c->face_Td;
     k.cell_code = c->cell_code;
     k.bslot = c->bslot;
     k.periodic_bits = periodic_bits(c->p);
-    k.bpt = c->bpt;
-    k.bwk = c->bwk;
-    k.btw = c->btw;
     k.wall_T = c->wall_T;
     k.outlet = c->outlet;
     k.outlet_un = c->outlet_un;
@@ -668,7 +644,7 @@ int lbfd_init(const lbfd_params *p, const uint8_t *mask, const double *wall_T, c
     const size_t sc_bytes = (size_t)(1 + c->nsp) * N * sc_elem_size(c->prec);
     c->outlet_n = (size_t)2 * c->Q * p->ny * p->nz;
     if (c->D == 2) {
-        c->block = dim3(64, 4, 1);
+        c->block = dim3(16, 16, 1);
     } else {
         c->block = dim3(64, 2, 2);
     }
@@ -683,11 +659,7 @@ int lbfd_init(const lbfd_params *p, const uint8_t *mask, const double *wall_T, c
     classify_cells(*p, mask, code, boundary);
     c->n_boundary = (long long)boundary.size();
     for (long long i = 0; i < c->N; ++i) c->n_fluid += mask[i] == LBFD_FLUID;
-    c->nblocks_interior = c->grid.x * c->grid.y * c->grid.z;
-    // boundary blocks padded to a multiple of 8 (one per XCD in turn), so
-    // that the interior tiles after them start on XCD 0
-    // (3-D tiles cover every fluid cell: no boundary blocks)
-    c->nblocks = c->nblocks_interior + (c->D == 2 ? (int)(((c->n_boundary + kBlock - 1) / kBlock + 7) / 8 * 8) : 0);
+    c->nblocks = c->grid.x * c->grid.y * c->grid.z;
 
 #define ALLOC(ptr, bytes)                                                                   \
     do {                                                                                    \
@@ -704,21 +676,8 @@ int lbfd_init(const lbfd_params *p, const uint8_t *mask, const double *wall_T, c
     ALLOC(c->sc[1], sc_bytes);
     ALLOC(c->mask, N);
     ALLOC(c->code, N);
-    ALLOC(c->boundary, sizeof(int) * (boundary.empty() ? 1 : boundary.size()));
-    {
-        const size_t nbd = boundary.empty() ? 1 : boundary.size();
-        if (c->D == 2) {
-            ALLOC(c->bsrc, sizeof(int) * c->Q * nbd);
-            ALLOC(c->bpt, sizeof(int) * 12 * nbd);
-            ALLOC(c->bwk, 12 * nbd);
-            ALLOC(c->btw, sizeof(double) * 12 * nbd);
-        } else {
-            ALLOC(c->cell_code, sizeof(ulonglong2) * (size_t)N);
-        }
-        ALLOC(c->bcode_pull, sizeof(unsigned long long) * nbd);
-        ALLOC(c->bcode_st, sizeof(unsigned long long) * nbd);
-        ALLOC(c->face_Td, sizeof(double) * 6);
-    }
+    ALLOC(c->cell_code, sizeof(ulonglong2) * N);
+    ALLOC(c->face_Td, sizeof(double) * 6);
     ALLOC(c->wall_T, N * sizeof(double));
     ALLOC(c->outlet, c->outlet_n * sizeof(double));
     ALLOC(c->outlet_un, (size_t)2 * p->ny * p->nz * sizeof(double));
@@ -767,8 +726,6 @@ int lbfd_init(const lbfd_params *p, const uint8_t *mask, const double *wall_T, c
     }
     HIP_OR_FREE(hipMemcpy(c->mask, mask, N, hipMemcpyHostToDevice));
     HIP_OR_FREE(hipMemcpy(c->code, code.data(), N, hipMemcpyHostToDevice));
-    if (!boundary.empty())
-        HIP_OR_FREE(hipMemcpy(c->boundary, boundary.data(), sizeof(int) * boundary.size(), hipMemcpyHostToDevice));
     c->mask_host.assign(mask, mask + N);
     if (wall_T)
         c->wall_T_host.assign(wall_T, wall_T + N);
@@ -1019,11 +976,11 @@ int lbfd_diagnostics(lbfd_ctx *c, lbfd_diag *d)
     return LBFD_OK;
 }
 
-// The boundary-list position of every cell on the device (3-D contexts with
+// The boundary-list position of every cell on the device (contexts with
 // curved walls; the list does not change over a context's life).
 static int upload_slots(lbfd_ctx *c, const std::vector<int> &slot)
 {
-    if (c->D == 2 || c->bslot) return LBFD_OK;
+    if (c->bslot) return LBFD_OK;
     if (hipMalloc((void **)&c->bslot, slot.size() * sizeof(int)) != hipSuccess) {
         c->bslot = nullptr;
         return fail(LBFD_ENOMEM, "hipMalloc of the boundary positions failed");

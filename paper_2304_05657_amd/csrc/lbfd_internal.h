@@ -25,9 +25,6 @@ enum DiagSlot {
 // finite-difference point is an in-box fluid cell), boundary fluid.
 enum CellCode { kCodeSolid = 0, kCodeInterior = 1, kCodeBoundary = 2 };
 
-// Special pull sources of boundary cells.
-enum { kSrcBounce = -1, kSrcInflow = -2, kSrcOutlet = -3 };
-
 // Kind of what a neighbour coordinate lands on.
 enum NbKind { kFluid = 0, kIso = 1, kAdia = 2, kInflow = 3, kOutflow = 4 };
 
@@ -122,23 +119,15 @@ struct KParams {
     double face_T[6];
     const uint8_t *mask;
     const uint8_t *code;        // CellCode per cell
-    const int *boundary;        // boundary fluid cells, increasing index
-    long long n_boundary;
+    long long n_boundary;       // boundary fluid cells
     const int *fluid;           // every fluid cell, increasing index (chemistry launch)
     int *chem_order;            // [n_fluid] fluid cells in the chemistry launch's order: cells whose last
                                 //   source took few sub-steps first, the others from the back
     unsigned char *chem_heavy;  // [N] the cell's last source took more than kChemLight sub-steps
     int *chem_count;            // [2] cells placed at the front / back by this step's ordering
     long long n_fluid;
-    // per boundary cell t (structure of arrays, stride n_boundary):
-    const int *bsrc;            // [Q][nb] pull source index, or kSrcBounce / kSrcInflow / kSrcOutlet
-    const int *bpt;             // [3*4][nb] finite-difference point (or ghost image) index, axis-major, m = -2,-1,1,2
-    const uint8_t *bwk;         // [3*4][nb] kind of the wall behind a ghost point, kFluid for a plain point
-    const double *btw;          // [3*4][nb] wall temperature of isothermal ghost walls
-    const unsigned long long *bcode_pull;  // [nb] compact pull codes (decode_pull_kind below)
-    const unsigned long long *bcode_st;    // [nb] compact stencil codes (decode_point below)
-    const ulonglong2 *cell_code;  // [N] {pull, stencil} codes of boundary cells (D3Q27)
-    const int *bslot;           // [N] position in the boundary-cell list (D3Q27 with curved walls)
+    const ulonglong2 *cell_code;  // [N] {pull, stencil} codes of boundary cells (decode_pull_kind, decode_point)
+    const int *bslot;           // [N] position in the tables of curved walls (boundary cells, increasing index)
     const double *face_Td;      // [6] face_T in device memory (read at a computed face index)
     unsigned periodic_bits;     // bit f: face f periodic
     const float *bq;            // [Q][nb] wall distance of the bounced link of population I, NaN: half-way
@@ -154,10 +143,7 @@ struct KParams {
     const int *sup_idx;         //   [n_sup] their cells
     double *sup_val;            //   [n_sup][2 + n_species] T, rho, Y_k (this level)
     double *img_val;            //   [2 + n_species][n_img] T, rho, Y_k at the image points (this level)
-    // block list of a step launch: boundary_blocks (a multiple of 8) blocks
-    // of 256 boundary cells, then interior_blocks tiles of tiles_x x tiles_y
-    // x (nz / tile depth); a launch covers blocks [block_begin, + gridDim.x)
-    long long boundary_blocks, interior_blocks, block_begin;
+    long long nblocks;     // blocks of a step launch: the tiles
     int tiles_x, tiles_y, tiles_z;
     int tile_band;        // D3Q27: tiles in y of a band of the tile order
     const double *wall_T;
@@ -170,7 +156,7 @@ struct KParams {
     // fields mode: rho [N], u [dim][N], T [N], Y [n_species][N], P_h [N]
     // (nullptr: not asked for)
     double *f_rho, *f_u, *f_T, *f_Y, *f_Ph;
-    double *partials;     // [interior_blocks + boundary_blocks][kNDiag]  (diagnostics modes)
+    double *partials;     // [nblocks][kNDiag]  (diagnostics modes)
     const lbfd_reaction *rx;
     const ChemRx *rxk;  // the same reactions as the chemistry reads them
     int n_rx;
@@ -198,21 +184,20 @@ enum { kModeStep = 0, kModeStepDiag = 1, kModeDiag = 2, kModeFields = 3 };
 constexpr bool mode_reduces(int mode) { return mode == kModeStepDiag || mode == kModeDiag; }
 constexpr bool mode_advances(int mode) { return mode == kModeStep || mode == kModeStepDiag; }
 
-// A step is one launch (boundary blocks and tiles), plus the outlet update
-// for D3Q27 with an outflow face, the chemistry and the image points.
+// A step is one launch of tiles, plus the outlet update for D3Q27 with an
+// outflow face, the chemistry and the image points.
 inline int step_launches(int Q, int nsp, const KParams &kp)
 {
     const int images = kp.bimg != nullptr && kp.n_img > 0 ? 2 : 0;
     const int chem = chem_pass(nsp) && kp.n_fluid > 0 ? 3 : 0;  // counter clear, ordering, sources
     const bool outlet = Q == 27 && kp.n_boundary > 0 &&
                         (kp.face[0] == LBFD_FACE_OUTFLOW || kp.face[1] == LBFD_FACE_OUTFLOW);
-    return (kp.boundary_blocks + kp.interior_blocks > 0 ? 1 : 0) + (outlet ? 1 : 0) + images + chem;
+    return 1 + (outlet ? 1 : 0) + images + chem;
 }
 
 // Where a step is launched: the context stream, and which launches (0: all;
-// for per-part timing 1: the tiles (D2Q9: interior cells; D3Q27: every cell,
-// with the image points), 2: D2Q9 boundary blocks with the image points,
-// D3Q27 outlet, 3: the chemistry launch only).
+// for per-part timing 1: the tiles, with the image points, 2: the outlet of
+// D3Q27, 3: the chemistry launch only).
 struct Streams {
     hipStream_t main;
     int part;

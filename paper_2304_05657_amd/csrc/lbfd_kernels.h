@@ -327,24 +327,6 @@ __device__ __forceinline__ void load_point(const KParams &P, long long idx, Pt<N
     o.rho = density<NSP>(P, o.T, o.Y);
 }
 
-// Ghost value across the wall `w` from the image point (Sec. III.B):
-// Dirichlet 2 phi_B - phi(I) for T at isothermal walls and for T, Y at the
-// inlet; Neumann phi(I) otherwise (walls are impermeable); the density
-// ghost is reconstructed directly from its wall value.
-template <int NSP, class C>
-__device__ __forceinline__ void ghost(const KParams &P, const Nb &w, const Pt<NSP, C> &img, Pt<NSP, C> &o)
-{
-    // selects rather than branches: every field of o is written once
-    const bool iso = w.kind == kIso, inf = w.kind == kInflow;
-    const C Tw = (C)w.Tw;
-    C rho_b = (C)P.rho_in;
-    if (iso) rho_b = density<NSP>(P, Tw, img.Y);
-    o.T = iso ? (C)2 * Tw - img.T : inf ? (C)2 * (C)P.T_in - img.T : img.T;
-#pragma unroll
-    for (int k = 0; k < NSP; ++k) o.Y[k] = inf ? (C)2 * (C)P.Y_in[k] - img.Y[k] : img.Y[k];
-    o.rho = iso || inf ? (C)2 * rho_b - img.rho : img.rho;
-}
-
 // Population I or its opposite (same lattice weight, hence the same scale
 // in the mixed forms) of cell idx, the direction chosen per lane.
 template <int Q, int PREC, int I>
@@ -368,95 +350,6 @@ __device__ __forceinline__ typename Prec<PREC>::calc pop_load_pair(const void *b
     }
 }
 
-// A zero that a lane loads in place of an entry it does not need.
-static __constant__ double kZeroEntry[1] = {0.0};
-
-// Boundary cells: pull and stencil from the per-cell descriptors built at
-// init (same rules as gather / axis_stencil, resolved once on the host).
-// The pull keeps every lane on one path: the source population is one load
-// whose direction and cell are selected per lane, and the rarer inlet,
-// outlet and interpolated-wall terms are evaluated under wave-uniform
-// conditions (some lane of the wave needs them) for every lane, each lane
-// keeping its own by selection.  (Per-lane branches here let the register
-// allocator of the toolchain place copies of values that live through the
-// branch in the join block, where only one side's lanes are active, so
-// that the other side's lanes later read stale registers.)
-template <int Q, int PREC, int I, bool CW>
-__device__ __forceinline__ typename Prec<PREC>::calc desc_pull(const KParams &P, long long t, long long nb,
-                                                               long long idx, int x, int y, int z,
-                                                               unsigned long long pcode)
-{
-    using C = typename Prec<PREC>::calc;
-    using L = Lat<Q>;
-    constexpr int OPP = Q - 1 - I;
-    if constexpr (I == (Q - 1) / 2) {
-        return pop_load<Q, PREC, I>(P.pop_in, P.N, (uint32_t)idx);
-    } else {
-        // the source: the full descriptor with curved-wall links (whose
-        // rule also reads the opposite direction's), else the compact code
-        int src;
-        if constexpr (CW) {
-            src = P.bsrc[I * nb + t];
-        } else {
-            const int kind = decode_pull_kind(pcode, I);
-            src = kind == kPullFluid    ? (int)cell_at(x, y, z, -L::cx(I), -L::cy(I), -L::cz(I), P.nx, P.ny, P.nz)
-                  : kind == kPullBounce ? kSrcBounce
-                  : kind == kPullInflow ? kSrcInflow
-                                        : kSrcOutlet;
-        }
-        const bool fluid = src >= 0;
-        // the source cell's population I, or this cell's opposite one
-        // (half-way bounce-back, and the base of the inlet rule)
-        C g = pop_load_pair<Q, PREC, I>(P.pop_in, P.N, !fluid, fluid ? (uint32_t)src : (uint32_t)idx);
-        const bool inflow = src == kSrcInflow, outlet = src == kSrcOutlet;
-        if (__any(inflow)) {
-            // inlet (Eq. 31): + 2 w_I rho_in c_I.u_in; an x face carries the
-            // per-cell profile indexed by the cell's (y, z)
-            constexpr int cx = L::cx(I), cy = L::cy(I), cz = L::cz(I);
-            const int f = (cx == 1 && x == 0 && P.face[0] == LBFD_FACE_INFLOW)               ? 0
-                          : (cx == -1 && x == P.nx - 1 && P.face[1] == LBFD_FACE_INFLOW) ? 1
-                                                                                         : -1;
-            const bool prof = inflow && f >= 0;
-            const long long s3 = (long long)P.ny * P.nz;
-            const double *ub = prof ? P.inflow_u : kZeroEntry;
-            const long long o = prof ? 3 * s3 * f + (long long)z * P.ny + y : 0;
-            const double ux = ub[o], uy = ub[prof ? o + s3 : 0], uz = ub[prof ? o + 2 * s3 : 0];
-            const double cu = prof ? cx * ux + cy * uy + cz * uz : cx * P.u_in[0] + cy * P.u_in[1] + cz * P.u_in[2];
-            g = inflow ? g + (C)(2.0 * L::w(I) * P.rho_in * cu) : g;
-        }
-        if (__any(outlet)) {
-            // outlet value kept in the outlet buffer
-            const double *ob = outlet ? P.outlet : kZeroEntry;
-            const C ov = (C)ob[outlet ? outlet_index(P, L::cx(I) < 0 ? 1 : 0, I, Q, y, z) : 0];
-            g = outlet ? ov : g;
-        }
-        if constexpr (CW) {
-            // linearly interpolated bounce-back (post-collision form) for a
-            // wall met at the fraction q of the link toward it (direction OPP)
-            if (P.bq != nullptr) {
-                const float qraw = P.bq[I * nb + t];
-                const float qs = src == kSrcBounce ? qraw : __builtin_nanf("");
-                const bool interp = qs == qs;
-                if (__any(interp)) {
-                    const C q2 = (C)2 * (C)qs;  // weights in the arithmetic precision
-                    // q < 1/2: the far node r + c_I is the pull source of
-                    // direction OPP (when it is a fluid cell)
-                    const int far = P.bsrc[OPP * nb + t];
-                    const bool near_half = qs < 0.5f;
-                    const bool use_far = interp && near_half && far >= 0;
-                    const C gfar = pop_load_pair<Q, PREC, I>(P.pop_in, P.N, true, use_far ? (uint32_t)far : (uint32_t)idx);
-                    const C gown = pop_load<Q, PREC, I>(P.pop_in, P.N, (uint32_t)idx);
-                    const C lo = q2 * g + ((C)1 - q2) * gfar;
-                    const C iq = (C)1 / (interp && !near_half ? q2 : (C)1);
-                    const C hi = g * iq + (q2 - (C)1) * iq * gown;
-                    g = use_far ? lo : (interp && !near_half) ? hi : g;
-                }
-            }
-        }
-        return g;
-    }
-}
-
 // Values (T, rho, Y_k) at a listed image point, reconstructed for this
 // level by image_kernel.
 template <int NSP, class C>
@@ -466,43 +359,6 @@ __device__ __forceinline__ void image_value(const KParams &P, int li, Pt<NSP, C>
     o.rho = (C)P.img_val[P.n_img + li];
 #pragma unroll
     for (int k = 0; k < NSP; ++k) o.Y[k] = (C)P.img_val[(2 + k) * P.n_img + li];
-}
-
-template <int NSP, int PREC, bool DIAG, bool CW = false>
-__device__ __forceinline__ void desc_stencil(const KParams &P, long long t, long long nb, int d,
-                                             const Pt<NSP, typename Prec<PREC>::calc> &ctr,
-                                             Pt<NSP, typename Prec<PREC>::calc> (&st)[5], bool &near, double &wallq)
-{
-    using C = typename Prec<PREC>::calc;
-    st[2] = ctr;
-    int pts[4], wks[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        pts[j] = P.bpt[(d * 4 + j) * nb + t];
-        wks[j] = P.bwk[(d * 4 + j) * nb + t];
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int slot = j < 2 ? j : j + 1;
-        Pt<NSP, C> img;
-        const int li = CW && P.bimg != nullptr ? P.bimg[(d * 4 + j) * nb + t] : -1;
-        if (li >= 0)
-            image_value<NSP>(P, li, img);
-        else
-            load_point<NSP, PREC>(P, pts[j], img);
-        // a fluid point passes through ghost() unchanged
-        Nb w;
-        w.kind = wks[j];
-        w.face = -1;
-        w.idx = 0;
-        w.Tw = P.btw[(d * 4 + j) * nb + t];
-        near |= w.kind != kFluid;
-        ghost<NSP>(P, w, img, st[slot]);
-        if constexpr (DIAG) {
-            if ((j == 1 || j == 2) && w.kind == kIso)
-                wallq += 2.0 * P.alpha * (double)density<NSP>(P, (C)w.Tw, ctr.Y) * ((double)ctr.T - w.Tw);
-        }
-    }
 }
 
 // fourth-order central first and second derivatives (Sec. II.D)
@@ -1036,15 +892,15 @@ __device__ __forceinline__ void finish_cell(const KParams &P, long long idx, con
     }
 }
 
-// ------------------------------------------------------------ 3-D tiles
-// The pull of one cell of a 3-D tile.  The rows of the 3 x 3 neighbour lines
+// ------------------------------------------------------------ tiles
+// The pull of one cell of a tile.  The rows of the neighbour lines
 // are the same for a wave (its lanes differ in x only), so an interior wave
 // loads each population at a scalar base plus one of three lane offsets.
 // Where the wave holds a boundary cell, a lane whose source is no fluid cell
 // takes its own cell's opposite population by selecting the address (no
-// branch and no wait between the 27 loads); inlet, outlet and interpolated
+// branch and no wait between the loads); inlet, outlet and interpolated
 // walls, which few waves hold, follow in passes of their own.
-// m: the momentum sums.  In the mixed forms an interior cell's sum takes the
+// m: the momentum sums (3-D).  In the mixed forms an interior cell's sum takes the
 // stored value and its scale in one fused multiply-add, a boundary cell's the
 // scaled population (one factor per lane and lattice weight tells them apart).
 template <int Q, int PREC, bool CW>
@@ -1065,7 +921,11 @@ __device__ __forceinline__ void tile_pull(const KParams &P, int x, int y, int z,
                             kB * (uint32_t)(x == P.nx - 1 ? 0 : x + 1)};
     const int ys[3] = {y == 0 ? P.ny - 1 : y - 1, y, y == P.ny - 1 ? 0 : y + 1};
     const int zs[3] = {z == 0 ? P.nz - 1 : z - 1, z, z == P.nz - 1 ? 0 : z + 1};
+    uint32_t rows[3];  // (2-D)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) rows[k] = (uint32_t)(ys[k] * P.nx) * kB;
     auto off = [&](int ox, int oy, int oz) -> uint32_t {
+        if constexpr (L::D == 2) return rows[1 + oy] + xs[1 + ox];
         return (uint32_t)((zs[1 + oz] * P.ny + ys[1 + oy]) * P.nx) * kB + xs[1 + ox];
     };
     const uint32_t own = off(0, 0, 0);
@@ -1086,6 +946,7 @@ __device__ __forceinline__ void tile_pull(const KParams &P, int x, int y, int z,
     };
     // sum of c v s over the populations (v with its scale s)
     auto momentum = [&](auto &&v, auto &&sc) {
+        if constexpr (L::D == 2) return;
         m[0] = m[1] = m[2] = 0;
         sfor<0, Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
@@ -1105,7 +966,11 @@ __device__ __forceinline__ void tile_pull(const KParams &P, int x, int y, int z,
         PlanePtr<const R> pl(P.pop_in, 0, P.N);
         sfor<0, Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
-            v[i] = raw(load_global<kStream>(pl.at(off(-L::cx(i), -L::cy(i), -L::cz(i)))));
+            if constexpr (L::D == 2)
+                // (one offset for the lane, the shift in the scalar base)
+                v[i] = raw(*((const R *)P.pop_in + i * P.N - (L::cy(i) * P.nx + L::cx(i)) + own / kB));
+            else
+                v[i] = raw(load_global<kStream>(pl.at(off(-L::cx(i), -L::cy(i), -L::cz(i)))));
             g[i] = PREC == LBFD_FP64 ? v[i] : v[i] * scale(I);
             pl.step(P.N);
         });
@@ -1117,7 +982,13 @@ __device__ __forceinline__ void tile_pull(const KParams &P, int x, int y, int z,
         sfor<0, Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
             const auto *src = pl.at(off(-L::cx(i), -L::cy(i), -L::cz(i))), *opp = po.at(own);
-            v[i] = raw(load_global<kStream>(decode_pull_kind(pcode, i) == kPullFluid ? src : opp));
+            if constexpr (L::D == 2) {
+                // both, so that the loads need not wait for the code
+                const R a = load_global<kStream>(src), b = load_global<kStream>(opp);
+                v[i] = raw(decode_pull_kind(pcode, i) == kPullFluid ? a : b);
+            } else {
+                v[i] = raw(load_global<kStream>(decode_pull_kind(pcode, i) == kPullFluid ? src : opp));
+            }
             g[i] = PREC == LBFD_FP64 ? v[i] : v[i] * scale(I);
             pl.step(P.N);
             po.step(-P.N);
@@ -1196,10 +1067,12 @@ __device__ __forceinline__ void tile_pull(const KParams &P, int x, int y, int z,
     if constexpr (PREC == LBFD_FP64) {
         momentum([&](auto I) { return g[decltype(I)::value]; }, scale);
     } else {
+        if constexpr (L::D == 2) return;
         // one factor per squared speed
-        const C f[4] = {bnd ? (C)1 : scale(std::integral_constant<int, 13>{}),
-                        bnd ? (C)1 : scale(std::integral_constant<int, 12>{}),
-                        bnd ? (C)1 : scale(std::integral_constant<int, 9>{}),
+        constexpr int kMid = (Q - 1) / 2, kEdge = L::D == 3 ? 9 : 0;
+        const C f[4] = {bnd ? (C)1 : scale(std::integral_constant<int, kMid>{}),
+                        bnd ? (C)1 : scale(std::integral_constant<int, kMid - 1>{}),
+                        bnd ? (C)1 : scale(std::integral_constant<int, kEdge>{}),
                         bnd ? (C)1 : scale(std::integral_constant<int, 0>{})};
         sfor<0, Q>([&](auto I) { v[decltype(I)::value] = bnd ? g[decltype(I)::value] : v[decltype(I)::value]; });
         momentum([&](auto I) { return v[decltype(I)::value]; },
@@ -1210,13 +1083,59 @@ __device__ __forceinline__ void tile_pull(const KParams &P, int x, int y, int z,
     }
 }
 
+// The lowest kind bit of the slots (five bits each) whose kind is kInflow.
+__device__ __forceinline__ unsigned inflow_slots(unsigned s20)
+{
+    static_assert(kInflow == 3 && kOutflow == 4, "the only kind with its two low bits set");
+    return s20 & (s20 >> 1) & 0x8421u;
+}
+
+// Ghosts behind isothermal walls among the stencil points m = -2, -1, 1, 2
+// of a cell along axis d (Dirichlet 2 phi_B - phi(I) for T, the density ghost
+// reconstructed from its wall value; Sec. III.B): T(j) and R(j) hold the image
+// values and receive the ghosts, wall_density(j, Tw) is the density at the
+// wall with the composition of slot j.  The two points of a side share their
+// wall, the first non-fluid point from the cell (the kinds of both slots are
+// its kind when it is the first neighbour), hence one wall temperature a side.
+// c: the cell's coordinate along the axis of n cells; off: the points' cell
+// offsets along the wrapped axis.
+template <bool DIAG, class C, class FT, class FR, class FD, class FQ>
+__device__ __forceinline__ void iso_ghosts(const KParams &P, int d, int c, int n, long long idx, const int (&off)[4],
+                                           unsigned s20, FT &&T, FR &&R, FD &&wall_density, FQ &&heat, double &wallq)
+{
+#pragma unroll
+    for (int side = 0; side < 2; ++side) {
+        const int j1 = side ? 2 : 1, j2 = side ? 3 : 0;
+        const int k1 = (int)(s20 >> (5 * j1)) & 7, k2 = (int)(s20 >> (5 * j2)) & 7;
+        const bool iso1 = k1 == kIso, iso2 = k2 == kIso;
+        if (__any(iso2)) {
+            const bool second = k1 == kFluid;
+            const int mw = (side ? 1 : -1) * (second ? 2 : 1);
+            const bool out = (unsigned)(c + mw) >= (unsigned)n && !((P.periodic_bits >> (2 * d + side)) & 1u);
+            const double *tw = out ? P.face_Td + (2 * d + side) : P.wall_T + (idx + off[second ? j2 : j1]);
+            const C Tw = (C)*(iso2 ? tw : P.face_Td);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int j = q ? j2 : j1;
+                const bool iso = q ? iso2 : iso1;
+                const C rb = wall_density(j, Tw);
+                R(j) = iso ? (C)2 * rb - R(j) : R(j);
+                T(j) = iso ? (C)2 * Tw - T(j) : T(j);
+            }
+            if constexpr (DIAG) {
+                const double q = heat(Tw);
+                wallq += iso1 ? q : 0.0;
+            }
+        }
+    }
+}
+
 // The stencil points m = -2, -1, 1, 2 of one cell of a 3-D tile along axis d
 // (T, rho, Y_k), ghosts included; near: some point lies behind a wall.  A
 // ghost's image is a cell of the same line (the point itself, the cell, a
 // first neighbour), so boundary lanes select their four cells and the loads
 // are those of interior lanes; ghost values are formed by selection where a
-// lane of the wave has one on this axis.  The two points of a side share
-// their wall, hence one wall temperature a side.
+// lane of the wave has one on this axis.
 // d1r: the density's first derivative (d1).  An interior cell leaves the
 // constant factor of the first point's density to the difference that takes
 // it (one rounding less); the select keeps that form beside the boundary
@@ -1283,44 +1202,23 @@ __device__ __forceinline__ void tile_stencil(const KParams &P, int d, int x, int
                 }
             }
         }
+        iso_ghosts<DIAG, C>(
+            P, d, c, n, idx, off, s20, [&](int j) -> C & { return pv[j].T; }, [&](int j) -> C & { return pv[j].rho; },
+            [&](int j, C Tw) -> C { return density<NSP>(P, Tw, pv[j].Y); },
+            [&](C Tw) -> double {
+                return 2.0 * P.alpha * (double)density<NSP>(P, Tw, ctr.Y) * ((double)ctr.T - (double)Tw);
+            },
+            wallq);
+        if (__any(inflow_slots(s20) != 0)) {
+            // Dirichlet ghosts of T, Y_k and rho at the inlet
 #pragma unroll
-        for (int side = 0; side < 2; ++side) {
-            const int j1 = side ? 2 : 1, j2 = side ? 3 : 0;
-            const int k1 = (int)(s20 >> (5 * j1)) & 7, k2 = (int)(s20 >> (5 * j2)) & 7;
-            // the side's wall: the first non-fluid point from the cell (the
-            // kinds of both slots are its kind when it is the first neighbour)
-            const bool iso1 = k1 == kIso, iso2 = k2 == kIso;
-            if (__any(iso2)) {
-                const bool second = k1 == kFluid;
-                const int mw = (side ? 1 : -1) * (second ? 2 : 1);
-                const bool out = (unsigned)(c + mw) >= (unsigned)n && !((P.periodic_bits >> (2 * d + side)) & 1u);
-                const double *tw = out ? P.face_Td + (2 * d + side) : P.wall_T + (idx + off[second ? j2 : j1]);
-                const C Tw = (C)*(iso2 ? tw : P.face_Td);
+            for (int j = 0; j < 4; ++j) {
+                const bool in = ((s20 >> (5 * j)) & 7u) == (unsigned)kInflow;
+                pv[j].rho = in ? (C)2 * (C)P.rho_in - pv[j].rho : pv[j].rho;
+                pv[j].T = in ? (C)2 * (C)P.T_in - pv[j].T : pv[j].T;
 #pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    const int j = q ? j2 : j1;
-                    const bool iso = q ? iso2 : iso1;
-                    const C rb = density<NSP>(P, Tw, pv[j].Y);
-                    pv[j].rho = iso ? (C)2 * rb - pv[j].rho : pv[j].rho;
-                    pv[j].T = iso ? (C)2 * Tw - pv[j].T : pv[j].T;
-                }
-                if constexpr (DIAG) {
-                    const double q = 2.0 * P.alpha * (double)density<NSP>(P, Tw, ctr.Y) * ((double)ctr.T - (double)Tw);
-                    wallq += iso1 ? q : 0.0;
-                }
-            }
-            const bool in1 = k1 == kInflow, in2 = k2 == kInflow;
-            if (__any(in2)) {
-#pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    const int j = q ? j2 : j1;
-                    const bool in = q ? in2 : in1;
-                    pv[j].rho = in ? (C)2 * (C)P.rho_in - pv[j].rho : pv[j].rho;
-                    pv[j].T = in ? (C)2 * (C)P.T_in - pv[j].T : pv[j].T;
-#pragma unroll
-                    for (int k = 0; k < NSP; ++k)
-                        pv[j].Y[k] = in ? (C)2 * (C)P.Y_in[k] - pv[j].Y[k] : pv[j].Y[k];
-                }
+                for (int k = 0; k < NSP; ++k)
+                    pv[j].Y[k] = in ? (C)2 * (C)P.Y_in[k] - pv[j].Y[k] : pv[j].Y[k];
             }
         }
     }
@@ -1329,116 +1227,159 @@ __device__ __forceinline__ void tile_stencil(const KParams &P, int d, int x, int
     d1r = (lo + hi) * (C)(1.0 / 12.0);
 }
 
-// Interior tile of one 256-thread block: 64 x 4 cells in 2-D, 64 x 2 x 2
-// in 3-D.
+// 2-D: the populations entering through outflow face f at face cell idx
+// (Eq. 32): g_i(r) <- g_i(r-n)(cs - u.n) + g_i(r)(1 - cs + u.n) with the
+// post-streaming values and velocity of this level; pc: the cell's pull code
+// (whose outlet kinds imply a fluid inner neighbour).
+template <int Q, int PREC>
+__device__ __forceinline__ void outlet_2d(const KParams &P, int f, int x, int y, long long idx, unsigned long long pc,
+                                          typename Prec<PREC>::calc ux, const typename Prec<PREC>::calc (&g)[Q])
+{
+    using L = Lat<Q>;
+    using C = typename Prec<PREC>::calc;
+    const int sign = f ? 1 : -1;
+    const long long in = idx - sign;
+    const unsigned long long pci = P.code[in] == kCodeBoundary ? P.cell_code[in].x : 0;
+    const C cs = (C)0.57735026918962576451;
+    const C un = (C)sign * ux;
+    sfor<0, Q>([&](auto I) {
+        constexpr int i = decltype(I)::value;
+        if constexpr (L::cx(i) != 0) {
+            if (L::cx(i) == -sign && decode_pull_kind(pc, i) == kPullOutlet) {
+                // the inner cell's source is a neighbour inside the box along x
+                const int kind = decode_pull_kind(pci, i);
+                const bool fluid = kind == kPullFluid;
+                const uint32_t src = (uint32_t)cell_at(x, y, 0, 0, -L::cy(i), 0, P.nx, P.ny, 1);
+                C G = pop_load_pair<Q, PREC, i>(P.pop_in, P.N, !fluid, fluid ? src : (uint32_t)in);
+                if (kind == kPullInflow)
+                    G += (C)(2.0 * L::w(i) * P.rho_in *
+                             (L::cx(i) * P.u_in[0] + L::cy(i) * P.u_in[1] + L::cz(i) * P.u_in[2]));
+                P.outlet[outlet_index(P, f, i, Q, y, 0)] = (double)(G * (cs - un) + g[i] * ((C)1 - cs + un));
+            }
+        }
+    });
+}
+
+// Tile of one 256-thread block: 16 x 16 cells in 2-D (a wave 16 x 4), 64 x 2 x 2
+// in 3-D (a wave one row).
 template <int D> struct TileShape {
-    static constexpr int X = 64, Y = D == 2 ? 4 : 2, Z = D == 2 ? 1 : 2;
+    static constexpr int X = D == 2 ? 16 : 64, Y = D == 2 ? 16 : 2, Z = D == 2 ? 1 : 2;
 };
 
-// One block of the step.
-// FAST = true, 2-D: an interior tile (bx, by) of the box whose threads work
-// only on interior fluid cells (every pull source and every finite-difference
-// point in the box and fluid), with plain offset loads.
-// FAST = false (2-D): block bx of the list of the other fluid cells (boundary
-// cells), with the general geometry logic.
-// 3-D (FAST = true): a tile (bx, by, bz) whose threads work on every fluid
-// cell.  A boundary cell differs from an interior one in its addresses and in
-// ghost values, both selected per lane from the cell's two 64-bit codes under
+// One tile (bx, by, bz) of the step: its threads work on every fluid cell.  A
+// boundary cell (some pull source or finite-difference point is no in-box
+// fluid cell) differs from an interior one in its addresses and in ghost
+// values, both selected per lane from the cell's two 64-bit codes under
 // wave-uniform conditions (some lane of the wave is a boundary cell), so that
 // the cache lines that interior and boundary cells share are fetched and
-// written once.  What bounded the two separate launches was that traffic:
-// interior tiles then listed boundary cells moved 53 GB a step on a 512 x 256
-// x 256 packing with 9 species, 2.6 times what the cells need.
-// (tx, ty, tz): the thread's place in the tile (FAST; ty and tz the same for
-// a wave) or tx in 0..255.
+// written once and no list of boundary cells, with its chain of dependent
+// loads, is walked.  Interior tiles and listed boundary cells apart moved 53 GB
+// a step on a 512 x 256 x 256 packing with 9 species, 2.6 times what the cells
+// need; in 2-D the list's chain was most of a small box's step (channel of
+// 256 x 64, FP64: 11.7 -> 8.6 us; 70 x 37: 16.0 -> 10.6 us).
+// 2-D tiles are 16 x 16 because the near-wall work is a wave's when any of its
+// lanes has it, and because a square halo is smaller (400 points, 544 around
+// 64 x 4): a burner of 2048 x 512 with cylinders every 64 cells issues 1160
+// vector instructions a wave against 1596 (FP64), 63 us a step against 75
+// (tiles and a list 64; the step with diagnostics 86, 106; a field read 46,
+// 67), in half precision 1103 against 1520, 40 us against 50 (40; 64, 67; 32).
+// Waves of 8 x 8 cells issue 2 % fewer and take as long.  The kernel then moves
+// 211 MB in FP64 (273 MB before), 3.4 TB/s; in half precision it is bound by
+// its instructions.
+// (tx, ty, tz): the thread's place in the tile, in 3-D ty and tz the same for
+// a wave;
 // slot: the block's row of the diagnostics partials.
 // CW: boundary cells apply the curved-wall treatments when listed: the
 // interpolated bounce-back of P.bq and the Shepard image points of P.bimg (a
 // separate instantiation, so that contexts without them keep the registers
 // of plain bounce-back and axis-mirror ghosts).
-template <int Q, int NSP, int PREC, int MODE, bool FAST, bool CW = false, bool LE = false>
+template <int Q, int NSP, int PREC, int MODE, bool CW = false, bool LE = false>
 __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int bz, int tx, int ty, int tz,
                                            long long slot)
 {
     using L = Lat<Q>;
     using C = typename Prec<PREC>::calc;
+    using S = typename Prec<PREC>::scal;
     constexpr int D = L::D;
     constexpr bool DIAG = mode_reduces(MODE);
-    constexpr bool ALL = D == 3;  // every fluid cell of the tile
     using TS = TileShape<D>;
-    static_assert(FAST || D == 2, "3-D blocks are tiles");
-    int x, y, z;
-    long long idx, tb = 0;
-    unsigned long long pcode = 0, scode = 0;  // a boundary cell's compact codes
-    bool active, inbox, bnd = !FAST;
-    if constexpr (FAST) {
-        x = bx * TS::X + tx;
-        y = by * TS::Y + ty;
-        z = bz * TS::Z + tz;
-        inbox = x < P.nx && y < P.ny && z < P.nz;
-        idx = inbox ? ((long long)z * P.ny + y) * P.nx + x : 0;
-        const int code = inbox ? (int)P.code[idx] : (int)kCodeSolid;
-        active = ALL ? code != kCodeSolid : code == kCodeInterior;
-        if constexpr (ALL) {
-            bnd = code == kCodeBoundary;
-            if (bnd) {
-                const ulonglong2 cc = P.cell_code[idx];
-                pcode = cc.x;
-                scode = cc.y;
-                if constexpr (CW) tb = P.bslot[idx];
-            }
-        }
-    } else {
-        tb = (long long)bx * kBlock + tx;
-        inbox = false;
-        active = tb < P.n_boundary;
-        idx = active ? (long long)P.boundary[tb] : 0;
-        if constexpr (!CW) {
-            pcode = P.bcode_pull[active ? tb : 0];
-            scode = P.bcode_st[active ? tb : 0];
-        }
-        x = (int)(idx % P.nx);
-        y = (int)((idx / P.nx) % P.ny);
-        z = (int)(idx / ((long long)P.nx * P.ny));
-    }
-    const long long sy = P.nx;
+    const int x = bx * TS::X + tx, y = by * TS::Y + ty, z = bz * TS::Z + tz;
+    const bool inbox = x < P.nx && y < P.ny && z < P.nz;
+    const long long idx = inbox ? ((long long)z * P.ny + y) * P.nx + x : 0;
+    const int code = inbox ? (int)P.code[idx] : (int)kCodeSolid;
+    const bool active = code != kCodeSolid, bnd = code == kCodeBoundary;
     double acc[kNDiag];
     if constexpr (DIAG) diag_identity(acc);
 
-    // 2-D interior kernel: T, Y_k and rho of the block's 64 x 4 cells and a
-    // 2-cell halo staged once in LDS (field-major planes of 68 x 8 points);
-    // every finite-difference point is then an LDS read at a fixed offset.
-    // Halo points outside the box hold the nearest in-box point's values and
-    // are never read: only interior cells, whose stencils stay inside the
-    // box, read the tile.
-    constexpr int kTX = 64, kTY = 4, kHX = kTX + 4, kHY = kTY + 4, kNP = kHX * kHY;
-    constexpr bool TILE = FAST && D == 2;
+    // 2-D: T, Y_k and rho of the tile's cells and a 2-cell halo staged
+    // once in LDS (field-major planes of 20 x 20 points); every finite-
+    // difference point and ghost image is then an LDS read.  Points across a
+    // periodic face wrap; a point beyond an inflow face holds the ghost itself
+    // (Dirichlet T, Y_k, rho), which depends on the point alone; others beyond
+    // the box hold the nearest in-box point's values and are never read.
+    constexpr int kTX = TS::X, kTY = TS::Y, kHX = kTX + 4, kHY = kTY + 4, kNP = kHX * kHY;
+    constexpr bool TILE = D == 2;
     __shared__ C tile[TILE ? (NSP + 2) * kNP : 1];
-    C g[Q];
+    C g[Q], m[3] = {0, 0, 0};
+    long long tb = 0;  // the cell's place in the curved-wall tables
+    unsigned long long pcode = 0, scode = 0;
+    auto load_codes = [&] {
+        if (bnd) {
+            const ulonglong2 cc = P.cell_code[idx];
+            pcode = cc.x;
+            scode = cc.y;
+            if constexpr (CW) tb = P.bslot[idx];
+        }
+    };
     if constexpr (TILE) {
-        // the cell's pull loads go out first, so that their latency overlaps
-        // the staging of the tile
-        if (active)
-            sfor<0, Q>([&](auto I) {
-                constexpr int i = decltype(I)::value;
-                g[i] = pop_load<Q, PREC, i>(P.pop_in, P.N, idx - (L::cx(i) + sy * L::cy(i)));
-            });
-        // staging: every thread loads its (at most three) halo points at
-        // addresses clamped into the box before storing any, so that all the
-        // loads are in flight together (clamped points are never read)
+        // the staging loads go out first, every thread's (at most three)
+        // points before any is stored, so that they are in flight together
+        // with the cell's codes and pulls
         const int tid = tx + kTX * ty;
         const int gx0 = bx * kTX - 2, gy0 = by * kTY - 2;
+        const bool edge = gx0 < 0 || gy0 < 0 || gx0 + kHX > P.nx || gy0 + kHY > P.ny;  // the same for the block
         constexpr int kRounds = (kNP + kBlock - 1) / kBlock;
         Pt<NSP, C> pt[kRounds];
+        bool in[kRounds];
+        // coordinate v of an axis of n cells between faces f and f + 1, moved
+        // into the box; dist: how far beyond an inflow face it was (0: not)
+        auto inside = [&](int v, int n, int f, int &dist) -> int {
+            const int lo = P.face[f], hi = P.face[f + 1];
+            dist = v < 0 && lo == LBFD_FACE_INFLOW ? -v : v >= n && hi == LBFD_FACE_INFLOW ? v - n + 1 : 0;
+            if (v < 0) v = lo == LBFD_FACE_PERIODIC ? v + n : lo == LBFD_FACE_INFLOW ? dist - 1 : 0;
+            if (v >= n) v = hi == LBFD_FACE_PERIODIC && v - n < 2 ? v - n : hi == LBFD_FACE_INFLOW ? n - dist : n - 1;
+            return min(max(v, 0), n - 1);
+        };
 #pragma unroll
         for (int r = 0; r < kRounds; ++r) {
             const int i = tid + r * kBlock;
-            const int gx = min(max(gx0 + i % kHX, 0), P.nx - 1), gy = min(max(gy0 + i / kHX, 0), P.ny - 1);
-            load_point<NSP, PREC>(P, (long long)gy * P.nx + gx, pt[r]);
+            int gx = gx0 + i % kHX, gy = gy0 + i / kHX;
+            in[r] = false;
+            if (edge) {
+                const int sx = gx < 0 ? -1 : 1, sy = gy < 0 ? -1 : 1;
+                int dx, dy;
+                gx = inside(gx, P.nx, 0, dx);
+                gy = inside(gy, P.ny, 2, dy);
+                in[r] = dx == 1 || dx == 2 || dy == 1 || dy == 2;
+                // the second ghost's image is the mirror cell where that is
+                // fluid, else the face cell
+                if (dx == 2 && P.code[(long long)gy * P.nx + gx] == kCodeSolid) gx = min(max(gx + sx, 0), P.nx - 1);
+                if (dy == 2 && P.code[(long long)gy * P.nx + gx] == kCodeSolid) gy = min(max(gy + sy, 0), P.ny - 1);
+            }
+            if (kNP % kBlock == 0 || r + 1 < kRounds || i < kNP)
+                load_point<NSP, PREC>(P, (long long)gy * P.nx + gx, pt[r]);
         }
+        load_codes();
+        if (active) tile_pull<Q, PREC, CW>(P, x, y, z, tb, bnd, pcode, g, m);
 #pragma unroll
         for (int r = 0; r < kRounds; ++r) {
             const int i = tid + r * kBlock;
+            if (edge && __any(in[r])) {
+                pt[r].T = in[r] ? (C)2 * (C)P.T_in - pt[r].T : pt[r].T;
+                pt[r].rho = in[r] ? (C)2 * (C)P.rho_in - pt[r].rho : pt[r].rho;
+#pragma unroll
+                for (int k = 0; k < NSP; ++k) pt[r].Y[k] = in[r] ? (C)2 * (C)P.Y_in[k] - pt[r].Y[k] : pt[r].Y[k];
+            }
             if (i < kNP) {
                 tile[i] = pt[r].T;
                 tile[kNP + i] = pt[r].rho;
@@ -1447,30 +1388,23 @@ __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int
             }
         }
         __syncthreads();
+    } else {
+        load_codes();
     }
-    auto tile_point = [&](int dx, int dy, Pt<NSP, C> &o) {
-        const int i = (ty + 2 + dy) * kHX + tx + 2 + dx;
-        o.T = tile[i];
-        o.rho = tile[kNP + i];
-#pragma unroll
-        for (int k = 0; k < NSP; ++k) o.Y[k] = tile[(2 + k) * kNP + i];
-    };
+    const int ic = (ty + 2) * kHX + tx + 2;  // the cell's place in the LDS tile
 
     if (active) {
-        C m[3] = {0, 0, 0};
-        // streaming with boundary conditions (pull; already issued for tiles)
-        if constexpr (ALL)
-            tile_pull<Q, PREC, CW>(P, x, y, z, tb, bnd, pcode, g, m);
-        else if constexpr (!TILE)
-            sfor<0, Q>([&](auto I) {
-                constexpr int i = decltype(I)::value;
-                g[i] = desc_pull<Q, PREC, i, CW>(P, tb, P.n_boundary, idx, x, y, z, pcode);
-            });
+        // streaming with boundary conditions (2-D: issued above)
+        if constexpr (!TILE) tile_pull<Q, PREC, CW>(P, x, y, z, tb, bnd, pcode, g, m);
         Pt<NSP, C> ctr;
-        if constexpr (TILE)
-            tile_point(0, 0, ctr);
-        else
+        if constexpr (TILE) {
+            ctr.T = tile[ic];
+            ctr.rho = tile[kNP + ic];
+#pragma unroll
+            for (int k = 0; k < NSP; ++k) ctr.Y[k] = tile[(2 + k) * kNP + ic];
+        } else {
             load_point<NSP, PREC>(P, idx, ctr);
+        }
         const C rho = ctr.rho;
 
         // moments: sum g and sum c g (Eq. 13; in 3-D formed with the pull)
@@ -1478,7 +1412,7 @@ __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int
         sfor<0, Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
             sg += g[i];
-            if constexpr (!ALL) {
+            if constexpr (D == 2) {
                 if constexpr (L::cx(i) == 1) m[0] += g[i];
                 if constexpr (L::cx(i) == -1) m[0] -= g[i];
                 if constexpr (L::cy(i) == 1) m[1] += g[i];
@@ -1488,6 +1422,13 @@ __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int
         const C inv_rho = rcp(rho);
         const C inv_rc = (C)3 * inv_rho;  // 1 / (rho cs^2)
         const C u[3] = {m[0] * inv_rc, m[1] * inv_rc, m[2] * inv_rc};
+        if constexpr (D == 2 && mode_advances(MODE)) {
+            // (here, while few values are live)
+#pragma unroll
+            for (int f = 0; f < 2; ++f)
+                if (P.face[f] == LBFD_FACE_OUTFLOW && x == (f ? P.nx - 1 : 0))
+                    outlet_2d<Q, PREC>(P, f, x, y, idx, pcode, u[0], g);
+        }
 
         // finite differences per axis with ghost nodes (Sec. II.D, III.B);
         // one axis at a time, one scalar at a time, to bound register use
@@ -1565,20 +1506,89 @@ __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int
             const C ud = d == 0 ? u[0] : d == 1 ? u[1] : u[2];
             C d1r;
             if constexpr (TILE) {
-                const int ic = (ty + 2) * kHX + tx + 2;
+                // the points' (or their images') places in the tile
                 const int sd = d == 0 ? 1 : kHX;
-                C r5[5];
+                const unsigned s20 = (unsigned)(scode >> (20 * d)) & 0xfffffu;
+                int li[4] = {ic - 2 * sd, ic - sd, ic + sd, ic + 2 * sd};
+                const unsigned kinds = s20 & 0x39ce7u;
+                const bool near = kinds != 0;
+                if (__any(near)) {
+                    const int self[4] = {li[0], li[1], li[2], li[3]};
 #pragma unroll
-                for (int m = 0; m < 5; ++m) r5[m] = tile[kNP + ic + (m - 2) * sd];
-                d1r = d1(r5[0], r5[1], r5[2], r5[3], r5[4]);
-                axis_terms([&](int f, int m) -> C { return tile[f * kNP + ic + m * sd]; }, d1r, false, ud);
-            } else if constexpr (D == 2) {
-                // boundary cell (2-D): whole stencil points from the descriptors
-                Pt<NSP, C> st[5];
-                bool near = false;
-                desc_stencil<NSP, PREC, DIAG, CW>(P, tb, P.n_boundary, d, ctr, st, near, wallq);
-                d1r = d1(st[0].rho, st[1].rho, st[2].rho, st[3].rho, st[4].rho);
-                axis_terms([&](int f, int m) -> C { return f == 0 ? st[m + 2].T : st[m + 2].Y[f - 2]; }, d1r, near, ud);
+                    for (int j = 0; j < 4; ++j) {
+                        // the two bits of the image: self, cell, mirror, same;
+                        // beyond an inflow face the point holds the ghost
+                        const bool b0 = (s20 >> (5 * j + 3)) & 1u, b1 = (s20 >> (5 * j + 4)) & 1u;
+                        const bool inf = ((s20 >> (5 * j)) & 3u) == 3u;
+                        const int same = self[j < 2 ? 1 : 2], mirror = self[j < 2 ? 2 : 1];
+                        const int lo = b0 ? ic : self[j], hi = b0 ? same : mirror;
+                        li[j] = inf ? self[j] : b1 ? hi : lo;
+                    }
+                }
+                C Tv[4], rv[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    Tv[j] = tile[li[j]];
+                    rv[j] = tile[kNP + li[j]];
+                }
+                C Yv[CW ? 4 : 1][NSP];  // (image points: values of their own)
+                if constexpr (CW) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+#pragma unroll
+                        for (int k = 0; k < NSP; ++k) Yv[j][k] = tile[(2 + k) * kNP + li[j]];
+                }
+                if (__any(near)) {
+                    if constexpr (CW) {
+                        if (P.bimg != nullptr) {
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) {
+                                const int im = near ? P.bimg[(d * 4 + j) * P.n_boundary + tb] : -1;
+                                if (__any(im >= 0)) {
+                                    Pt<NSP, C> iv;
+                                    image_value<NSP>(P, im >= 0 ? im : 0, iv);
+                                    Tv[j] = im >= 0 ? iv.T : Tv[j];
+                                    rv[j] = im >= 0 ? iv.rho : rv[j];
+#pragma unroll
+                                    for (int k = 0; k < NSP; ++k) Yv[j][k] = im >= 0 ? iv.Y[k] : Yv[j][k];
+                                }
+                            }
+                        }
+                    }
+                    const int c = d == 0 ? x : y, n = d == 0 ? P.nx : P.ny, stride = d == 0 ? 1 : P.nx;
+                    int off[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) off[j] = (wrap_once(c + slot_offset(j), n) - c) * stride;
+                    iso_ghosts<DIAG, C>(
+                        P, d, c, n, idx, off, s20, [&](int j) -> C & { return Tv[j]; },
+                        [&](int j) -> C & { return rv[j]; },
+                        [&](int j, C Tw) -> C {
+                            C Yj[NSP];
+#pragma unroll
+                            for (int k = 0; k < NSP; ++k) {
+                                if constexpr (CW)
+                                    Yj[k] = Yv[j][k];
+                                else
+                                    Yj[k] = tile[(2 + k) * kNP + li[j]];
+                            }
+                            return density<NSP>(P, Tw, Yj);
+                        },
+                        [&](C Tw) -> double {
+                            return 2.0 * P.alpha * (double)density<NSP>(P, Tw, ctr.Y) * ((double)ctr.T - (double)Tw);
+                        },
+                        wallq);
+                }
+                d1r = d1(rv[0], rv[1], rho, rv[2], rv[3]);
+                axis_terms(
+                    [&](int f, int mm) -> C {
+                        const int j = mm < 0 ? mm + 2 : mm + 1;
+                        if (f == 0) return Tv[j];
+                        if constexpr (CW)
+                            return Yv[j][f - 2];
+                        else
+                            return tile[f * kNP + li[j]];
+                    },
+                    d1r, near, ud);
             } else {
                 // 3-D: the four points' T and Y, read once for their densities
                 // and kept for the finite differences; behind a wall a point
@@ -1607,53 +1617,24 @@ __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int
         for (int k = 0; k < NSP; ++k) diffY[k] *= alpha;
 
         finish_cell<Q, NSP, PREC, MODE, LE>(P, idx, g, ctr, u, m, sg, inv_rc, diffT, diffY, CT, CY, grad, wallq, acc);
-        if constexpr (mode_advances(MODE)) {
-            if constexpr (!FAST && D == 2) {
-                // outlet (Eq. 32): g_i(r) <- g_i(r-n)(cs - u.n) + g_i(r)(1 - cs + u.n)
-                // for the populations entering through the face, with the
-                // post-streaming values and velocity of this level
+
+        if constexpr (D == 3 && mode_advances(MODE)) {
+            // 3-D: outlet cells hand their outward normal velocity to
+            // outlet_kernel, which applies the same update (keeps the nine
+            // extra gathers out of this kernel's registers)
 #pragma unroll
-                for (int f = 0; f < 2; ++f) {
-                    if (P.face[f] != LBFD_FACE_OUTFLOW || x != (f ? P.nx - 1 : 0)) continue;
-                    const int sign = f ? 1 : -1;
-                    Nb in = classify(P, x - sign, y, z);
-                    if (in.kind != kFluid) continue;
-                    const C cs = (C)0.57735026918962576451;
-                    const C un = (C)sign * u[0];
-                    sfor<0, Q>([&](auto I) {
-                        constexpr int i = decltype(I)::value;
-                        if constexpr (L::cx(i) != 0) {
-                            if (L::cx(i) == -sign) {
-                                Nb s = classify(P, x - L::cx(i), y - L::cy(i), z - L::cz(i));
-                                if (s.kind == kOutflow && s.face == f) {
-                                    C G = gather<Q, PREC, i>(P, x - sign, y, z, in.idx);
-                                    P.outlet[outlet_index(P, f, i, Q, y, z)] =
-                                        (double)(G * (cs - un) + g[i] * ((C)1 - cs + un));
-                                }
-                            }
-                        }
-                    });
-                }
-            } else if constexpr (D == 3) {
-                // 3-D: outlet cells hand their outward normal velocity to
-                // outlet_kernel, which applies the same update (keeps the
-                // nine extra gathers out of this kernel's registers)
-#pragma unroll
-                for (int f = 0; f < 2; ++f)
-                    if (P.face[f] == LBFD_FACE_OUTFLOW && x == (f ? P.nx - 1 : 0))
-                        P.outlet_un[(long long)f * P.ny * P.nz + (long long)z * P.ny + y] =
-                            (double)(f ? u[0] : -u[0]);
-            }
+            for (int f = 0; f < 2; ++f)
+                if (P.face[f] == LBFD_FACE_OUTFLOW && x == (f ? P.nx - 1 : 0))
+                    P.outlet_un[(long long)f * P.ny * P.nz + (long long)z * P.ny + y] = (double)(f ? u[0] : -u[0]);
         }
-    } else if constexpr (MODE == kModeFields && FAST) {
+    } else if constexpr (MODE == kModeFields) {
         // solid cells: their stored T and Y, no flow
-        if (inbox && P.code[idx] == kCodeSolid) {
+        if (inbox) {
             if (P.f_rho) P.f_rho[idx] = 0.0;
             if (P.f_u)
 #pragma unroll
                 for (int d = 0; d < D; ++d) P.f_u[d * P.N + idx] = 0.0;
             if (P.f_Ph) P.f_Ph[idx] = 0.0;
-            using S = typename Prec<PREC>::scal;
             if (P.f_T) P.f_T[idx] = (double)((const S *)P.sc_in)[idx];
             if (P.f_Y)
 #pragma unroll
@@ -1667,47 +1648,35 @@ __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int
 
 // Minimum waves per SIMD asked of the register allocator for a step
 // kernel (measured on MI355X).  2-D with up to 4 species: three waves
-// (168 VGPRs) in FP64 and four (128) in the mixed forms -- the boundary
-// path, which needs more, spills instead of lowering the tiles' occupancy.
+// (168 VGPRs) in FP64 and four (128) in the mixed forms, there also with the
+// diagnostics (2048 x 512, half: 70 us free, 64 us at four; one more wave
+// than these spills: FP64 64 -> 70 us, half 41 -> 45 us a step).
 // 3-D FP64: two waves (256 VGPRs).  Otherwise the allocator is left free
-// (1): for the launches with diagnostics or fields (MODE != kModeStep),
-// which run once per check or read, and for the curved-wall and
+// (1): for the other launches with diagnostics or fields (MODE !=
+// kModeStep), which run once per check or read, and for the curved-wall and
 // mixture-transport instantiations (CW, LE).  The 2-D FP64 fields launch
 // with curved walls and mixture-averaged transport once returned wrong
 // velocities at the three-wave budget (spilling) and exact ones without it;
 // the assembly check of the build finds no one-sided copy in it, so the
 // budget stays off on those paths.
 template <int Q, int NSP, int PREC, int MODE = kModeStep, bool CWLE = false> struct StepWaves {
-    static constexpr int value = (MODE != kModeStep || CWLE)           ? 1
+    static constexpr int value = CWLE                                   ? 1
+                                 : (Q == 9 && NSP <= 4 && PREC != LBFD_FP64 && MODE == kModeStepDiag) ? 4
+                                 : MODE != kModeStep                    ? 1
                                  : (Q == 9 && NSP <= 4)                 ? (PREC == LBFD_FP64 ? 3 : 4)
                                  : (Q == 27 && PREC == LBFD_FP64)       ? 2
                                                                         : 1;
 };
 
-// The step over the block range [block_begin, block_begin + gridDim.x) of
-// the list (boundary blocks, then tiles).  D2Q9: boundary blocks first, so
-// that their long dependent chains of descriptor and neighbour loads start
-// with the launch and the interior tiles fill the remaining wave slots.
-// D3Q27: no boundary blocks, the tiles cover every fluid cell.
-// Consecutive blocks go to the 8 XCDs in turn, so the tiles are renumbered
-// to give each XCD one contiguous band of the box; boundary_blocks is a
-// multiple of 8, which keeps the XCD of a tile block equal to its index
-// modulo 8.
+// The step, a tile a block.  Consecutive blocks go to the 8 XCDs in turn, so
+// the tiles are renumbered to give each XCD one contiguous band of the box.
 template <int Q, int NSP, int PREC, int MODE, bool CW = false, bool LE = false>
 __global__ void __launch_bounds__(kBlock)
 __attribute__((amdgpu_waves_per_eu(StepWaves<Q, NSP, PREC, MODE, CW || LE>::value))) step_kernel(const KParams P)
 {
     using TS = TileShape<Lat<Q>::D>;
-    const long long b = (long long)blockIdx.x + P.block_begin;
-    if constexpr (Lat<Q>::D == 2) {
-        if (b < P.boundary_blocks) {
-            step_block<Q, NSP, PREC, MODE, false, CW, LE>(P, (int)b, 0, 0, (int)threadIdx.x, 0, 0,
-                                                  P.interior_blocks + b);
-            return;
-        }
-    }
-    const long long t = b - P.boundary_blocks;
-    const long long n = P.interior_blocks, q = n >> 3;
+    const long long t = (long long)blockIdx.x;
+    const long long n = P.nblocks, q = n >> 3;
     const int xcd = (int)(t & 7), r = (int)(n & 7);
     const long long tile = xcd * q + (xcd < r ? xcd : r) + (t >> 3);
     int bx, by, bz;
@@ -1727,9 +1696,9 @@ __attribute__((amdgpu_waves_per_eu(StepWaves<Q, NSP, PREC, MODE, CW || LE>::valu
         bz = 0;
     }
     const int tx = (int)threadIdx.x % TS::X;
-    // a wave is one row of the tile: its y and z are scalars
-    const int row = Lat<Q>::D == 3 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / TS::X) : (int)threadIdx.x / TS::X;
-    step_block<Q, NSP, PREC, MODE, true, CW && Lat<Q>::D == 3, LE>(P, bx, by, bz, tx, row % TS::Y, row / TS::Y, tile);
+    // 3-D: a wave is one row of the tile, its y and z are scalars
+    const int trow = (int)threadIdx.x / TS::X, row = Lat<Q>::D == 3 ? __builtin_amdgcn_readfirstlane(trow) : trow;
+    step_block<Q, NSP, PREC, MODE, CW, LE>(P, bx, by, bz, tx, row % TS::Y, row / TS::Y, tile);
 }
 
 // ------------------------------------------------------------ image points
@@ -1947,7 +1916,7 @@ hipError_t launch_chem(const KParams &kp, hipStream_t s)
 // post-streaming values g_i(r) (the outlet buffer, read by this step) and
 // g_i(r-n) (pulled again from the buffer this step read), and u.n of this
 // level (written by the step).  Runs after it; used for D3Q27 (D2Q9 applies
-// the update in the boundary blocks).
+// the update in the step).
 // A thread per face cell; it is bound by the latency of its loads, so both
 // cells' sources come from their pull codes -- the face cell's name the
 // populations the outlet sets, the inner cell's where its own are pulled from
@@ -2061,50 +2030,40 @@ __global__ void __launch_bounds__(kBlock) init_kernel(const KParams P, const dou
 // ------------------------------------------------------------ launchers
 // Instantiated once per configuration in inst/*.hip (explicit
 // instantiation), declared extern in the dispatcher.
-// One step: the boundary blocks (D2Q9) and the tiles (both read level n and
-// write disjoint cells of level n+1) in one launch on the context stream,
-// then for D3Q27 the outlet update.
+// One step: the tiles in one launch on the context stream, then for D3Q27
+// the outlet update.
 template <int Q, int NSP, int PREC, int MODE, bool LE>
-hipError_t launch_range_t(const KParams &kp, long long count, hipStream_t s)
+hipError_t launch_tiles_t(const KParams &kp, hipStream_t s)
 {
     // boundary cells with curved-wall links or image points
+    const dim3 grid((unsigned)kp.nblocks), block(kBlock);
     if (kp.bq != nullptr || kp.bimg != nullptr)
-        step_kernel<Q, NSP, PREC, MODE, true, LE><<<dim3((unsigned)count), dim3(kBlock), 0, s>>>(kp);
+        step_kernel<Q, NSP, PREC, MODE, true, LE><<<grid, block, 0, s>>>(kp);
     else
-        step_kernel<Q, NSP, PREC, MODE, false, LE><<<dim3((unsigned)count), dim3(kBlock), 0, s>>>(kp);
+        step_kernel<Q, NSP, PREC, MODE, false, LE><<<grid, block, 0, s>>>(kp);
     return hipGetLastError();
 }
 
 template <int Q, int NSP, int PREC, int MODE>
-hipError_t launch_range(const KParams &kp0, long long begin, long long count, hipStream_t s)
+hipError_t launch_parts(const KParams &kp, const Streams &st)
 {
-    if (count <= 0) return hipSuccess;
-    KParams kp = kp0;
-    kp.block_begin = begin;
-    // the mixture-averaged transport is a separate instantiation, so that
-    // unity-Lewis steps keep their registers
-    if (kp.transport == LBFD_MIXTURE_AVERAGED) return launch_range_t<Q, NSP, PREC, MODE, true>(kp, count, s);
-    return launch_range_t<Q, NSP, PREC, MODE, false>(kp, count, s);
-}
-
-template <int Q, int NSP, int PREC, int MODE>
-hipError_t launch_pair(const KParams &kp, const Streams &st)
-{
-    // st.part 0: every launch; 1: the tiles; 2: the boundary blocks (D2Q9)
-    // and the outlet; the image points run with the launch that reads them;
-    // 3: the chemistry launch only
-    const long long nbb = kp.boundary_blocks, nti = kp.interior_blocks;
+    // st.part 0: every launch; 1: the tiles (and the image points they read);
+    // 2: the outlet; 3: the chemistry launch only
     hipError_t e = hipSuccess;
     if constexpr (chem_pass(NSP)) {
         if ((st.part == 0 || st.part == 3) && (e = launch_chem<NSP, PREC>(kp, st.main)) != hipSuccess)
             return e;
     }
     if (st.part == 3) return hipSuccess;
-    if (kp.bimg != nullptr && kp.n_img > 0 && st.part != (Lat<Q>::D == 2 ? 1 : 2))
-        if ((e = launch_images<NSP, PREC>(kp, st.main)) != hipSuccess) return e;
-    const long long begin = st.part == 1 ? nbb : 0;
-    const long long count = st.part == 1 ? nti : st.part == 2 ? nbb : nbb + nti;
-    if ((e = launch_range<Q, NSP, PREC, MODE>(kp, begin, count, st.main)) != hipSuccess) return e;
+    if (st.part != 2) {
+        if (kp.bimg != nullptr && kp.n_img > 0)
+            if ((e = launch_images<NSP, PREC>(kp, st.main)) != hipSuccess) return e;
+        // the mixture-averaged transport is a separate instantiation, so that
+        // unity-Lewis steps keep their registers
+        e = kp.transport == LBFD_MIXTURE_AVERAGED ? launch_tiles_t<Q, NSP, PREC, MODE, true>(kp, st.main)
+                                                  : launch_tiles_t<Q, NSP, PREC, MODE, false>(kp, st.main);
+        if (e != hipSuccess) return e;
+    }
     if constexpr (Lat<Q>::D == 3 && mode_advances(MODE)) {
         if (st.part != 1 && kp.n_boundary > 0 &&
             (kp.face[0] == LBFD_FACE_OUTFLOW || kp.face[1] == LBFD_FACE_OUTFLOW)) {
@@ -2121,10 +2080,10 @@ template <int Q, int NSP, int PREC>
 hipError_t launch_step_t(int mode, const KParams &kp, const Streams &st)
 {
     switch (mode) {
-    case kModeStep: return launch_pair<Q, NSP, PREC, kModeStep>(kp, st);
-    case kModeStepDiag: return launch_pair<Q, NSP, PREC, kModeStepDiag>(kp, st);
-    case kModeDiag: return launch_pair<Q, NSP, PREC, kModeDiag>(kp, st);
-    default: return launch_pair<Q, NSP, PREC, kModeFields>(kp, st);
+    case kModeStep: return launch_parts<Q, NSP, PREC, kModeStep>(kp, st);
+    case kModeStepDiag: return launch_parts<Q, NSP, PREC, kModeStepDiag>(kp, st);
+    case kModeDiag: return launch_parts<Q, NSP, PREC, kModeDiag>(kp, st);
+    default: return launch_parts<Q, NSP, PREC, kModeFields>(kp, st);
     }
 }
 

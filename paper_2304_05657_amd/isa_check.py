@@ -24,6 +24,20 @@ copies of a live-range split (moves into AGPRs, spill stores) exactly there
 in the large boundary kernels; the results were wrong velocities, wrong
 states and, when the stale value formed a store address, memory faults.
 
+A per-lane if without an else has the same hazard at its join:
+
+    s_and_saveexec_b64 S, cond   ; EXEC <- then-lanes
+    s_cbranch_execz END
+    ...then part...
+  END:
+    ...copies...                 ; still under the then-lanes' EXEC
+    s_or_b64 exec, exec, S       ; EXEC <- all
+
+A copy before the restore of EXEC, of a value that the then part did not
+compute, leaves the other lanes' destination unwritten (seen after a rare
+store in the middle of a large step kernel: every lane outside the rare case
+read registers that no instruction had written).
+
 check(paths) scans assembly files and returns the offending copies;
 main() exits non-zero when there are any.  The scan is linear over each
 kernel's text and recognises the patterns above; it is a guard against that
@@ -169,6 +183,41 @@ def check_kernel(L: list) -> list:
                 continue  # the else part writes it too
             if _read_after(L, k, dest):
                 found.append((p, L[p]))
+    return found + _check_joins(L)
+
+
+def _check_joins(L: list) -> list:
+    """Copies in the join block of an if without an else, before EXEC is
+    restored."""
+    found = []
+    for i, t in enumerate(L):
+        m = re.match(r's_or_b64 exec, exec, (s\[\d+:\d+\])$', t)
+        if not m:
+            continue
+        S = m.group(1)
+        f = i
+        while f > 0 and not _LABEL.match(L[f]):
+            f -= 1
+        j = f
+        while j >= 0 and not (re.match(r's_\w+_b64 ' + re.escape(S) + ',', L[j]) or L[j].startswith('s_endpgm')):
+            j -= 1
+        # (the mask of an if without an else comes straight from its saveexec)
+        if j < 0 or not re.match(r's_and_saveexec_b64 ' + re.escape(S) + ',', L[j]):
+            continue
+        written = set()
+        for q in range(j + 1, f):
+            written |= _dests(L[q])
+        for p in range(f, i):
+            c = _copy(L[p])
+            if c:
+                dest, srcs = c
+                dregs = _regs(dest) or {dest}
+                later = set()
+                for q in range(p + 1, i):
+                    later |= _dests(L[q])
+                if srcs - written and not dregs & later and _read_after(L, i, dest):
+                    found.append((p, L[p]))
+            written |= _dests(L[p])
     return found
 
 

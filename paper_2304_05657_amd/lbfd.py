@@ -254,8 +254,8 @@ class Solver:
         return ms.value
 
     def time_kernels(self, n: int) -> tuple:
-        """(ms interior kernel, ms boundary kernel, ms chemistry launch)
-        summed over n serialised steps."""
+        """(ms tiles, ms outlet launch, ms chemistry launch) summed over n
+        serialised steps."""
         a, b, c = C.c_double(), C.c_double(), C.c_double()
         _check(self._lib, self._lib.lbfd_time_kernels(self._h, int(n), C.byref(a), C.byref(b), C.byref(c)))
         return a.value, b.value, c.value
