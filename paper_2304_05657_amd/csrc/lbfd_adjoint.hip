@@ -11,8 +11,7 @@
 //   dJ/dtheta = sum_n (dF/dtheta)^T lambda^{n+1} + dq^n/dtheta.
 // One thread per fluid cell c gathers the cell's inputs (pull sources,
 // the finite-difference stencil's scalars, ghost wall temperatures; at
-// interior cells plain offsets, elsewhere neighbours classified on the fly)
-// and runs the cell's update forward in FP64, then backward: the reverse of
+// interior cells plain offsets, elsewhere from the cell's codes) and runs the cell's update forward in FP64, then backward: the reverse of
 // every operation, hand-derived, from the adjoint of the cell's outputs to
 // those of its inputs, in two kernels (cell_vjp_collision,
 // cell_vjp_stencil).  The sub-stepped Arrhenius source is reversed sub-step
@@ -144,8 +143,8 @@ struct CellIn {
     int wall[S];          // ghost slot behind an isothermal in-box solid: its cell, else -1
 };
 
-// PULLS = false: the stencil's slots only.
-template <int Q, int NSP, bool PULLS = true>
+// (the tangent's; the reverse sweep reads the cell's codes instead)
+template <int Q, int NSP>
 __device__ void gather_inputs(const KParams &P, int x, int y, int z, long long idx, CellIn<Q, NSP> &in)
 {
     using L = Lat<Q>;
@@ -155,7 +154,7 @@ __device__ void gather_inputs(const KParams &P, int x, int y, int z, long long i
         // every pull source and stencil point is an in-box fluid cell
         const long long st[3] = {1, P.nx, (long long)P.nx * P.ny};
 #pragma unroll
-        for (int i = 0; i < (PULLS ? Q : 0); ++i) {
+        for (int i = 0; i < Q; ++i) {
             in.tdir[i] = i;
             in.tcell[i] = (int)(idx - (L::cx(i) * st[0] + L::cy(i) * st[1] + L::cz(i) * st[2]));
             in.g[i] = pop[(long long)i * P.N + in.tcell[i]];
@@ -173,7 +172,7 @@ __device__ void gather_inputs(const KParams &P, int x, int y, int z, long long i
         return;
     }
 #pragma unroll
-    for (int i = 0; i < (PULLS ? Q : 0); ++i) {
+    for (int i = 0; i < Q; ++i) {
         const int cx = i % 3 - 1, cy = (i / 3) % 3 - 1, cz = Q == 9 ? 0 : i / 9 - 1;
         const int opp = Q - 1 - i;
         double corr = 0.0;
@@ -365,10 +364,11 @@ __device__ __forceinline__ void chem_substep(const KParams &P, const double *tab
 
 // Reverse of chem_source (FP64): given ls, the adjoint of (srcT, srcY),
 // adds ls^T d src / d (T0, Y0) to aT0, aY0 and ls^T d src / d (A_j, Ta_j) to
-// lam_param[2 j], lam_param[2 j + 1] (LDS).  The sub-steps are reversed
+// the thread's copies of lam_param[2 j], lam_param[2 j + 1] (LDS).  The sub-steps are reversed
 // from the last; the state of each is recomputed from (T0, Y0), so the cost
 // grows with the square of the sub-step count (one sub-step: one forward
 // and one reverse evaluation).
+constexpr int kParamCopies = 16;
 template <int NSP>
 __device__ void chem_vjp(const KParams &P, const double *tab, double T0, const double (&Y0)[NSP],
                          const double (&ls)[1 + NSP], double &aT0, double (&aY0)[NSP], double *lam_param)
@@ -444,8 +444,11 @@ __device__ void chem_vjp(const KParams &P, const double *tab, double T0, const d
 #pragma unroll
             for (int k = 0; k < NSP; ++k) lrr += r.nu_mass[k] * lincY[k];
             lTc += lrr * rr * (r.b * invTc + r.Ta * invTc * invTc);
-            atomicAdd(&lam_param[2 * j], lrr * P.dt_phys * e * inv_nsub * pr);
-            atomicAdd(&lam_param[2 * j + 1], -lrr * rr * invTc);
+            // (per-lane copies: on one address the compiler adds the lanes one
+            // by one in a loop, 96 -> 5 us of a 2-D level's 69)
+            double *lp = lam_param + 2 * j * kParamCopies + (threadIdx.x & (kParamCopies - 1));
+            atomicAdd(lp, lrr * P.dt_phys * e * inv_nsub * pr);
+            atomicAdd(lp + kParamCopies, -lrr * rr * invTc);
             // each factor: the product of the other three
             const double other[4] = {F[1] * F[2] * F[3], F[0] * F[2] * F[3], F[0] * F[1] * F[3], F[0] * F[1] * F[2]};
 #pragma unroll
@@ -715,66 +718,196 @@ struct AdjOut {
     double *lam_pop;    // [Q][N]: stored (every entry is pulled by one cell)
     double *lam_sc;     // [1+NSP][N]: accumulated atomically
     double *dwallT;     // [N]: accumulated atomically
-    double *lam_param;  // [2 n_rx] in LDS: accumulated atomically
+    double *lam_param;  // [2 n_rx][kParamCopies] in LDS: accumulated atomically
     double *mid;        // [AdjMid::n][N]
     double *nb;         // [S - 1][1+NSP][N]: what each stencil slot's cell receives
 };
 
-// The stencil's T, Y, rho and sum_k Y_k / W_k, ghosts from their images
-// (fluid slots: the cell or a first neighbour).  Reciprocals of these
-// positive normal values by rcp() (the divisions here and in the stencil's
-// reverse: about one ulp).
-template <int Q, int NSP>
-__device__ __forceinline__ void fill_stencil(const KParams &P, const CellIn<Q, NSP> &in, double (&T)[n_slots<Q>()],
-                                             double (&Y)[n_slots<Q>()][NSP], double (&R)[n_slots<Q>()],
-                                             double (&Sw)[n_slots<Q>()])
+// Entry of plane k ([planes][N]) at a cell's byte offset: a scalar base and a
+// 32-bit offset (N < 2^29), not an address in two registers for each plane.
+template <class T>
+__device__ __forceinline__ T &plane_at(T *base, long long N, int k, uint32_t off)
 {
-    constexpr int S = n_slots<Q>();
+    return *(T *)((std::conditional_t<std::is_const_v<T>, const char, char> *)(base + (long long)k * N) + off);
+}
+
+// A cell as the reverse sweep reads it: its coordinates and codes (boundary
+// cells; an interior cell's codes are 0 and its coordinates are not needed).
+struct AdjCell {
+    long long idx;
+    int x, y, z;
+    bool bnd;
+    unsigned long long pcode, scode;
+};
+
+// The fluid cell of a thread; false when there is none.
+__device__ __forceinline__ bool adj_cell(const KParams &P, AdjCell &c)
+{
+    c.idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (c.idx >= P.N) return false;
+    const int code = P.code[c.idx];
+    c.bnd = code == kCodeBoundary;
+    c.x = c.y = c.z = 0;
+    c.pcode = c.scode = 0;
+    if (c.bnd) {
+        const unsigned i = (unsigned)c.idx, row = i / (unsigned)P.nx;  // (N < 2^29)
+        c.x = (int)(i - row * (unsigned)P.nx);
+        c.z = (int)(row / (unsigned)P.ny);
+        c.y = (int)(row - (unsigned)c.z * (unsigned)P.ny);
+        const ulonglong2 cc = P.cell_code[c.idx];
+        c.pcode = cc.x;
+        c.scode = cc.y;
+    }
+    return code != kCodeSolid;
+}
+
+// The cell offsets of the neighbours at -1, 0, 1 along each axis (wrapped).
+struct AdjNb {
+    int x[3], y[3], z[3];
+};
+__device__ __forceinline__ AdjNb adj_neighbours(const KParams &P, const AdjCell &c)
+{
+    const int sy = P.nx, sz = P.nx * P.ny;
+    AdjNb o = {{-1, 0, 1}, {-sy, 0, sy}, {-sz, 0, sz}};
+    if (c.bnd) {
+        o.x[0] = c.x == 0 ? P.nx - 1 : -1;
+        o.x[2] = c.x == P.nx - 1 ? 1 - P.nx : 1;
+        o.y[0] = (c.y == 0 ? P.ny - 1 : -1) * sy;
+        o.y[2] = (c.y == P.ny - 1 ? 1 - P.ny : 1) * sy;
+        o.z[0] = (c.z == 0 ? P.nz - 1 : -1) * sz;
+        o.z[2] = (c.z == P.nz - 1 ? 1 - P.nz : 1) * sz;
+    }
+    return o;
+}
+
+// f(I, population entry that the cell's population I is pulled from) for
+// every I: the neighbour's entry, or behind a wall or an inlet the cell's own
+// opposite one.
+template <int Q, class T, class F>
+__device__ __forceinline__ void pull_entries(const KParams &P, const AdjCell &c, T *pop, F &&f)
+{
+    using L = Lat<Q>;
+    const uint32_t own = (uint32_t)c.idx * 8u;
+    if (!__any(c.bnd)) {
+        sfor<0, Q>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            const long long shift = (L::cz(i) * (long long)P.ny + L::cy(i)) * P.nx + L::cx(i);
+            f(I, plane_at(pop - shift, P.N, i, own));
+        });
+        return;
+    }
+    const AdjNb o = adj_neighbours(P, c);
+    sfor<0, Q>([&](auto I) {
+        constexpr int i = decltype(I)::value;
+        const uint32_t src = own + 8u * (uint32_t)(o.x[1 - L::cx(i)] + o.y[1 - L::cy(i)] + o.z[1 - L::cz(i)]);
+        const bool fl = decode_pull_kind(c.pcode, i) == kPullFluid;
+        f(I, *(fl ? &plane_at(pop, P.N, i, src) : &plane_at(pop, P.N, Q - 1 - i, own)));
+    });
+}
+
+// sum_d c_d v_d over the axes with c_d != 0 (a product with a constant zero is
+// not dropped by itself)
+template <int Q, int I>
+__device__ __forceinline__ double dot_c(const double (&v)[3])
+{
+    using L = Lat<Q>;
+    double r = 0.0;
+    if constexpr (L::cx(I) != 0) r = L::cx(I) * v[0];
+    if constexpr (L::cy(I) != 0) r = L::cx(I) != 0 ? r + L::cy(I) * v[1] : L::cy(I) * v[1];
+    if constexpr (L::cz(I) != 0) r = L::cx(I) != 0 || L::cy(I) != 0 ? r + L::cz(I) * v[2] : L::cz(I) * v[2];
+    return r;
+}
+// v_d += c_d a
+template <int Q, int I>
+__device__ __forceinline__ void add_c(double (&v)[3], double a)
+{
+    using L = Lat<Q>;
+    if constexpr (L::cx(I) != 0) v[0] += L::cx(I) * a;
+    if constexpr (L::cy(I) != 0) v[1] += L::cy(I) * a;
+    if constexpr (L::cz(I) != 0) v[2] += L::cz(I) * a;
+}
+
+// One axis of a cell's stencil: T, Y, rho and sum_k Y_k / W_k at the points
+// m = -2, -1, 1, 2, a ghost formed from its image; the kinds and images of
+// the four slots (s20) and the points' cell offsets along the wrapped axis.
+// The points are read here, axis by axis, rather than all at once: every slot
+// held through the cell's evaluation took 182 registers in 3-D.
+template <int NSP>
+struct AdjAxis {
+    double T[4], Y[4][NSP], R[4], Sw[4];
+    double Tw[2];       // wall temperature behind the isothermal ghosts of side 0, 1
+    int wall[2];        // that wall's cell when it is an in-box solid, else -1
+    unsigned s20;
+    __device__ __forceinline__ int kind(int j) const { return (int)(s20 >> (5 * j)) & 7; }
+    __device__ __forceinline__ int image(int j) const { return (int)(s20 >> (5 * j + 3)) & 3; }
+    __device__ __forceinline__ bool near() const { return (s20 & 0x39ce7u) != 0; }
+};
+
+template <int NSP>
+__device__ __forceinline__ void load_axis(const KParams &P, const AdjCell &c, int d, AdjAxis<NSP> &A)
+{
+    const double *sc = (const double *)P.sc_in;
     const double c0 = P.T_ref_over_W_ref;
-    slot_scalars<Q, NSP>(P, in, T, Y);
+    const int stride = d == 0 ? 1 : d == 1 ? P.nx : P.nx * P.ny;
+    const int x = d == 0 ? c.x : d == 1 ? c.y : c.z, n = d == 0 ? P.nx : d == 1 ? P.ny : P.nz;
+    A.s20 = (unsigned)(c.scode >> (20 * d)) & 0xfffffu;
+    int off[4];
 #pragma unroll
-    for (int s = 0; s < S; ++s) {
-        double sw = 0.0;
+    for (int j = 0; j < 4; ++j) off[j] = slot_offset(j) * stride;
+    if (c.bnd) {
 #pragma unroll
-        for (int k = 0; k < NSP; ++k) sw += Y[s][k] * P.invW[k];
-        const bool fl = in.kind[s] == kFluid;
-        Sw[s] = fl ? sw : 1.0;
-        R[s] = fl ? c0 * rcp(T[s] * Sw[s]) : 0.0;
+        for (int j = 0; j < 4; ++j) off[j] = (wrap_once(x + slot_offset(j), n) - x) * stride;
     }
 #pragma unroll
-    for (int s = 1; s < S; ++s) {
-        const int kd = in.kind[s];
-        if (kd == kFluid) continue;
-        const int im = in.img[s];
-        const int ca = img_lo(s), cb = img_hi(s);
-        const bool ia = im == ca, ib = !ia && im == cb;
-        // the image's values as an exact 0/1 blend of the three candidates
-        // (a select between array elements would become an indexed load and
-        // keep the arrays in scratch memory)
-        const double fa = ia ? 1.0 : 0.0, fb = ib ? 1.0 : 0.0, f0 = 1.0 - fa - fb;
-        auto blend = [&](double va, double vb, double v0) { return fa * va + fb * vb + f0 * v0; };
-        const double Ti = blend(T[ca], T[cb], T[0]);
-        const double Ri = blend(R[ca], R[cb], R[0]);
-        const double Swi = blend(Sw[ca], Sw[cb], Sw[0]);
-        double Yi[NSP];
+    for (int j = 0; j < 4; ++j) {
+        // the value point, or the ghost's image: the point itself, the cell,
+        // the first neighbour on the other side, on the same side
+        static_assert(kImgSelf == 0 && kImgCell == 1 && kImgMirror == 2 && kImgSame == 3);
+        const bool b0 = A.image(j) & 1, b1 = A.image(j) & 2;
+        const int same = off[j < 2 ? 1 : 2], mirror = off[j < 2 ? 2 : 1];
+        const int lo = b0 ? 0 : off[j], hi = b0 ? same : mirror;
+        const int at = b1 ? hi : lo;
+        const uint32_t p = (uint32_t)((int)c.idx + at) * 8u;
+        A.T[j] = plane_at(sc, P.N, 0, p);
+        double sw = 0.0;
 #pragma unroll
-        for (int k = 0; k < NSP; ++k) Yi[k] = blend(Y[ca][k], Y[cb][k], Y[0][k]);
-        Sw[s] = Swi;
-        if (kd == kIso) {
-            T[s] = 2.0 * in.Tw[s] - Ti;
+        for (int k = 0; k < NSP; ++k) {
+            A.Y[j][k] = plane_at(sc, P.N, 1 + k, p);
+            sw += A.Y[j][k] * P.invW[k];
+        }
+        A.Sw[j] = sw;
+        A.R[j] = c0 * rcp(A.T[j] * sw);
+    }
 #pragma unroll
-            for (int k = 0; k < NSP; ++k) Y[s][k] = Yi[k];
-            R[s] = 2.0 * (c0 * rcp(in.Tw[s] * Swi)) - Ri;
-        } else if (kd == kInflow) {
-            T[s] = 2.0 * P.T_in - Ti;
+    for (int side = 0; side < 2; ++side) {
+        const int j1 = side ? 2 : 1, j2 = side ? 3 : 0;
+        A.Tw[side] = 0.0;
+        A.wall[side] = -1;
+        if (A.kind(j2) == kIso) {
+            // the two points of a side share their wall, the first non-fluid
+            // point from the cell
+            const bool second = A.kind(j1) == kFluid;
+            const int mw = (side ? 1 : -1) * (second ? 2 : 1);
+            const bool out = (unsigned)(x + mw) >= (unsigned)n && !((P.periodic_bits >> (2 * d + side)) & 1u);
+            const int w = (int)c.idx + off[second ? j2 : j1];
+            A.wall[side] = out ? -1 : w;
+            A.Tw[side] = out ? P.face_Td[2 * d + side] : P.wall_T[w];
+        }
+    }
+    if (A.near()) {
 #pragma unroll
-            for (int k = 0; k < NSP; ++k) Y[s][k] = 2.0 * P.Y_in[k] - Yi[k];
-            R[s] = 2.0 * P.rho_in - Ri;
-        } else {
-            T[s] = Ti;
+        for (int j = 0; j < 4; ++j) {
+            const int kd = A.kind(j);
+            if (kd == kIso) {
+                const double Tw = A.Tw[j < 2 ? 0 : 1];
+                A.T[j] = 2.0 * Tw - A.T[j];
+                A.R[j] = 2.0 * (c0 * rcp(Tw * A.Sw[j])) - A.R[j];
+            } else if (kd == kInflow) {
+                A.T[j] = 2.0 * P.T_in - A.T[j];
 #pragma unroll
-            for (int k = 0; k < NSP; ++k) Y[s][k] = Yi[k];
-            R[s] = Ri;
+                for (int k = 0; k < NSP; ++k) A.Y[j][k] = 2.0 * P.Y_in[k] - A.Y[j][k];
+                A.R[j] = 2.0 * P.rho_in - A.R[j];
+            }
         }
     }
 }
@@ -786,62 +919,82 @@ __device__ __forceinline__ void fill_stencil(const KParams &P, const CellIn<Q, N
 // of the outputs (g*, T^{n+1}, Y^{n+1}; read from out) and the weight wT0 of
 // the cell's own T (the flame position's linear term): the adjoints of the
 // pulled populations (stored) and the cell's AdjMid.
+// hxs (D3Q27): [Q][kBlock] doubles of LDS for the moments' input between the
+// forward and the reverse half, which together with the relaxed moments, the
+// adjoints and a transform's passes would not fit the registers.
 template <int Q, int NSP>
-__device__ void cell_vjp_collision(const KParams &P, const CellIn<Q, NSP> &in, double wT0, const double *tab,
-                                   const AdjOut &out)
+__device__ __forceinline__ void cell_vjp_collision(const KParams &P, const AdjCell &c, double wT0, const double *tab,
+                                                   const AdjOut &out, double *hxs)
 {
     using L = Lat<Q>;
     using M = AdjMid<Lat<Q>::D, NSP>;
-    constexpr int D = L::D, S = n_slots<Q>(), NS = 1 + NSP;
+    constexpr int D = L::D, NS = 1 + NSP;
 
     // ------------------------------------------------ forward (values)
+    const double *pop = (const double *)P.pop_in;
+    const double *sc = (const double *)P.sc_in;
+    const uint32_t self = (uint32_t)c.idx * 8u;
     double g[Q];
-#pragma unroll
-    for (int i = 0; i < Q; ++i) g[i] = in.g[i];
-    double m[3] = {0.0, 0.0, 0.0};
-#pragma unroll
-    for (int i = 0; i < Q; ++i) {
-        m[0] += L::cx(i) * g[i];
-        m[1] += L::cy(i) * g[i];
-        m[2] += L::cz(i) * g[i];
+    pull_entries<Q>(P, c, pop, [&](auto I, const double &v) { g[decltype(I)::value] = v; });
+    if (c.pcode & 0xaaaaaaaaaaaaaaaaull) {
+        sfor<0, Q>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            if constexpr (i != (Q - 1) / 2) {
+                if (decode_pull_kind(c.pcode, i) == kPullInflow)
+                    g[i] += 2.0 * L::w(i) * P.rho_in * inflow_cu_c(P, L::cx(i), L::cy(i), L::cz(i), c.x, c.y, c.z);
+            }
+        });
     }
-    double T0, Y0[NSP], rho;
-    double diffT = 0.0, grad[3] = {0.0, 0.0, 0.0}, diffY[NSP];
-    double cT[3] = {0.0, 0.0, 0.0}, cY[3][NSP], sumc[3] = {0.0, 0.0, 0.0};
-    double u[3], inv_rc, inv_rho;
-    {
-        double T[S], Y[S][NSP], R[S], Sw[S];
-        fill_stencil<Q, NSP>(P, in, T, Y, R, Sw);
-        T0 = T[0];
+    double T0 = plane_at(sc, P.N, 0, self), Y0[NSP], invWs = 0.0;
 #pragma unroll
-        for (int k = 0; k < NSP; ++k) Y0[k] = Y[0][k];
-        rho = R[0];
-        inv_rc = rcp(rho * kCs2);
+    for (int k = 0; k < NSP; ++k) {
+        Y0[k] = plane_at(sc, P.N, 1 + k, self);
+        invWs += Y0[k] * P.invW[k];
+    }
+    const double rho = P.T_ref_over_W_ref * rcp(T0 * invWs);
+    double m[3] = {0.0, 0.0, 0.0};
+    sfor<0, Q>([&](auto I) { add_c<Q, decltype(I)::value>(m, g[decltype(I)::value]); });
+    const double inv_rc = rcp(rho * kCs2), inv_rho = rcp(rho);
+    double u[3];
 #pragma unroll
-        for (int d = 0; d < 3; ++d) u[d] = m[d] * inv_rc;
-        inv_rho = rcp(rho);
+    for (int d = 0; d < 3; ++d) u[d] = m[d] * inv_rc;
+    // the scalars' outputs are T' = T0 - CT + DtT, Y' = Y0 - CY + DtY with
+    // CT = sum_d u_d cT_d, CY_k = sum_d u_d (cY_k - Y0_k sumc): the adjoints of
+    // the convection's u (luc) and of Y0 through sumc (us) are linear in the
+    // outputs' and are formed with the axis
+    double lsc[NS];
 #pragma unroll
-        for (int k = 0; k < NSP; ++k) diffY[k] = 0.0;
+    for (int k = 0; k < NS; ++k) lsc[k] = plane_at(out.lo_sc, P.N, k, self);
+    double diffT = 0.0, grad[3] = {0.0, 0.0, 0.0}, diffY[NSP], luc[3] = {0.0, 0.0, 0.0}, us = 0.0;
 #pragma unroll
-        for (int d = 0; d < D; ++d) {
-            const int sl[5] = {1 + 4 * d, 2 + 4 * d, 0, 3 + 4 * d, 4 + 4 * d};
-            bool near = false;
+    for (int k = 0; k < NSP; ++k) diffY[k] = 0.0;
+#pragma unroll 1
+    for (int d = 0; d < D; ++d) {
+        const double ud = d == 0 ? u[0] : d == 1 ? u[1] : u[2];
+        AdjAxis<NSP> A;
+        load_axis<NSP>(P, c, d, A);
+        const bool near = A.near();
+        const double d1r = d1(A.R[0], A.R[1], rho, A.R[2], A.R[3]);
+        double l = 0.0, sumc = 0.0, cY[NSP];
+        {
+            diffT += d2(A.T[0], A.T[1], T0, A.T[2], A.T[3]) + d1r * d1(A.T[0], A.T[1], T0, A.T[2], A.T[3]) * inv_rho;
+            const double cT = near ? 0.5 * (A.T[2] - A.T[1]) : weno3(A.T[0], A.T[1], T0, A.T[2], A.T[3], ud);
+            l -= lsc[0] * cT;
+        }
 #pragma unroll
-            for (int j = 0; j < 5; ++j) near |= in.kind[sl[j]] != kFluid;
-            const double d1r = d1(R[sl[0]], R[sl[1]], R[sl[2]], R[sl[3]], R[sl[4]]);
-            {
-                const double p = T[sl[0]], b = T[sl[1]], c = T[sl[2]], e = T[sl[3]], f = T[sl[4]];
-                diffT += d2(p, b, c, e, f) + d1r * d1(p, b, c, e, f) * inv_rho;
-                cT[d] = near ? 0.5 * (e - b) : weno3(p, b, c, e, f, u[d]);
-            }
+        for (int k = 0; k < NSP; ++k) {
+            const double p = A.Y[0][k], b = A.Y[1][k], e = A.Y[2][k], f = A.Y[3][k];
+            diffY[k] += d2(p, b, Y0[k], e, f) + d1r * d1(p, b, Y0[k], e, f) * inv_rho;
+            cY[k] = near ? 0.5 * (e - b) : weno3(p, b, Y0[k], e, f, ud);
+            sumc += cY[k];
+        }
 #pragma unroll
-            for (int k = 0; k < NSP; ++k) {
-                const double p = Y[sl[0]][k], b = Y[sl[1]][k], c = Y[sl[2]][k], e = Y[sl[3]][k], f = Y[sl[4]][k];
-                diffY[k] += d2(p, b, c, e, f) + d1r * d1(p, b, c, e, f) * inv_rho;
-                cY[d][k] = near ? 0.5 * (e - b) : weno3(p, b, c, e, f, u[d]);
-                sumc[d] += cY[d][k];
-            }
-            grad[d] = d1r;
+        for (int k = 0; k < NSP; ++k) l -= lsc[1 + k] * (cY[k] - Y0[k] * sumc);
+        us += ud * sumc;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            grad[a] = a == d ? d1r : grad[a];
+            luc[a] = a == d ? l : luc[a];
         }
     }
     diffT *= P.alpha;
@@ -856,12 +1009,9 @@ __device__ void cell_vjp_collision(const KParams &P, const CellIn<Q, NSP> &in, d
         },
         srcT, srcY);
     const double DtT = diffT + srcT;
-    double DtY[NSP], invWs = 0.0;
+    double DtY[NSP];
 #pragma unroll
-    for (int k = 0; k < NSP; ++k) {
-        DtY[k] = diffY[k] + srcY[k];
-        invWs += Y0[k] * P.invW[k];
-    }
+    for (int k = 0; k < NSP; ++k) DtY[k] = diffY[k] + srcY[k];
     const double Wm = rcp(invWs);
     const double inv_T0 = rcp(T0);
     double Lam = DtT * inv_T0;
@@ -870,167 +1020,190 @@ __device__ void cell_vjp_collision(const KParams &P, const CellIn<Q, NSP> &in, d
 
     // xi_i = cs2 (feq_i - w_i) proj_i + w_i rho cs2 Lam, feq_i and proj_i
     // from u and grad (recomputed in the reverse)
-    const double uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
-    auto xi_of = [&](int i, double &feq, double &proj) {
-        const double wi = L::w(i);
-        const double cu = L::cx(i) * u[0] + L::cy(i) * u[1] + L::cz(i) * u[2];
-        feq = wi * (1.0 + 3.0 * cu + 4.5 * cu * cu - 1.5 * uu);
-        proj = (L::cx(i) - u[0]) * grad[0] + (L::cy(i) - u[1]) * grad[1] + (L::cz(i) - u[2]) * grad[2];
-        return kCs2 * (feq - wi) * proj + wi * rho * kCs2 * Lam;
+    struct Feq {
+        double feq, proj, cu;
+    };
+    auto feq_of = [](auto I, const double (&u)[3], const double (&grad)[3], double uu, double ug) -> Feq {
+        constexpr int i = decltype(I)::value;
+        const double cu = dot_c<Q, i>(u);
+        return {L::w(i) * (1.0 + 3.0 * cu + 4.5 * cu * cu - 1.5 * uu), dot_c<Q, i>(grad) - ug, cu};
     };
     const double half_inv = 0.5 * inv_rc;
     double hx[Q], pi = 0.0;
-#pragma unroll
-    for (int i = 0; i < Q; ++i) {
-        double feq, proj;
-        hx[i] = g[i] * inv_rc + xi_of(i, feq, proj) * half_inv;
-        pi += hx[i];
+    {
+        const double uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
+        const double ug = u[0] * grad[0] + u[1] * grad[1] + u[2] * grad[2];
+        sfor<0, Q>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            const Feq f = feq_of(I, u, grad, uu, ug);
+            const double xi = kCs2 * (f.feq - L::w(i)) * f.proj + L::w(i) * rho * kCs2 * Lam;
+            hx[i] = g[i] * inv_rc + xi * half_inv;
+            pi += hx[i];
+        });
     }
     const double sh = 1.0 - pi;
 #pragma unroll
     for (int i = 0; i < Q; ++i) hx[i] += L::w(i) * sh;
-    // moments (kept: kr, the relaxed central moments; the passes' other
-    // inputs are recomputed in the reverse)
+    // the relaxed central moments (the passes' inputs are recomputed in the
+    // reverse)
     double kr[Q];
 #pragma unroll
     for (int i = 0; i < Q; ++i) kr[i] = hx[i];
+    if constexpr (Q == 27) {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) hxs[i * kBlock + threadIdx.x] = hx[i];
+    }
+    auto hx_at = [&](int i) -> double {
+        if constexpr (Q == 27)
+            return hxs[i * kBlock + threadIdx.x];
+        else
+            return hx[i];
+    };
     central_fwd<Q>(kr, u);
     relax<Q>(kr, P.omega2, P.omega3, P.omega4);
     const double rc = rho * kCs2;
 
     // ------------------------------------------------------ reverse
-    const long long c_self = in.cell[0];
-    double lo[Q + 1 + NSP];
+    double lu[3], lrho = 0.0, linv_rc = 0.0;
 #pragma unroll
-    for (int i = 0; i < Q; ++i) lo[i] = out.lo_pop[(long long)i * P.N + c_self];
-#pragma unroll
-    for (int k = 0; k < 1 + NSP; ++k) lo[Q + k] = out.lo_sc[(long long)k * P.N + c_self];
-    double lu[3] = {0.0, 0.0, 0.0}, lrho = 0.0, linv_rc = 0.0;
+    for (int d = 0; d < 3; ++d) lu[d] = luc[d];
 
-    // out_i = rc (h3_i - w_i sh) + xi_i / 2, h3 = central_inv(kr)
+    // out_i = rc (h3_i - w_i sh) + xi_i / 2, h3 = central_inv(kr); the passes
+    // in x and y plane by plane
     double lh[Q], lrc = 0.0, lsh = 0.0;
-    {
-        double iz[Q], iy[Q];
 #pragma unroll
-        for (int i = 0; i < Q; ++i) iz[i] = kr[i];
+    for (int i = 0; i < Q; ++i) lh[i] = plane_at(out.lo_pop, P.N, i, self);
+    {
+        double(&iz)[Q] = kr;  // in place: the z pass's input is its output's transform
         if constexpr (Q == 27) {
 #pragma unroll
             for (int r = 0; r < 9; ++r) cm_inv_line(iz[r], iz[r + 9], iz[r + 18], u[2]);
         }
 #pragma unroll
-        for (int i = 0; i < Q; ++i) iy[i] = iz[i];
+        for (int zp = 0; zp < Q / 9; ++zp) {
+            const int o = 9 * zp;
+            double iy[9];
 #pragma unroll
-        for (int zp = 0; zp < Q / 9; ++zp)
+            for (int p = 0; p < 9; ++p) iy[p] = iz[o + p];
 #pragma unroll
-            for (int p = 0; p < 3; ++p) cm_inv_line(iy[9 * zp + p], iy[9 * zp + p + 3], iy[9 * zp + p + 6], u[1]);
-        double h3[Q];
+            for (int p = 0; p < 3; ++p) cm_inv_line(iy[p], iy[p + 3], iy[p + 6], u[1]);
 #pragma unroll
-        for (int i = 0; i < Q; ++i) h3[i] = iy[i];
+            for (int l = 0; l < 3; ++l) {
+                double h3[3] = {iy[3 * l], iy[3 * l + 1], iy[3 * l + 2]};
+                cm_inv_line(h3[0], h3[1], h3[2], u[0]);
 #pragma unroll
-        for (int l = 0; l < Q / 3; ++l) cm_inv_line(h3[3 * l], h3[3 * l + 1], h3[3 * l + 2], u[0]);
-#pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            lh[i] = rc * lo[i];
-            lrc += lo[i] * (h3[i] - L::w(i) * sh);
-            lsh -= rc * L::w(i) * lo[i];
-        }
-        // central_inv, reversed
-#pragma unroll
-        for (int l = 0; l < Q / 3; ++l)
-            lu[0] += cm_inv_line_adj(iy[3 * l], iy[3 * l + 1], iy[3 * l + 2], u[0], lh[3 * l], lh[3 * l + 1],
-                                     lh[3 * l + 2]);
-#pragma unroll
-        for (int zp = 0; zp < Q / 9; ++zp)
-#pragma unroll
-            for (int p = 0; p < 3; ++p) {
-                const int i0 = 9 * zp + p, i1 = i0 + 3, i2 = i0 + 6;
-                lu[1] += cm_inv_line_adj(iz[i0], iz[i1], iz[i2], u[1], lh[i0], lh[i1], lh[i2]);
+                for (int q = 0; q < 3; ++q) {
+                    const int i = o + 3 * l + q;
+                    lrc += lh[i] * (h3[q] - L::w(i) * sh);
+                    lh[i] *= rc;
+                    lsh -= L::w(i) * lh[i];
+                }
+                lu[0] += cm_inv_line_adj(iy[3 * l], iy[3 * l + 1], iy[3 * l + 2], u[0], lh[o + 3 * l],
+                                         lh[o + 3 * l + 1], lh[o + 3 * l + 2]);
             }
+#pragma unroll
+            for (int p = 0; p < 3; ++p)
+                lu[1] += cm_inv_line_adj(iz[o + p], iz[o + p + 3], iz[o + p + 6], u[1], lh[o + p], lh[o + p + 3],
+                                         lh[o + p + 6]);
+        }
         if constexpr (Q == 27) {
 #pragma unroll
-            for (int r = 0; r < 9; ++r)
-                lu[2] += cm_inv_line_adj(kr[r], kr[r + 9], kr[r + 18], u[2], lh[r], lh[r + 9], lh[r + 18]);
+            for (int r = 0; r < 9; ++r) {
+                cm_fwd_line(iz[r], iz[r + 9], iz[r + 18], u[2]);
+                lu[2] += cm_inv_line_adj(iz[r], iz[r + 9], iz[r + 18], u[2], lh[r], lh[r + 9], lh[r + 18]);
+            }
         }
     }
     relax_adj<Q>(lh, P.omega2, P.omega3, P.omega4);
     // central_fwd, reversed
-    {
-        double hy[Q], hz[Q];
+    if constexpr (Q == 27) {
+        double hz[Q];
 #pragma unroll
-        for (int i = 0; i < Q; ++i) hy[i] = hx[i];
+        for (int i = 0; i < Q; ++i) hz[i] = hx_at(i);
 #pragma unroll
-        for (int l = 0; l < Q / 3; ++l) cm_fwd_line(hy[3 * l], hy[3 * l + 1], hy[3 * l + 2], u[0]);
-#pragma unroll
-        for (int i = 0; i < Q; ++i) hz[i] = hy[i];
+        for (int l = 0; l < Q / 3; ++l) cm_fwd_line(hz[3 * l], hz[3 * l + 1], hz[3 * l + 2], u[0]);
 #pragma unroll
         for (int zp = 0; zp < Q / 9; ++zp)
 #pragma unroll
             for (int p = 0; p < 3; ++p) cm_fwd_line(hz[9 * zp + p], hz[9 * zp + p + 3], hz[9 * zp + p + 6], u[1]);
-        if constexpr (Q == 27) {
 #pragma unroll
-            for (int r = 0; r < 9; ++r)
-                lu[2] += cm_fwd_line_adj(hz[r], hz[r + 9], hz[r + 18], u[2], lh[r], lh[r + 9], lh[r + 18]);
-        }
+        for (int r = 0; r < 9; ++r)
+            lu[2] += cm_fwd_line_adj(hz[r], hz[r + 9], hz[r + 18], u[2], lh[r], lh[r + 9], lh[r + 18]);
+    }
 #pragma unroll
-        for (int zp = 0; zp < Q / 9; ++zp)
+    for (int zp = 0; zp < Q / 9; ++zp) {
+        // (the plane's input read again, not kept)
+        if constexpr (Q == 27) asm volatile("" ::: "memory");
+        const int o = 9 * zp;
+        double hp[9], hy[9];
 #pragma unroll
-            for (int p = 0; p < 3; ++p) {
-                const int i0 = 9 * zp + p, i1 = i0 + 3, i2 = i0 + 6;
-                lu[1] += cm_fwd_line_adj(hy[i0], hy[i1], hy[i2], u[1], lh[i0], lh[i1], lh[i2]);
-            }
+        for (int p = 0; p < 9; ++p) hy[p] = hp[p] = hx_at(o + p);
 #pragma unroll
-        for (int l = 0; l < Q / 3; ++l)
-            lu[0] += cm_fwd_line_adj(hx[3 * l], hx[3 * l + 1], hx[3 * l + 2], u[0], lh[3 * l], lh[3 * l + 1],
-                                     lh[3 * l + 2]);
+        for (int l = 0; l < 3; ++l) cm_fwd_line(hy[3 * l], hy[3 * l + 1], hy[3 * l + 2], u[0]);
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+            lu[1] += cm_fwd_line_adj(hy[p], hy[p + 3], hy[p + 6], u[1], lh[o + p], lh[o + p + 3], lh[o + p + 6]);
+#pragma unroll
+        for (int l = 0; l < 3; ++l)
+            lu[0] += cm_fwd_line_adj(hp[3 * l], hp[3 * l + 1], hp[3 * l + 2], u[0], lh[o + 3 * l], lh[o + 3 * l + 1],
+                                     lh[o + 3 * l + 2]);
     }
     // hx = h0 + w sh, sh = 1 - sum h0
 #pragma unroll
     for (int i = 0; i < Q; ++i) lsh += L::w(i) * lh[i];
+    // (from here the outputs' adjoints are read again and the equilibrium's
+    // terms formed again: kept from above they would be 100 more values)
+    asm volatile("" : "+v"(u[0]), "+v"(u[1]), "+v"(u[2]), "+v"(grad[0]), "+v"(grad[1]), "+v"(grad[2])::"memory");
     double ag[Q];
     double lLam = 0.0, lgrad[3] = {0.0, 0.0, 0.0}, luu = 0.0;
-#pragma unroll
-    for (int i = 0; i < Q; ++i) {
-        const double lh0 = lh[i] - lsh;
-        double feq, proj;
-        const double xi = xi_of(i, feq, proj);
-        // h0 = g inv_rc + xi inv_rc / 2
-        ag[i] = inv_rc * lh0;
-        const double lxi = 0.5 * lo[i] + half_inv * lh0;
-        linv_rc += lh0 * (g[i] + 0.5 * xi);
-        // xi = cs2 (feq - w) proj + w rho cs2 Lam
-        const double wi = L::w(i);
-        const double lfeq = kCs2 * proj * lxi;
-        const double lproj = kCs2 * (feq - wi) * lxi;
-        lrho += wi * kCs2 * Lam * lxi;
-        lLam += wi * rho * kCs2 * lxi;
-        // proj = sum_d (c_d - u_d) grad_d
-        const double cd[3] = {(double)L::cx(i), (double)L::cy(i), (double)L::cz(i)};
+    {
+        const double uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
+        const double ug = u[0] * grad[0] + u[1] * grad[1] + u[2] * grad[2];
+        double lug = 0.0;
+        sfor<0, Q>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            constexpr double wi = L::w(i);
+            const double lh0 = lh[i] - lsh;
+            const Feq f = feq_of(I, u, grad, uu, ug);
+            // h0 = g inv_rc + xi inv_rc / 2 = hx - w sh
+            ag[i] = inv_rc * lh0;
+            const double lxi = 0.5 * plane_at(out.lo_pop, P.N, i, self) + half_inv * lh0;
+            linv_rc += lh0 * (rc * (hx_at(i) - wi * sh));
+            // xi = cs2 (feq - w) proj + w rho cs2 Lam
+            const double lfeq = kCs2 * f.proj * lxi;
+            const double lproj = kCs2 * (f.feq - wi) * lxi;
+            lLam += wi * lxi;
+            // proj = sum_d c_d grad_d - sum_d u_d grad_d
+            add_c<Q, i>(lgrad, lproj);
+            lug -= lproj;
+            // feq = w (1 + 3 cu + 9/2 cu^2 - 3/2 uu)
+            add_c<Q, i>(lu, wi * (3.0 + 9.0 * f.cu) * lfeq);
+            luu -= 1.5 * wi * lfeq;
+        });
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
-            lgrad[d] += lproj * (cd[d] - u[d]);
-            lu[d] -= lproj * grad[d];
+            lgrad[d] += lug * u[d];
+            lu[d] += lug * grad[d] + 2.0 * u[d] * luu;
         }
-        // feq = w (1 + 3 cu + 9/2 cu^2 - 3/2 uu)
-        const double cu = cd[0] * u[0] + cd[1] * u[1] + cd[2] * u[2];
-        const double lcu = wi * (3.0 + 9.0 * cu) * lfeq;
-        luu -= 1.5 * wi * lfeq;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) lu[d] += cd[d] * lcu;
+        lrho += kCs2 * Lam * lLam;
+        lLam *= rho * kCs2;
     }
-#pragma unroll
-    for (int d = 0; d < 3; ++d) lu[d] += 2.0 * u[d] * luu;
     lrho += kCs2 * lrc;
 
+    // (the scalars and their outputs' adjoints, too, are read again)
+    asm volatile("" ::: "memory");
+    T0 = plane_at(sc, P.N, 0, self);
+#pragma unroll
+    for (int k = 0; k < NSP; ++k) Y0[k] = plane_at(sc, P.N, 1 + k, self);
+#pragma unroll
+    for (int k = 0; k < NS; ++k) lsc[k] = plane_at(out.lo_sc, P.N, k, self);
     // scalar outputs: T' = T0 - CT + DtT, Y' = Y0 - CY + DtY
-    const double lTo = lo[Q];
-    double aT0 = lTo + wT0, aY0[NSP];
-    const double lCT = -lTo;
-    double lDtT = lTo, lCY[NSP], lDtY[NSP];
+    double aT0 = lsc[0] + wT0, aY0[NSP];
+    double lDtT = lsc[0], lDtY[NSP];
 #pragma unroll
     for (int k = 0; k < NSP; ++k) {
-        aY0[k] = lo[Q + 1 + k];
-        lCY[k] = -lo[Q + 1 + k];
-        lDtY[k] = lo[Q + 1 + k];
+        aY0[k] = lsc[1 + k] + lsc[1 + k] * us;
+        lDtY[k] = lsc[1 + k];
     }
     // Lam = DtT / T0 + sum_k Wm / W_k DtY_k, Wm = 1 / sum_k Y0_k / W_k
     lDtT += lLam * inv_T0;
@@ -1044,34 +1217,23 @@ __device__ void cell_vjp_collision(const KParams &P, const CellIn<Q, NSP> &in, d
     const double linvWs = -lWm * Wm * Wm;
 #pragma unroll
     for (int k = 0; k < NSP; ++k) aY0[k] += linvWs * P.invW[k];
-    // the convection's dependence on u (CT = sum_d u_d cT_d, CY_k = sum_d
-    // u_d (cY_k - Y0_k sumc)) and on Y0 through sumc's factor
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-        lu[d] += lCT * cT[d];
-#pragma unroll
-        for (int k = 0; k < NSP; ++k) {
-            lu[d] += lCY[k] * (cY[d][k] - Y0[k] * sumc[d]);
-            aY0[k] -= lCY[k] * u[d] * sumc[d];
-        }
-    }
     // u = m / (rho cs2)
+    double lm[3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-        const double lm = lu[d] * inv_rc;
+        lm[d] = lu[d] * inv_rc;
         linv_rc += lu[d] * m[d];
-#pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            const int c = d == 0 ? L::cx(i) : d == 1 ? L::cy(i) : L::cz(i);
-            if (c != 0) ag[i] += c * lm;
-        }
     }
+    sfor<0, Q>([&](auto I) { ag[decltype(I)::value] += dot_c<Q, decltype(I)::value>(lm); });
     lrho -= linv_rc * inv_rc * inv_rho;
 
     // pull streaming reads every population entry at most once (the source
     // cell's, or the cell's own opposite entry behind a wall)
-#pragma unroll
-    for (int i = 0; i < Q; ++i) out.lam_pop[(long long)in.tdir[i] * P.N + in.tcell[i]] = ag[i];
+    {
+        AdjCell c2 = c;  // (the entries computed again, not kept)
+        asm volatile("" : "+v"(c2.idx));
+        pull_entries<Q>(P, c2, out.lam_pop, [&](auto I, double &v) { v = ag[decltype(I)::value]; });
+    }
     // the source, reversed
     {
         double ls[NS];
@@ -1080,19 +1242,19 @@ __device__ void cell_vjp_collision(const KParams &P, const CellIn<Q, NSP> &in, d
         for (int k = 0; k < NSP; ++k) ls[1 + k] = lDtY[k];
         chem_vjp<NSP>(P, tab, T0, Y0, ls, aT0, aY0, out.lam_param);
     }
-    double *mid = out.mid + c_self;
-    mid[(long long)M::ls * P.N] = lDtT;
+    auto mid = [&](int k) -> double & { return plane_at(out.mid, P.N, k, self); };
+    mid(M::ls) = lDtT;
 #pragma unroll
-    for (int k = 0; k < NSP; ++k) mid[(long long)(M::ls + 1 + k) * P.N] = lDtY[k];
+    for (int k = 0; k < NSP; ++k) mid(M::ls + 1 + k) = lDtY[k];
 #pragma unroll
     for (int d = 0; d < D; ++d) {
-        mid[(long long)(M::lgrad + d) * P.N] = lgrad[d];
-        mid[(long long)(M::u + d) * P.N] = u[d];
+        mid(M::lgrad + d) = lgrad[d];
+        mid(M::u + d) = u[d];
     }
-    mid[(long long)M::aT0 * P.N] = aT0;
+    mid(M::aT0) = aT0;
 #pragma unroll
-    for (int k = 0; k < NSP; ++k) mid[(long long)(M::aY0 + k) * P.N] = aY0[k];
-    mid[(long long)M::lR0 * P.N] = lrho;
+    for (int k = 0; k < NSP; ++k) mid(M::aY0 + k) = aY0[k];
+    mid(M::lR0) = lrho;
 }
 
 // Second half: the reverse of the finite-difference stencils (diffusion,
@@ -1102,36 +1264,37 @@ __device__ void cell_vjp_collision(const KParams &P, const CellIn<Q, NSP> &in, d
 // Y (atomically, per axis as soon as its slots are finished), of the wall
 // temperatures and of A_j, Ta_j.
 template <int Q, int NSP>
-__device__ void cell_vjp_stencil(const KParams &P, const CellIn<Q, NSP> &in, double wq, const AdjOut &out)
+__device__ __forceinline__ void cell_vjp_stencil(const KParams &P, const AdjCell &c, double wq, const AdjOut &out)
 {
     using L = Lat<Q>;
     using M = AdjMid<Lat<Q>::D, NSP>;
-    constexpr int D = L::D, S = n_slots<Q>(), NS = 1 + NSP;
+    constexpr int D = L::D, NS = 1 + NSP;
     constexpr double c1[5] = {1.0 / 12.0, -8.0 / 12.0, 0.0, 8.0 / 12.0, -1.0 / 12.0};
     constexpr double c2[5] = {-1.0 / 12.0, 16.0 / 12.0, -30.0 / 12.0, 16.0 / 12.0, -1.0 / 12.0};
     const double c0 = P.T_ref_over_W_ref;
-    const long long c_self = in.cell[0];
-    const double *mid = out.mid + c_self;
-    double ls[NS], u[3] = {0.0, 0.0, 0.0}, lgrad[3] = {0.0, 0.0, 0.0};
+    const uint32_t self = (uint32_t)c.idx * 8u;
+    const double *sc = (const double *)P.sc_in;
+    auto mid = [&](int k) -> double { return plane_at(out.mid, P.N, k, self); };
+    double ls[NS];
 #pragma unroll
-    for (int o = 0; o < NS; ++o) ls[o] = mid[(long long)(M::ls + o) * P.N];
+    for (int o = 0; o < NS; ++o) ls[o] = mid(M::ls + o);
+    double aT0 = mid(M::aT0), aY0[NSP];
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-        lgrad[d] = mid[(long long)(M::lgrad + d) * P.N];
-        u[d] = mid[(long long)(M::u + d) * P.N];
-    }
-    double aT0 = mid[(long long)M::aT0 * P.N], aY0[NSP];
-#pragma unroll
-    for (int k = 0; k < NSP; ++k) aY0[k] = mid[(long long)(M::aY0 + k) * P.N];
-    double lR0 = mid[(long long)M::lR0 * P.N];
-    const double lCT = -out.lo_sc[c_self];
+    for (int k = 0; k < NSP; ++k) aY0[k] = mid(M::aY0 + k);
+    double lR0 = mid(M::lR0);
+    const double lCT = -plane_at(out.lo_sc, P.N, 0, self);
     double lCY[NSP];
 #pragma unroll
-    for (int k = 0; k < NSP; ++k) lCY[k] = -out.lo_sc[(long long)(1 + k) * P.N + c_self];
+    for (int k = 0; k < NSP; ++k) lCY[k] = -plane_at(out.lo_sc, P.N, 1 + k, self);
 
-    double T[S], Y[S][NSP], R[S], Sw[S];
-    fill_stencil<Q, NSP>(P, in, T, Y, R, Sw);
-    const double inv_rho = rcp(R[0]);
+    double Y0[NSP], Sw0 = 0.0;
+    const double T0 = plane_at(sc, P.N, 0, self);
+#pragma unroll
+    for (int k = 0; k < NSP; ++k) {
+        Y0[k] = plane_at(sc, P.N, 1 + k, self);
+        Sw0 += Y0[k] * P.invW[k];
+    }
+    const double rho = c0 * rcp(T0 * Sw0), inv_rho = rcp(rho);
     const double ldT = P.alpha * ls[0];
     double ldY[NSP];
 #pragma unroll
@@ -1139,152 +1302,130 @@ __device__ void cell_vjp_stencil(const KParams &P, const CellIn<Q, NSP> &in, dou
     double linv_rho = 0.0;
 
     // the axes, reversed; each axis's four slots finished and scattered
-#pragma unroll
+#pragma unroll 1
     for (int d = 0; d < D; ++d) {
-        const int sl[5] = {1 + 4 * d, 2 + 4 * d, 0, 3 + 4 * d, 4 + 4 * d};
-        bool near = false;
-#pragma unroll
-        for (int j = 0; j < 5; ++j) near |= in.kind[sl[j]] != kFluid;
-        // adjoints of the stencil's T, Y, rho (index 2: the cell, accumulated
-        // into aT0, aY0, lR0 at the end of the axis)
-        double aT[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, aY[5][NSP], lR[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-        double aTw[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int j = 0; j < 5; ++j)
-#pragma unroll
-            for (int k = 0; k < NSP; ++k) aY[j][k] = 0.0;
+        AdjAxis<NSP> A;
+        load_axis<NSP>(P, c, d, A);
+        const double ud = mid(M::u + d);
+        const bool near = A.near();
+        // adjoints of the stencil's values of one field at a time (index 2:
+        // the cell, accumulated into aT0, aY0, lR0), the density's first
+        double aTw[2] = {0.0, 0.0};
         // wall heat flux q += 2 alpha rho(Tw, Y0) (T0 - Tw), rho(Tw, Y0) = c0 / (Tw Sw0)
 #pragma unroll
-        for (int j = 1; j <= 3; j += 2)
-            if (in.kind[sl[j]] == kIso && wq != 0.0) {
-                const double Tw = in.Tw[sl[j]], rw = c0 * rcp(Tw * Sw[0]), f = 2.0 * P.alpha * wq;
+        for (int side = 0; side < 2; ++side)
+            if (A.kind(side ? 2 : 1) == kIso && wq != 0.0) {
+                const double Tw = A.Tw[side], rw = c0 * rcp(Tw * Sw0), f = 2.0 * P.alpha * wq;
                 aT0 += f * rw;
-                aTw[j] += f * (-rw * rcp(Tw) * (T[0] - Tw) - rw);
-                const double rwS = rw * rcp(Sw[0]);
+                aTw[side] += f * (-rw * rcp(Tw) * (T0 - Tw) - rw);
+                const double rwS = rw * rcp(Sw0);
 #pragma unroll
-                for (int k = 0; k < NSP; ++k) aY0[k] += f * (T[0] - Tw) * (-rwS * P.invW[k]);
+                for (int k = 0; k < NSP; ++k) aY0[k] += f * (T0 - Tw) * (-rwS * P.invW[k]);
             }
-        const double d1r = d1(R[sl[0]], R[sl[1]], R[sl[2]], R[sl[3]], R[sl[4]]);
-        double ld1r = lgrad[d];
-        // diffusion: d2(phi) + d1r d1(phi) / rho
-        {
-            const double dT1 = d1(T[sl[0]], T[sl[1]], T[sl[2]], T[sl[3]], T[sl[4]]);
-#pragma unroll
-            for (int j = 0; j < 5; ++j) aT[j] += ldT * (c2[j] + d1r * inv_rho * c1[j]);
-            ld1r += ldT * dT1 * inv_rho;
-            linv_rho += ldT * d1r * dT1;
-        }
+        const double d1r = d1(A.R[0], A.R[1], rho, A.R[2], A.R[3]);
+        // diffusion: d2(phi) + d1r d1(phi) / rho, through d1r = d1(R) and rho
+        const double dT1 = d1(A.T[0], A.T[1], T0, A.T[2], A.T[3]);
+        double s1 = ldT * dT1, lsumc = 0.0;
 #pragma unroll
         for (int k = 0; k < NSP; ++k) {
-            const double dY1 = d1(Y[sl[0]][k], Y[sl[1]][k], Y[sl[2]][k], Y[sl[3]][k], Y[sl[4]][k]);
-#pragma unroll
-            for (int j = 0; j < 5; ++j) aY[j][k] += ldY[k] * (c2[j] + d1r * inv_rho * c1[j]);
-            ld1r += ldY[k] * dY1 * inv_rho;
-            linv_rho += ldY[k] * d1r * dY1;
+            s1 += ldY[k] * d1(A.Y[0][k], A.Y[1][k], Y0[k], A.Y[2][k], A.Y[3][k]);
+            lsumc -= lCY[k] * ud * Y0[k];
         }
-        // convection of T: CT += u_d cT_d, cT_d from the stencil
-        {
-            const double lc = lCT * u[d];
+        linv_rho += d1r * s1;
+        const double ld1r = mid(M::lgrad + d) + s1 * inv_rho;
+        double lR[5];
+#pragma unroll
+        for (int j = 0; j < 5; ++j) lR[j] = ld1r * c1[j];
+        // Adjoint of a field with the adjoint ld of its diffusion and lc of its
+        // convection's derivative
+        const double e1 = d1r * inv_rho;
+        auto field = [&](double m2, double m1, double v0, double p1, double p2, double ld, double lc, double (&l)[5]) {
+#pragma unroll
+            for (int j = 0; j < 5; ++j) l[j] = ld * (c2[j] + e1 * c1[j]);
             if (near) {
-                aT[3] += 0.5 * lc;
-                aT[1] -= 0.5 * lc;
+                l[3] += 0.5 * lc;
+                l[1] -= 0.5 * lc;
             } else {
-                weno3_adj(T[sl[0]], T[sl[1]], T[sl[2]], T[sl[3]], T[sl[4]], u[d], lc, aT);
+                weno3_adj(m2, m1, v0, p1, p2, ud, lc, l);
             }
-        }
-        // convection of Y: CY_k += u_d (cY_k - Y0_k sumc), sumc = sum_k cY_k
-        double lsumc = 0.0;
+        };
+        // Ghosts of this axis onto their images (the cell, index 2, or a first
+        // neighbour, index 1 or 3): slot j's value is s v(image) + constant, s
+        // = -1 behind Dirichlet walls (T, R; Y at inlets).  add: what the image
+        // receives beyond s l[a]
+        auto onto_images = [&](double (&l)[5], bool species, auto &&add) {
 #pragma unroll
-        for (int k = 0; k < NSP; ++k) lsumc -= lCY[k] * u[d] * Y[0][k];
+            for (int j = 0; j < 4; ++j) {
+                const int kd = A.kind(j), a = j < 2 ? j : j + 1, side = j < 2 ? 0 : 1, im = A.image(j);
+                const int li = im == kImgCell ? 2 : (im == kImgSame) == (side == 0) ? 1 : 3;
+                const bool odd = kd == kInflow || (kd == kIso && !species);
+                double gv = odd ? -l[a] : l[a];
+                if (kd == kIso) gv += add(j, side, a);
+                if (kd == kFluid) gv = 0.0;
+                l[1] += li == 1 ? gv : 0.0;
+                l[3] += li == 3 ? gv : 0.0;
+                l[2] += li == 2 ? gv : 0.0;
+            }
+        };
+        // Densities at isothermal ghosts: R = 2 c0 / (Tw Sw) - R(image), onto
+        // Tw and the image's Y (f[j] invW_k)
+        double f[4] = {0.0, 0.0, 0.0, 0.0};
+        if (near) {
+            onto_images(lR, false, [&](int j, int side, int a) -> double {
+                const double Tw = A.Tw[side], rw = c0 * rcp(Tw * A.Sw[j]);
+                aTw[side] -= 2.0 * lR[a] * rw * rcp(Tw);
+                f[j] = -2.0 * lR[a] * rw * rcp(A.Sw[j]);
+                return 0.0;
+            });
+        }
+        // what each slot's cell receives, stored for the gather (0 at ghost
+        // slots): with the densities R = c0 / (T Sw) onto T and Y
+        const int nb = 4 * d * NS;
+        {
+            double l[5];
+            field(A.T[0], A.T[1], T0, A.T[2], A.T[3], ldT, lCT * ud, l);
+            if (near)
+                onto_images(l, false, [&](int, int side, int a) -> double {
+                    aTw[side] += 2.0 * l[a];
+                    return 0.0;
+                });
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int a = j < 2 ? j : j + 1;
+                plane_at(out.nb, P.N, nb + j * NS, self) =
+                    A.kind(j) == kFluid ? l[a] - lR[a] * (A.R[j] * rcp(A.T[j])) : 0.0;
+            }
+            aT0 += l[2];
+        }
+        if (near) {
+#pragma unroll
+            for (int side = 0; side < 2; ++side)
+                if (A.wall[side] >= 0) atomicAdd(&out.dwallT[A.wall[side]], aTw[side]);
+        }
+        double rS[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) rS[j] = A.R[j] * rcp(A.Sw[j]) * lR[j < 2 ? j : j + 1];
 #pragma unroll
         for (int k = 0; k < NSP; ++k) {
-            const double lc = lCY[k] * u[d] + lsumc;
-            if (near) {
-                aY[3][k] += 0.5 * lc;
-                aY[1][k] -= 0.5 * lc;
-            } else {
-                double l5[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-                weno3_adj(Y[sl[0]][k], Y[sl[1]][k], Y[sl[2]][k], Y[sl[3]][k], Y[sl[4]][k], u[d], lc, l5);
+            double l[5];
+            field(A.Y[0][k], A.Y[1][k], Y0[k], A.Y[2][k], A.Y[3][k], ldY[k], lCY[k] * ud + lsumc, l);
+            if (near) onto_images(l, true, [&](int j, int, int) -> double { return f[j] * P.invW[k]; });
 #pragma unroll
-                for (int j = 0; j < 5; ++j) aY[j][k] += l5[j];
+            for (int j = 0; j < 4; ++j) {
+                const int a = j < 2 ? j : j + 1;
+                plane_at(out.nb, P.N, nb + j * NS + 1 + k, self) = A.kind(j) == kFluid ? l[a] - rS[j] * P.invW[k] : 0.0;
             }
+            aY0[k] += l[2];
         }
-        // d1r = d1(R)
-#pragma unroll
-        for (int j = 0; j < 5; ++j) lR[j] += ld1r * c1[j];
-
-        // ghosts of this axis onto their images (the cell, j = 2, or a first
-        // neighbour, j = 1 or 3) and their wall temperatures
-#pragma unroll
-        for (int j = 0; j < 5; ++j) {
-            if (j == 2) continue;
-            const int s = sl[j], kd = in.kind[s];
-            if (kd == kFluid) continue;
-            const int im = in.img[s];
-            // local index of the image: slot img_lo(s) is j = 1, img_hi(s) is j = 3
-            const bool second = j == 0 || j == 4;
-            const bool ia = second && im == img_lo(s), ib = second && !ia && im == img_hi(s);
-            const int li = ia ? 1 : ib ? 3 : 2;
-            const double fa = ia ? 1.0 : 0.0, fb = ib ? 1.0 : 0.0;
-            const double Swi = fa * Sw[sl[1]] + fb * Sw[sl[3]] + (1.0 - fa - fb) * Sw[0];
-            double gT, gY[NSP], gR;  // what the image receives
-            if (kd == kIso) {
-                const double Tw = in.Tw[s], rw = c0 * rcp(Tw * Swi), rwS = rw * rcp(Swi);
-                aTw[j] += 2.0 * aT[j] + 2.0 * lR[j] * (-rw * rcp(Tw));
-                gT = -aT[j];
-#pragma unroll
-                for (int k = 0; k < NSP; ++k) gY[k] = aY[j][k] + 2.0 * lR[j] * (-rwS * P.invW[k]);
-                gR = -lR[j];
-            } else if (kd == kInflow) {
-                gT = -aT[j];
-#pragma unroll
-                for (int k = 0; k < NSP; ++k) gY[k] = -aY[j][k];
-                gR = -lR[j];
-            } else {
-                gT = aT[j];
-#pragma unroll
-                for (int k = 0; k < NSP; ++k) gY[k] = aY[j][k];
-                gR = lR[j];
-            }
-            aT[1] += li == 1 ? gT : 0.0;
-            aT[3] += li == 3 ? gT : 0.0;
-            aT[2] += li == 2 ? gT : 0.0;
-            lR[1] += li == 1 ? gR : 0.0;
-            lR[3] += li == 3 ? gR : 0.0;
-            lR[2] += li == 2 ? gR : 0.0;
-#pragma unroll
-            for (int k = 0; k < NSP; ++k) {
-                aY[1][k] += li == 1 ? gY[k] : 0.0;
-                aY[3][k] += li == 3 ? gY[k] : 0.0;
-                aY[2][k] += li == 2 ? gY[k] : 0.0;
-            }
-            if (kd == kIso && in.wall[s] >= 0) atomicAdd(&out.dwallT[in.wall[s]], aTw[j]);
-        }
-        // the axis's fluid slots: densities R = c0 / (T Sw) onto T and Y; what
-        // each slot's cell receives, stored for the gather (0 at ghost slots)
-#pragma unroll
-        for (int j = 0; j < 5; ++j) {
-            if (j == 2) continue;
-            const int s = sl[j];
-            const bool fl = in.kind[s] == kFluid;
-            const double rT = fl ? R[s] * rcp(T[s]) : 0.0, rS = fl ? R[s] * rcp(Sw[s]) : 0.0;
-            double *nb = out.nb + (long long)(s - 1) * NS * P.N + c_self;
-            nb[0] = fl ? aT[j] - lR[j] * rT : 0.0;
-#pragma unroll
-            for (int k = 0; k < NSP; ++k) nb[(long long)(1 + k) * P.N] = fl ? aY[j][k] - lR[j] * rS * P.invW[k] : 0.0;
-        }
-        aT0 += aT[2];
         lR0 += lR[2];
-#pragma unroll
-        for (int k = 0; k < NSP; ++k) aY0[k] += aY[2][k];
     }
 
     // inv_rho = 1 / rho; the cell's own slot
     lR0 -= linv_rho * inv_rho * inv_rho;
-    const double rT0 = R[0] * rcp(T[0]), rS0 = R[0] * rcp(Sw[0]);
-    out.lam_sc[c_self] = aT0 - lR0 * rT0;
+    const double rT0 = rho * rcp(T0), rS0 = rho * rcp(Sw0);
+    plane_at(out.lam_sc, P.N, 0, self) = aT0 - lR0 * rT0;
 #pragma unroll
-    for (int k = 0; k < NSP; ++k) out.lam_sc[(long long)(1 + k) * P.N + c_self] = aY0[k] - lR0 * rS0 * P.invW[k];
+    for (int k = 0; k < NSP; ++k) plane_at(out.lam_sc, P.N, 1 + k, self) = aY0[k] - lR0 * rS0 * P.invW[k];
 }
 
 struct AdjParams {
@@ -1302,40 +1443,38 @@ struct AdjParams {
 };
 
 template <int Q, int NSP>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) adjoint_collision_kernel(const AdjParams AP)
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(Q == 27 ? 1 : 2))) adjoint_collision_kernel(const AdjParams AP)
 {
     const KParams &P = AP.k;
-    const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    __shared__ double red[2 * LBFD_MAX_REACTIONS];
+    __shared__ double red[2 * LBFD_MAX_REACTIONS * kParamCopies];
     __shared__ double tab[kExpTabN];
-    for (int j = threadIdx.x; j < 2 * LBFD_MAX_REACTIONS; j += blockDim.x) red[j] = 0.0;
+    __shared__ double hxs[Q == 27 ? Q * kBlock : 1];
+    for (int j = threadIdx.x; j < 2 * P.n_rx * kParamCopies; j += blockDim.x) red[j] = 0.0;
     for (int j = threadIdx.x; j < kExpTabN; j += blockDim.x) tab[j] = kExp2Tab[j];
     __syncthreads();
-    if (idx < P.N && P.mask[idx] == LBFD_FLUID) {
-        const int x = (int)(idx % P.nx), y = (int)((idx / P.nx) % P.ny), z = (int)(idx / ((long long)P.nx * P.ny));
-        CellIn<Q, NSP> in;
-        gather_inputs<Q, NSP>(P, x, y, z, idx, in);
+    AdjCell c;
+    if (adj_cell(P, c)) {
         const double wT0 = AP.obj_kind == LBFD_OBJ_FLAME_POSITION ? AP.obj_w : 0.0;
         AdjOut o{AP.lam_pop_next, AP.lam_sc_next, AP.lam_pop, AP.lam_sc, AP.dwallT, red, AP.mid, AP.nb};
-        cell_vjp_collision<Q, NSP>(P, in, wT0, tab, o);
+        cell_vjp_collision<Q, NSP>(P, c, wT0, tab, o, hxs);
     }
     __syncthreads();
-    for (int j = threadIdx.x; j < 2 * P.n_rx; j += blockDim.x)
-        if (red[j] != 0.0) atomicAdd(&AP.dparam[j], red[j]);
+    for (int j = threadIdx.x; j < 2 * P.n_rx; j += blockDim.x) {
+        double v = 0.0;
+        for (int q = 0; q < kParamCopies; ++q) v += red[j * kParamCopies + q];
+        if (v != 0.0) atomicAdd(&AP.dparam[j], v);
+    }
 }
 
 template <int Q, int NSP>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) adjoint_stencil_kernel(const AdjParams AP)
 {
     const KParams &P = AP.k;
-    const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= P.N || P.mask[idx] != LBFD_FLUID) return;
-    const int x = (int)(idx % P.nx), y = (int)((idx / P.nx) % P.ny), z = (int)(idx / ((long long)P.nx * P.ny));
-    CellIn<Q, NSP> in;
-    gather_inputs<Q, NSP, false>(P, x, y, z, idx, in);
+    AdjCell c;
+    if (!adj_cell(P, c)) return;
     const double wq = AP.obj_kind == LBFD_OBJ_WALL_HEAT_FLUX ? AP.obj_w : 0.0;
     AdjOut o{AP.lam_pop_next, AP.lam_sc_next, AP.lam_pop, AP.lam_sc, AP.dwallT, nullptr, AP.mid, AP.nb};
-    cell_vjp_stencil<Q, NSP>(P, in, wq, o);
+    cell_vjp_stencil<Q, NSP>(P, c, wq, o);
 }
 
 // The stencil scalars' adjoints: each fluid cell adds to its own share (in
@@ -1348,31 +1487,34 @@ __global__ void __launch_bounds__(kBlock) adjoint_gather_kernel(const AdjParams 
 {
     constexpr int S = n_slots<Q>(), NS = 1 + NSP;
     const KParams &P = AP.k;
-    const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= P.N || P.mask[idx] != LBFD_FLUID) return;
-    const int x = (int)(idx % P.nx), y = (int)((idx / P.nx) % P.ny), z = (int)(idx / ((long long)P.nx * P.ny));
-    const bool interior = P.code[idx] == kCodeInterior;
-    const long long st[3] = {1, P.nx, (long long)P.nx * P.ny};
+    AdjCell c;
+    if (!adj_cell(P, c)) return;
+    const uint32_t self = (uint32_t)c.idx * 8u;
+    const int st[3] = {1, P.nx, P.nx * P.ny};
     double acc[NS];
 #pragma unroll
-    for (int v = 0; v < NS; ++v) acc[v] = AP.lam_sc[(long long)v * P.N + idx];
+    for (int v = 0; v < NS; ++v) acc[v] = plane_at(AP.lam_sc, P.N, v, self);
 #pragma unroll
     for (int s = 1; s < S; ++s) {
-        const int d = (s - 1) / 4, j = (s - 1) % 4;
-        const int mm = j == 0 ? -2 : j == 1 ? -1 : j == 2 ? 1 : 2;
-        long long src = idx - mm * st[d];
-        bool ok = true;
-        if (!interior) {
-            const Nb c = classify(P, x - (d == 0 ? mm : 0), y - (d == 1 ? mm : 0), z - (d == 2 ? mm : 0));
-            ok = c.kind == kFluid;
-            src = ok ? c.idx : idx;
+        // (the slot of the opposite offset holds the source cell's kind; a
+        // fluid cell behind a first-neighbour wall, whose slot carries the
+        // wall's kind, stored 0)
+        const int d = (s - 1) / 4, j = (s - 1) % 4, mm = slot_offset(j);
+        const bool ok = decode_kind(c.scode, d, 3 - j) == kFluid;
+        int o = -mm * st[d];
+        if (c.bnd) {
+            const int x = d == 0 ? c.x : d == 1 ? c.y : c.z, n = d == 0 ? P.nx : d == 1 ? P.ny : P.nz;
+            o = (wrap_once(x - mm, n) - x) * st[d];
         }
-        const double *nb = AP.nb + (long long)(s - 1) * NS * P.N + src;
+        const uint32_t src = (uint32_t)((int)c.idx + (ok ? o : 0)) * 8u;
 #pragma unroll
-        for (int v = 0; v < NS; ++v) acc[v] += ok ? nb[(long long)v * P.N] : 0.0;
+        for (int v = 0; v < NS; ++v) {
+            const double b = plane_at(AP.nb, P.N, (s - 1) * NS + v, src);
+            acc[v] += ok ? b : 0.0;
+        }
     }
 #pragma unroll
-    for (int v = 0; v < NS; ++v) AP.lam_sc[(long long)v * P.N + idx] = acc[v];
+    for (int v = 0; v < NS; ++v) plane_at(AP.lam_sc, P.N, v, self) = acc[v];
 }
 
 struct TanParams {
