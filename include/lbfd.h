@@ -360,9 +360,10 @@ int lbfd_objective(lbfd_ctx *c, int64_t nsteps, double *J);
  * is cleared by a fill kernel at the start of every call.  Every call on a
  * GPU shares that GPU's array and leaves its contents there: calls that
  * overlap on one GPU (from several threads or streams) race and must be
- * serialised by the caller.  LBFD_EINVAL when the context's step needs more
- * than the array holds (512 + 104 bytes per step block: boxes up to about
- * 161,000 blocks of 256 cells); J is a host pointer; synchronous. */
+ * serialised by the caller.  LBFD_EINVAL when the context's box needs more
+ * than the array holds (512 + 104 bytes per block of 256 cells and per 256
+ * boundary cells: boxes up to about 161,000 blocks); J is a host pointer;
+ * synchronous. */
 int lbfd_objective_static(lbfd_ctx *c, int64_t nsteps, double *J);
 
 /* Discrete adjoint of the FP64 step.  Not a method of the paper: the paper

@@ -444,8 +444,8 @@ __device__ void chem_vjp(const KParams &P, const double *tab, double T0, const d
 #pragma unroll
             for (int k = 0; k < NSP; ++k) lrr += r.nu_mass[k] * lincY[k];
             lTc += lrr * rr * (r.b * invTc + r.Ta * invTc * invTc);
-            // (per-lane copies: on one address the compiler adds the lanes one
-            // by one in a loop, 96 -> 5 us of a 2-D level's 69)
+            // (copies by lane: on one address the compiler adds the lanes one
+            // after the other in a loop, 6 of 69 us of a 2-D level)
             double *lp = lam_param + 2 * j * kParamCopies + (threadIdx.x & (kParamCopies - 1));
             atomicAdd(lp, lrr * P.dt_phys * e * inv_nsub * pr);
             atomicAdd(lp + kParamCopies, -lrr * rr * invTc);
@@ -698,9 +698,15 @@ __device__ __forceinline__ void weno3_adj(double m2, double m1, double c0, doubl
 // the collision, the moments and the velocity's part of the convection: it
 // finishes the adjoints of the pulled populations and leaves, per cell, the
 // few adjoints the rest needs (AdjMid).  The second (adjoint_stencil_kernel)
-// reverses the finite-difference stencils, the ghosts and densities, and the
-// Arrhenius source, and scatters the stencil scalars' adjoints.  Split so
-// that each kernel's registers leave room for more than one wave per SIMD.
+// reverses the finite-difference stencils, the ghosts and densities, and
+// leaves the stencil scalars' adjoints for the gather.  Split so that each
+// kernel's live values fit the registers: what a kernel spills goes through
+// memory for every lane.  Measured a level, 1024 x 256 (D2Q9): 63, 43 and 16 us
+// for the collision, the stencils and the gather, 126, 147 and 90 MB that they
+// must move (29, 34, 21 us at a copy's rate; the gather's reads are partly in
+// the caches); 72 x 56 x 40 (D3Q27): 100, 59, 18 us.  Two waves a SIMD in D2Q9
+// and for the stencils (three spill: 127 and 88 us), one for the D3Q27
+// collision (two spill 395 registers: 209 us).
 
 // Fields of the per-cell state between the two kernels, [field][N]:
 // lDtT, lDtY_k (adjoints of the increments Dt), lgrad_d (of d1 rho), u_d,
@@ -716,7 +722,7 @@ struct AdjOut {
     const double *lo_pop;  // [Q][N] adjoint of the populations the step writes
     const double *lo_sc;   // [1+NSP][N] adjoint of the scalars the step writes
     double *lam_pop;    // [Q][N]: stored (every entry is pulled by one cell)
-    double *lam_sc;     // [1+NSP][N]: accumulated atomically
+    double *lam_sc;     // [1+NSP][N]: the cell's own share, completed by the gather
     double *dwallT;     // [N]: accumulated atomically
     double *lam_param;  // [2 n_rx][kParamCopies] in LDS: accumulated atomically
     double *mid;        // [AdjMid::n][N]
@@ -1259,10 +1265,9 @@ __device__ __forceinline__ void cell_vjp_collision(const KParams &P, const AdjCe
 
 // Second half: the reverse of the finite-difference stencils (diffusion,
 // the convection's dependence on the stencil values, d1 rho), the ghosts
-// and densities, the wall-heat-flux term (weight wq) and the Arrhenius
-// source, from the cell's AdjMid; scatters the adjoints of the stencil's T,
-// Y (atomically, per axis as soon as its slots are finished), of the wall
-// temperatures and of A_j, Ta_j.
+// and densities and the wall-heat-flux term (weight wq), from the cell's
+// AdjMid: the adjoints of the stencil's T, Y for the gather, field by field,
+// and of the wall temperatures (atomically).
 template <int Q, int NSP>
 __device__ __forceinline__ void cell_vjp_stencil(const KParams &P, const AdjCell &c, double wq, const AdjOut &out)
 {

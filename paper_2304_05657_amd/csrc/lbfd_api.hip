@@ -117,6 +117,8 @@ struct lbfd_ctx {
     std::vector<int> boundary_host;
     std::vector<uint8_t> mask_host;
     std::vector<double> wall_T_host;
+    char *adj_ws = nullptr;   // the adjoint's workspace between calls (AdjWorkspace)
+    size_t adj_bytes = 0;
     double *face_Td = nullptr;                                         // face_T in device memory
     ulonglong2 *cell_code = nullptr;  // [N] the boundary cells' pull and stencil codes
     int *bslot = nullptr;             // [N] position in the boundary list (with curved walls)
@@ -159,7 +161,8 @@ static void free_ctx(lbfd_ctx *c)
     void *ptrs[] = {c->pop[0], c->pop[1], c->sc[0], c->sc[1], c->mask, c->code, c->wall_T, c->outlet, c->outlet_un,
                     c->inflow_u, c->inflow_du, c->bq, c->bimg, c->img_rng, c->img_idx, c->img_w, c->img_val, c->sup_idx, c->sup_val,
                     c->fields, c->partials, c->diag_dev, c->bad_dev, c->rx_dev, c->rxk_dev, c->fluid,
-                    c->chem_order, c->chem_heavy, c->chem_count, c->face_Td, c->cell_code, c->bslot};
+                    c->chem_order, c->chem_heavy, c->chem_count, c->face_Td, c->cell_code, c->bslot,
+                    c->adj_ws};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
     delete c;
@@ -1489,6 +1492,44 @@ struct AdjBuffers {
 };
 }  // namespace
 
+// The workspace of one adjoint call: the context's, when it is large enough,
+// else a new one.  At the end the context keeps it if it is at most kAdjKeep
+// bytes, so that an optimisation
+// loop's calls allocate once, and a larger one is given back, whose allocation
+// is a small part of its call.
+constexpr size_t kAdjKeep = (size_t)1 << 30;
+namespace {
+struct AdjWorkspace {
+    lbfd_ctx *c;
+    char *p = nullptr;
+    size_t bytes;
+    AdjWorkspace(lbfd_ctx *ctx, size_t need) : c(ctx), bytes(need)
+    {
+        if (c->adj_bytes >= need) {
+            p = c->adj_ws;
+            bytes = c->adj_bytes;
+        } else {
+            if (c->adj_ws) (void)hipFree(c->adj_ws);
+            if (hipMalloc((void **)&p, need) != hipSuccess) p = nullptr;
+        }
+        c->adj_ws = nullptr;
+        c->adj_bytes = 0;
+    }
+    ~AdjWorkspace()
+    {
+        if (!p) return;
+        if (bytes <= kAdjKeep) {
+            // (after an error work may still be queued; the next call's wait
+            // for the stream comes before it uses the memory)
+            c->adj_ws = p;
+            c->adj_bytes = bytes;
+        } else {
+            (void)hipFree(p);
+        }
+    }
+};
+}  // namespace
+
 // The selected objective's share of level offset t: accumulate coefficients
 // (*acc += a diag[slot] + b) and the adjoint weight.
 struct ObjTerm {
@@ -1557,13 +1598,21 @@ int lbfd_objective(lbfd_ctx *c, int64_t nsteps, double *J)
 int lbfd_objective_static(lbfd_ctx *c, int64_t nsteps, double *J)
 {
     if (!c || !J || nsteps < 0) return fail(LBFD_EINVAL, "bad arguments");
-    const size_t need = kScratchPartials + (size_t)c->nblocks * kNDiag * sizeof(double);
+    // The limit counts blocks of 64 x 4 (64 x 2 x 2) cells and the boundary cells
+    // in blocks of 256, by eights, whatever the step's own blocks are; a box
+    // within it whose tiles are more than the array's rows (a long one a few
+    // cells thin) keeps its partials in the context's buffer.
+    const long long by = c->D == 2 ? 4 : 2, bz = c->D == 2 ? 1 : 2;
+    const long long rows = (c->p.nx + 63LL) / 64 * ((c->p.ny + by - 1) / by) * ((c->p.nz + bz - 1) / bz) +
+                           ((c->n_boundary + kBlock - 1) / kBlock + 7) / 8 * 8;
+    const size_t need = kScratchPartials + (size_t)rows * kNDiag * sizeof(double);
     if (need > kScratchBytes)
         return fail(LBFD_EINVAL, "lbfd_objective_static: this box needs %zu bytes of scratch, the static array "
                     "holds %zu (use lbfd_objective)", need, kScratchBytes);
     double *acc = (double *)(c->scratch + kScratchAcc);
     double *diag = (double *)(c->scratch + kScratchDiag);
     double *partials = (double *)(c->scratch + kScratchPartials);
+    if (kScratchPartials + (size_t)c->nblocks * kNDiag * sizeof(double) > kScratchBytes) partials = c->partials;
     hipError_t e = launch_fill(acc, 1, 0.0, c->stream);
     for (int64_t n = 0; n < nsteps && e == hipSuccess; ++n) {
         KParams k = c->base;
@@ -1710,27 +1759,36 @@ static int adjoint_impl(lbfd_ctx *c, int64_t nsteps, int K, double *J, double *d
     const size_t pop_b = (size_t)Q * N * sizeof(double), sc_b = (size_t)(1 + ns) * N * sizeof(double);
     const int64_t nseg = (nsteps + K - 1) / K;
     const int kseg = (int)(nsteps < K ? nsteps : K);
-    AdjBuffers mem;
-    char *ckpt = (char *)mem.get((size_t)nseg * (pop_b + sc_b));
-    char *segs = (char *)mem.get((size_t)kseg * (pop_b + sc_b));
-    double *lam[2], *lsc[2];
-    for (int b = 0; b < 2; ++b) {
-        lam[b] = (double *)mem.get(pop_b);
-        lsc[b] = (double *)mem.get(sc_b);
-    }
-    double *dW = (double *)mem.get(N * sizeof(double));
-    double *dP = (double *)mem.get(2 * LBFD_MAX_REACTIONS * sizeof(double));
-    double *Jd = (double *)mem.get(sizeof(double));
-    double *mid = (double *)mem.get((size_t)adjoint_mid_fields(Q, ns) * N * sizeof(double));
-    if (!ckpt || !segs || !lam[0] || !lam[1] || !lsc[0] || !lsc[1] || !dW || !dP || !Jd || !mid)
-        return fail(LBFD_ENOMEM, "adjoint: device allocation failed");
-    auto ck_pop = [&](int64_t s) { return ckpt + (size_t)s * (pop_b + sc_b); };
-    auto ck_sc = [&](int64_t s) { return ckpt + (size_t)s * (pop_b + sc_b) + pop_b; };
-    auto sg_pop = [&](int64_t s) { return segs + (size_t)s * (pop_b + sc_b); };
-    auto sg_sc = [&](int64_t s) { return segs + (size_t)s * (pop_b + sc_b) + pop_b; };
+    // One allocation: the checkpoints, the later states of a segment (its
+    // first is the checkpoint), the scratch between the backward kernels, and
+    // what starts from zero -- the two levels' adjoints, dJ/d wall_T, dJ/d(A,
+    // Ta) and J.  The context keeps it for the next call up to kAdjKeep bytes:
+    // ten allocations and frees a call took 1.4 of the 2.9 ms of a 72 x 56 x 40
+    // box over four steps.
+    const size_t state = pop_b + sc_b, wall_b = N * sizeof(double);
+    constexpr size_t kAcc = 2 * LBFD_MAX_REACTIONS + 1;
+    const size_t mid_b = (size_t)adjoint_mid_fields(Q, ns) * N * sizeof(double);
+    const size_t zero_b = 2 * state + wall_b + kAcc * sizeof(double);
+    AdjWorkspace ws(c, (size_t)nseg * state + (size_t)(kseg - 1) * state + mid_b + zero_b);
+    if (!ws.p) return fail(LBFD_ENOMEM, "adjoint: device allocation failed");
+    char *const ckpt = ws.p, *const segs = ckpt + (size_t)nseg * state;
+    double *const mid = (double *)(segs + (size_t)(kseg - 1) * state);
+    char *const zero = (char *)mid + mid_b;
+    double *const lam[2] = {(double *)zero, (double *)(zero + pop_b)};
+    double *const lsc[2] = {(double *)(zero + 2 * pop_b), (double *)(zero + 2 * pop_b + sc_b)};
+    double *const dW = (double *)(zero + 2 * state), *const dP = (double *)(zero + 2 * state + wall_b);
+    double *const Jd = dP + 2 * LBFD_MAX_REACTIONS;
+    auto ck_pop = [&](int64_t s) { return ckpt + (size_t)s * state; };
+    auto ck_sc = [&](int64_t s) { return ck_pop(s) + pop_b; };
+    // level n0 + s of segment seg
+    auto sg_pop = [&](int64_t seg, int64_t s) { return s == 0 ? ck_pop(seg) : segs + (size_t)(s - 1) * state; };
+    auto sg_sc = [&](int64_t seg, int64_t s) { return sg_pop(seg, s) + pop_b; };
 
+    // Every backward step stores the adjoints of every fluid cell's
+    // populations and scalars; entries of solid cells are never written and
+    // keep the zeros of this clear.
+    HIP_TRY(hipMemsetAsync(zero, 0, zero_b, c->stream));
     // forward pass: checkpoints and the objective
-    HIP_TRY(hipMemsetAsync(Jd, 0, sizeof(double), c->stream));
     for (int64_t n = 0; n < nsteps; ++n) {
         if (n % K == 0) {
             HIP_TRY(hipMemcpyAsync(ck_pop(n / K), c->pop[c->cur], pop_b, hipMemcpyDeviceToDevice, c->stream));
@@ -1752,33 +1810,22 @@ static int adjoint_impl(lbfd_ctx *c, int64_t nsteps, int K, double *J, double *d
     }
 
     // backward sweep over segments, each recomputed from its checkpoint
-    // Every backward step stores the adjoints of every fluid cell's
-    // populations and scalars; entries of solid cells are never written and
-    // keep the zeros of this clear.
-    for (int b = 0; b < 2; ++b) {
-        HIP_TRY(hipMemsetAsync(lam[b], 0, pop_b, c->stream));
-        HIP_TRY(hipMemsetAsync(lsc[b], 0, sc_b, c->stream));
-    }
-    HIP_TRY(hipMemsetAsync(dW, 0, N * sizeof(double), c->stream));
-    HIP_TRY(hipMemsetAsync(dP, 0, 2 * LBFD_MAX_REACTIONS * sizeof(double), c->stream));
     int nxt = 0;  // lam[nxt], lsc[nxt]: adjoint of level n+1
     for (int64_t seg = nseg - 1; seg >= 0; --seg) {
         const int64_t n0 = seg * K, n1 = (n0 + K < nsteps) ? n0 + K : nsteps;
-        HIP_TRY(hipMemcpyAsync(sg_pop(0), ck_pop(seg), pop_b, hipMemcpyDeviceToDevice, c->stream));
-        HIP_TRY(hipMemcpyAsync(sg_sc(0), ck_sc(seg), sc_b, hipMemcpyDeviceToDevice, c->stream));
         for (int64_t n = n0; n < n1 - 1; ++n) {
             KParams k = c->base;
-            k.pop_in = sg_pop(n - n0);
-            k.pop_out = sg_pop(n - n0 + 1);
-            k.sc_in = sg_sc(n - n0);
-            k.sc_out = sg_sc(n - n0 + 1);
+            k.pop_in = sg_pop(seg, n - n0);
+            k.pop_out = sg_pop(seg, n - n0 + 1);
+            k.sc_in = sg_sc(seg, n - n0);
+            k.sc_out = sg_sc(seg, n - n0 + 1);
             HIP_TRY(launch_step(c->Q, c->nsp, c->prec, kModeStep, k, c->streams));
         }
         for (int64_t n = n1 - 1; n >= n0; --n) {
             const int cu = 1 - nxt;
             KParams k = c->base;
-            k.pop_in = sg_pop(n - n0);
-            k.sc_in = sg_sc(n - n0);
+            k.pop_in = sg_pop(seg, n - n0);
+            k.sc_in = sg_sc(seg, n - n0);
             const ObjTerm o = objective_term(c, n);
             HIP_TRY(launch_adjoint(c->Q, c->nsp, k, lam[nxt], lsc[nxt], lam[cu], lsc[cu], dW, dP, mid, c->obj_kind,
                                    o.w, c->stream));
@@ -1786,9 +1833,9 @@ static int adjoint_impl(lbfd_ctx *c, int64_t nsteps, int K, double *J, double *d
         }
     }
     HIP_TRY(hipStreamSynchronize(c->stream));
-    double hP[2 * LBFD_MAX_REACTIONS];
+    double hP[kAcc];
     HIP_TRY(hipMemcpy(hP, dP, sizeof(hP), hipMemcpyDeviceToHost));
-    if (J) HIP_TRY(hipMemcpy(J, Jd, sizeof(double), hipMemcpyDeviceToHost));
+    if (J) *J = hP[2 * LBFD_MAX_REACTIONS];
     if (dJ_dwallT)
         HIP_TRY(hipMemcpy(dJ_dwallT, dW, N * sizeof(double), wall_dev ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost));
     for (int j = 0; j < nrx; ++j) {

@@ -18,7 +18,7 @@ def test_diagnostics_of_many_blocks(nx, ny):
     from paper_2304_05657_amd.lbfd import Solver
     need_gpu()
     p = W.channel_flame(nx=nx, ny=ny, front_x=nx / 3.0)
-    say("diagnostics %dx%d: %d tiles" % (nx, ny, -(-nx // 64) * -(-ny // 4)))
+    say("diagnostics %dx%d: %d tiles" % (nx, ny, -(-nx // 16) * -(-ny // 16)))
     g, o = Solver(p), oracle.Oracle(p, threads=oracle_threads())
     g.step(2)
     o.step(2)
@@ -27,3 +27,28 @@ def test_diagnostics_of_many_blocks(nx, ny):
         assert abs(dg[k] - do[k]) <= 1e-12 * abs(do[k]), (k, dg[k], do[k])
     assert dg["nonfinite"] == 0 and dg["max_sumY_err"] < 1e-13
     assert abs(dg["hrr_max"] - do["hrr_max"]) <= 1e-12 * do["hrr_max"]
+
+
+def test_objective_static_of_a_thin_box():
+    """A box one cell high has more tiles than the static array has rows and
+    stays within its limit: same objective as with allocation (the same
+    kernels and order of sums)."""
+    import ctypes as C
+    import numpy as np
+    from paper_2304_05657_amd.lbfd import Solver
+    need_gpu()
+    nx = 2_600_000
+    base = W.channel_flame(nx=64, ny=4)
+    mask = np.zeros((1, 1, nx), dtype=np.uint8)
+    mask[..., ::50] = 1
+    p = base.replace(nx=nx, ny=1, mask=mask, wall_T=np.full(mask.shape, 500.0), T0=np.full(mask.shape, 600.0),
+                     Y0=np.broadcast_to(np.array(base.Y_in)[:, None, None, None], (4,) + mask.shape).copy())
+    say("objective_static %dx1" % nx)
+    out = []
+    for name in ("lbfd_objective", "lbfd_objective_static"):
+        s = Solver(p)
+        J = C.c_double()
+        assert getattr(s._lib, name)(s._h, C.c_int64(2), C.byref(J)) == 0
+        out.append(J.value)
+        s.close()
+    assert out[0] == out[1] > 0.0
