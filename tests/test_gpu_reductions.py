@@ -41,7 +41,7 @@ def test_objective_static_of_a_thin_box():
     base = W.channel_flame(nx=64, ny=4)
     mask = np.zeros((1, 1, nx), dtype=np.uint8)
     mask[..., ::50] = 1
-    p = base.replace(nx=nx, ny=1, mask=mask, wall_T=np.full(mask.shape, 500.0), T0=np.full(mask.shape, 600.0),
+    p = base.replace(nx=nx, ny=1, faces=("periodic",) * 2 + ("wall",) * 2 + ("periodic",) * 2, mask=mask, wall_T=np.full(mask.shape, 500.0), T0=np.full(mask.shape, 600.0),
                      Y0=np.broadcast_to(np.array(base.Y_in)[:, None, None, None], (4,) + mask.shape).copy())
     say("objective_static %dx1" % nx)
     out = []
