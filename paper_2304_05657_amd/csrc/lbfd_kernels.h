@@ -741,8 +741,8 @@ __device__ __forceinline__ void block_reduce_diag(double (&a)[kNDiag], double *o
 // source, Lambda (Eq. 6), Euler update, P_h (Eq. 13a), source Xi_i (Eq. 9),
 // central-moment collision (Eqs. 14, 19, 21), diagnostics, stores.
 // diffT, diffY already carry the factor alpha.
-template <int Q, int NSP, int PREC, int MODE, bool LE = false>
-__device__ __forceinline__ void finish_cell(const KParams &P, long long idx, const typename Prec<PREC>::calc (&g)[Q],
+template <int Q, int NSP, int PREC, int MODE, bool LE = false, class Pops>
+__device__ __forceinline__ void finish_cell(const KParams &P, long long idx, Pops &&g,
                                             const Pt<NSP, typename Prec<PREC>::calc> &ctr,
                                             const typename Prec<PREC>::calc (&u)[3],
                                             const typename Prec<PREC>::calc (&m)[3], typename Prec<PREC>::calc sg,
@@ -805,6 +805,36 @@ __device__ __forceinline__ void finish_cell(const KParams &P, long long idx, con
         return;
     }
 
+    // the scalars' stores go out here, so that they need not be held through
+    // the collision
+    if constexpr (mode_advances(MODE)) {
+        const uint32_t off = (uint32_t)idx * (uint32_t)sizeof(S);
+        if constexpr (L::D == 3) {
+            PlanePtr<S> ps(P.sc_out, 0, P.N);
+            *ps.at(off) = (S)Tn;
+#pragma unroll
+            for (int k = 0; k < NSP; ++k) {
+                ps.step(P.N);
+                *ps.at(off) = (S)Yn[k];
+            }
+        } else {
+            char *so = (char *)P.sc_out;
+            const size_t fstride = (size_t)P.N * sizeof(S);
+            sto<S>(so, off, (S)Tn);
+#pragma unroll
+            for (int k = 0; k < NSP; ++k) sto<S>(so + (size_t)(1 + k) * fstride, off, (S)Yn[k]);
+        }
+    }
+    bool bad = false;
+    if constexpr (DIAG) {
+        bad = !isfinite((double)ctr.T);
+#pragma unroll
+        for (int k = 0; k < NSP; ++k) bad |= !isfinite((double)ctr.Y[k]);
+        // (a sum with a term that is not finite is not finite; the terms are
+        // looked at only where it is not, which it also is on overflow)
+        if (__any(!isfinite((double)sg))) sfor<0, Q>([&](auto I) { bad |= !isfinite((double)g(I)); });
+    }
+
     // source Xi_i (Eq. 9) and pre-conditioned populations (Eq. 19)
     const C uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
     C xi[Q], h[Q], pi = 0, sxi = 0;
@@ -818,7 +848,12 @@ __device__ __forceinline__ void finish_cell(const KParams &P, long long idx, con
                        ((C)L::cz(i) - u[2]) * grad[2];
         xi[i] = (C)kCs2 * (feq_r - wi) * proj + wi * rho * (C)kCs2 * Lam;
         sxi += xi[i];
-        h[i] = g[i] * inv_rc + xi[i] * half_inv;
+        // (3-D: which product is rounded is stated, so that populations held in
+        // registers or in LDS give the same bits)
+        if constexpr (L::D == 3)
+            h[i] = fma(g(I), inv_rc, xi[i] * half_inv);
+        else
+            h[i] = g(I) * inv_rc + xi[i] * half_inv;
         pi += h[i];
     });
     // unit-mass shift, central-moment relaxation, shift back (Eq. 14)
@@ -837,11 +872,6 @@ __device__ __forceinline__ void finish_cell(const KParams &P, long long idx, con
     });
 
     if constexpr (DIAG) {
-        bool bad = !isfinite((double)ctr.T);
-#pragma unroll
-        for (int k = 0; k < NSP; ++k) bad |= !isfinite((double)ctr.Y[k]);
-#pragma unroll
-        for (int i = 0; i < Q; ++i) bad |= !isfinite((double)g[i]);
         if (bad) {
             acc[kNonfinite] = 1.0;
         } else {
@@ -864,7 +894,6 @@ __device__ __forceinline__ void finish_cell(const KParams &P, long long idx, con
     }
 
     if constexpr (mode_advances(MODE)) {
-        const uint32_t off = (uint32_t)idx * (uint32_t)sizeof(S);
         if constexpr (L::D == 3) {
             using T = typename Prec<PREC>::pop;
             PlanePtr<T> pl(P.pop_out, 0, P.N);
@@ -873,21 +902,9 @@ __device__ __forceinline__ void finish_cell(const KParams &P, long long idx, con
                 plane_store<Q, PREC, i>(pl.at((uint32_t)idx * (uint32_t)sizeof(T)), h[i]);
                 pl.step(P.N);
             });
-            PlanePtr<S> ps(P.sc_out, 0, P.N);
-            *ps.at(off) = (S)Tn;
-#pragma unroll
-            for (int k = 0; k < NSP; ++k) {
-                ps.step(P.N);
-                *ps.at(off) = (S)Yn[k];
-            }
         } else {
             sfor<0, Q>(
                 [&](auto I) { pop_store<Q, PREC, decltype(I)::value>(P.pop_out, P.N, idx, h[decltype(I)::value]); });
-            char *so = (char *)P.sc_out;
-            const size_t fstride = (size_t)P.N * sizeof(S);
-            sto<S>(so, off, (S)Tn);
-#pragma unroll
-            for (int k = 0; k < NSP; ++k) sto<S>(so + (size_t)(1 + k) * fstride, off, (S)Yn[k]);
         }
     }
 }
@@ -1419,6 +1436,19 @@ __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int
                 if constexpr (L::cy(i) == -1) m[1] -= g[i];
             }
         });
+        // 3-D: the populations wait in LDS while the stencils are evaluated
+        // where their registers make the difference.  FP64 with more than 4
+        // species: with them two waves a SIMD spill 34 registers, which moved 1
+        // GB of the 4.1 GB of a step on 256 x 128 x 128 through memory (1046 ->
+        // 889 us).  Mixed with up to 4: 148 -> 122 registers, four waves for
+        // three (161 x 99 x 83, half: 139 -> 123 us).  FP64 with up to 4 would
+        // stay at two waves, mixed with more at three (154 us either way).
+        constexpr bool STASH = D == 3 && (PREC == LBFD_FP64) == (NSP > 4) && MODE != kModeFields;
+        __shared__ C pops[STASH ? Q * kBlock : 1];
+        if constexpr (STASH) {
+            sfor<0, Q>([&](auto I) { pops[decltype(I)::value * kBlock + threadIdx.x] = g[decltype(I)::value]; });
+            asm volatile("" ::: "memory");
+        }
         const C inv_rho = rcp(rho);
         const C inv_rc = (C)3 * inv_rho;  // 1 / (rho cs^2)
         const C u[3] = {m[0] * inv_rc, m[1] * inv_rc, m[2] * inv_rc};
@@ -1616,7 +1646,14 @@ __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int
 #pragma unroll
         for (int k = 0; k < NSP; ++k) diffY[k] *= alpha;
 
-        finish_cell<Q, NSP, PREC, MODE, LE>(P, idx, g, ctr, u, m, sg, inv_rc, diffT, diffY, CT, CY, grad, wallq, acc);
+        auto pop = [&](auto I) -> C {
+            if constexpr (STASH)
+                return pops[decltype(I)::value * kBlock + threadIdx.x];
+            else
+                return g[decltype(I)::value];
+        };
+        if constexpr (STASH) asm volatile("" ::: "memory");
+        finish_cell<Q, NSP, PREC, MODE, LE>(P, idx, pop, ctr, u, m, sg, inv_rc, diffT, diffY, CT, CY, grad, wallq, acc);
 
         if constexpr (D == 3 && mode_advances(MODE)) {
             // 3-D: outlet cells hand their outward normal velocity to
@@ -1651,9 +1688,14 @@ __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int
 // (168 VGPRs) in FP64 and four (128) in the mixed forms, there also with the
 // diagnostics (2048 x 512, half: 70 us free, 64 us at four; one more wave
 // than these spills: FP64 64 -> 70 us, half 41 -> 45 us a step).
-// 3-D FP64: two waves (256 VGPRs).  Otherwise the allocator is left free
-// (1): for the other launches with diagnostics or fields (MODE !=
-// kModeStep), which run once per check or read, and for the curved-wall and
+// 3-D FP64: two waves (256 VGPRs), also with the diagnostics (256 x 256 x 128,
+// 4 species: 2476 -> 1664 us with the 27 finiteness tests behind that of their
+// sum, which had kept it at one wave; 9 species, spilling 37: 1402 free, 1223).
+// 3-D mixed: four waves (128) with up to 4 species, there also for the fields
+// (104 -> 99 us; 9 species spill: 117 -> 147), three (168) with more.
+// Otherwise the allocator is left free (1): for the other launches with
+// diagnostics or fields (MODE != kModeStep), which run once per check or read,
+// and for the curved-wall and
 // mixture-transport instantiations (CW, LE).  The 2-D FP64 fields launch
 // with curved walls and mixture-averaged transport once returned wrong
 // velocities at the three-wave budget (spilling) and exact ones without it;
@@ -1662,9 +1704,11 @@ __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int
 template <int Q, int NSP, int PREC, int MODE = kModeStep, bool CWLE = false> struct StepWaves {
     static constexpr int value = CWLE                                   ? 1
                                  : (Q == 9 && NSP <= 4 && PREC != LBFD_FP64 && MODE == kModeStepDiag) ? 4
+                                 : (Q == 27 && PREC == LBFD_FP64 && MODE == kModeStepDiag) ? 2
+                                 : (Q == 27 && NSP <= 4 && PREC != LBFD_FP64 && MODE == kModeFields) ? 4
                                  : MODE != kModeStep                    ? 1
                                  : (Q == 9 && NSP <= 4)                 ? (PREC == LBFD_FP64 ? 3 : 4)
-                                 : (Q == 27 && PREC == LBFD_FP64)       ? 2
+                                 : Q == 27                              ? (PREC == LBFD_FP64 ? 2 : NSP <= 4 ? 4 : 3)
                                                                         : 1;
 };
 
