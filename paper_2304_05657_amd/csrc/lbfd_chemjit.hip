@@ -76,10 +76,13 @@ std::string generate(const ChemRx *rx, int n_rx, int nsp, bool fp64)
     w("using namespace lbfd;");
     w("struct ChemJitArgs { const char *sc_in; char *sc_out; const int *order; unsigned char *heavy;");
     w("    long long n_fluid; unsigned long long fstride; int substeps_max, anyb; };");
-    // three waves per SIMD (168 registers): at four (128) the unrolled
-    // text spills (the compiler's schedule keeps more values live than in
-    // the generic kernel's loop over reaction groups)
-    w("extern \"C\" __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))");
+    // Bound by its vector instructions (some 500 a sub-step for 9 species and
+    // 20 reactions, 4 cycles each): four waves per SIMD (128 registers; the
+    // text takes 116 to 118 -- 168 and spills while the fields were addressed by
+    // 64-bit offsets and the limiter stood in the update's way).  256 x 128 x
+    // 128: 2187 -> 2001 us with the limiter behind one comparison a species and
+    // 32-bit offsets; 133 x 97 x 75, single: 521 -> 505.
+    w("extern \"C\" __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))");
     // (named for its storage type, so that profiles tell the launches apart)
     f("lbfd_chem_jit_%s(const ChemJitArgs a)", fp64 ? "f64" : "f32");
     w("{");
@@ -87,10 +90,12 @@ std::string generate(const ChemRx *rx, int n_rx, int nsp, bool fp64)
     w("    for (int i = (int)threadIdx.x; i < kExpTabN; i += (int)blockDim.x) tab[i] = kExp2Tab[i];");
     w("    for (int i = (int)threadIdx.x; i < 2 * kLogTabN; i += (int)blockDim.x) ltab[i] = kLogTab[i];");
     w("    __syncthreads();");
-    w("    const long long t = (long long)blockIdx.x * 256 + threadIdx.x;");
-    w("    if (t >= a.n_fluid) return;");
+    // (from the back of the order: the cells with the most sub-steps first)
+    w("    const long long t = a.n_fluid - 1 - ((long long)blockIdx.x * 256 + threadIdx.x);");
+    w("    if (t < 0) return;");
     w("    const long long idx = a.order[t];");
-    f("    const unsigned long long off = (unsigned long long)idx * sizeof(%s);", S);
+    // a 32-bit byte offset (N < 2^29) to the fields' scalar bases
+    f("    const unsigned off = (unsigned)idx * (unsigned)sizeof(%s);", S);
     f("    const double T = (double)*(const %s *)(a.sc_in + off);", S);
     w("    const bool anyb = a.anyb != 0;");
     w("    int nsub = 1;");
@@ -113,7 +118,7 @@ std::string generate(const ChemRx *rx, int n_rx, int nsp, bool fp64)
     // held in registers for the whole loop: the offset passes through an
     // empty asm so that the loads stay in the loop.  Nine fewer register
     // pairs live across the loop cut the spills at three waves per SIMD.
-    w("        unsigned long long offv = off;");
+    w("        unsigned offv = off;");
     w("        asm volatile(\"\" : \"+v\"(offv));");
     for (int k = 0; k < nsp; ++k)
         f("        const double Yc%d = (double)*(const %s *)(a.sc_in + %d * a.fstride + offv) + dY%d;", k, S, k + 1, k);
@@ -137,18 +142,37 @@ std::string generate(const ChemRx *rx, int n_rx, int nsp, bool fp64)
             if (!(rx[j].adt > 0.0)) continue;
             f("        double r%d = k%d;", j, j);
             for (int m = 0; m < rx[j].n_react; ++m) f("        r%d *= Yc%d;", j, rx[j].react[m]);
+            // (opaque: with a coefficient of 1 the last product would be fused
+            // into the increment, unrounded, unlike the generic kernel's)
+            f("        asm(\"\" : \"+v\"(r%d));", j);
             for (int k = 0; k < nsp; ++k)
                 if (rx[j].nu[k] != 0.0)
                     f("        incY%d += %s * r%d;", k, num(rx[j].nu[k]).c_str(), j);
             f("        incT += %s * r%d;", num(rx[j].q).c_str(), j);
         }
     }
+    // the limiter: most sub-steps consume no species below zero, so its scales
+    // are formed only where one comparison a species says so (a sum is
+    // negative exactly when one term is below the other's negative)
     w("        double lam = 1.0;");
-    for (int k = 0; k < nsp; ++k)
-        f("        if (incY%d < 0.0 && Yc%d + incY%d < 0.0) lam = fmin(lam, fmax(Yc%d, 0.0) * rcp(-incY%d));", k, k, k, k,
-          k);
-    w("        dT += lam * incT;");
-    for (int k = 0; k < nsp; ++k) f("        dY%d += lam * incY%d;", k, k);
+    std::string below;
+    for (int k = 0; k < nsp; ++k) {
+        bool consumed = false;
+        for (int j = 0; j < n_rx; ++j) consumed |= rx[j].adt > 0.0 && rx[j].nu[k] != 0.0;
+        if (!consumed) continue;
+        char t[64];
+        snprintf(t, sizeof t, "%s(incY%d < -Yc%d)", below.empty() ? "" : " | ", k, k);
+        below += t;
+    }
+    if (!below.empty()) {
+        w("        if (" + below + ") {");
+        for (int k = 0; k < nsp; ++k)
+            f("            if (incY%d < 0.0 && Yc%d + incY%d < 0.0) lam = fmin(lam, fmax(Yc%d, 0.0) * rcp(-incY%d));", k, k,
+              k, k, k);
+        w("        }");
+    }
+    w("        dT = fma(lam, incT, dT);");
+    for (int k = 0; k < nsp; ++k) f("        dY%d = fma(lam, incY%d, dY%d);", k, k, k);
     w("    }");
     f("    *(%s *)(a.sc_out + off) = (%s)dT;", S, S);
     for (int k = 0; k < nsp; ++k) f("    *(%s *)(a.sc_out + %d * a.fstride + off) = (%s)dY%d;", S, k + 1, S, k);
