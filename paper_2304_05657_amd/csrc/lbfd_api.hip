@@ -344,13 +344,15 @@ static unsigned periodic_bits(const lbfd_params &p)
     return b;
 }
 
-// The boundary cells' codes to their cells on the device.
+// The boundary cells' codes to their cells on the device, by way of the second
+// population buffer, which holds nothing yet, where they fit.
 static int upload_codes(lbfd_ctx *c, const std::vector<unsigned long long> &pull,
                         const std::vector<unsigned long long> &st)
 {
-    const size_t nb = pull.size(), b = nb * sizeof(unsigned long long);
-    char *tmp = nullptr;
-    if (hipMalloc((void **)&tmp, 2 * b + nb * sizeof(int)) != hipSuccess)
+    const size_t nb = pull.size(), b = nb * sizeof(unsigned long long), need = 2 * b + nb * sizeof(int);
+    const bool fits = need <= (size_t)c->Q * c->N * pop_elem_size(c->prec);
+    char *tmp = (char *)c->pop[1];
+    if (!fits && hipMalloc((void **)&tmp, need) != hipSuccess)
         return fail(LBFD_ENOMEM, "hipMalloc of the boundary codes failed");
     unsigned long long *dp = (unsigned long long *)tmp, *ds = dp + nb;
     int *db = (int *)(ds + nb);
@@ -359,11 +361,15 @@ static int upload_codes(lbfd_ctx *c, const std::vector<unsigned long long> &pull
     if (e == hipSuccess) e = hipMemcpy(db, c->boundary_host.data(), nb * sizeof(int), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = launch_cell_codes(db, dp, ds, (long long)nb, c->cell_code, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    (void)hipFree(tmp);
+    if (!fits)
+        (void)hipFree(tmp);
+    else if (e == hipSuccess)
+        e = hipMemset(tmp, 0, need);  // (as it was)
     return e == hipSuccess ? LBFD_OK : fail(LBFD_EDEVICE, "upload of the boundary codes failed: %s", hipGetErrorString(e));
 }
 
-static int build_descriptors(lbfd_ctx *c)
+// upload = false: the check alone (new wall temperatures; the codes hold none).
+static int build_descriptors(lbfd_ctx *c, bool upload)
 {
     const lbfd_params &p = c->p;
     const long long nb = c->n_boundary;
@@ -463,6 +469,7 @@ static int build_descriptors(lbfd_ctx *c)
         pcode[t] = pc;
         scode[t] = sc;
     }
+    if (!upload) return LBFD_OK;
     HIP_TRY(hipMemcpy(c->face_Td, p.face_T, sizeof(p.face_T), hipMemcpyHostToDevice));
     c->bwk_host = wk;
     return upload_codes(c, pcode, scode);
@@ -746,7 +753,7 @@ int lbfd_init(const lbfd_params *p, const uint8_t *mask, const double *wall_T, c
         HIP_OR_FREE(hipMemset(c->chem_heavy, 0, (size_t)N));
         HIP_OR_FREE(hipMemset(c->chem_count, 0, 2 * sizeof(int)));
     }
-    TRY_OR_FREE(build_descriptors(c));
+    TRY_OR_FREE(build_descriptors(c, true));
     long long minus1 = -1;
     HIP_OR_FREE(hipMemcpy(c->bad_dev, &minus1, sizeof(minus1), hipMemcpyHostToDevice));
     TRY_OR_FREE(upload_scalars(c, c->sc[0], T0, Y0));
@@ -1341,7 +1348,7 @@ int lbfd_set_wall_temperature(lbfd_ctx *c, const double *wall_T)
     HIP_TRY(hipStreamSynchronize(c->stream));
     c->wall_T_host.assign(wall_T, wall_T + c->N);
     HIP_TRY(hipMemcpy(c->wall_T, wall_T, c->N * sizeof(double), hipMemcpyHostToDevice));
-    return build_descriptors(c);
+    return build_descriptors(c, false);
 }
 
 static void state_sizes(const lbfd_ctx *c, size_t *pop, size_t *sc, size_t *outl)
