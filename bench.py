@@ -60,8 +60,8 @@ KERNEL_SOURCES = [os.path.join(ROOT, "paper_2304_05657_amd", "csrc", f)
 # (profiles/traffic_porous_mech_512x256x256_and_porous_256.md)
 TRAFFIC = {
     ("porous3d_mech_512x256x256", "fp64", "lbfd_chem_jit_f64"): {
-        "bytes_per_launch": 6496.3e6,
-        "kernel_sha256": "02d1a6caa69771f1a4fa715b1a274a2725aea9fecd517f4306499dd90ff15e5e",
+        "bytes_per_launch": 6504.9e6,
+        "kernel_sha256": "85e1f64e01cc23371eb346d23d97157e75765e960080d5f822f0d281fea9e85c",
     },
 }
 POP_BYTES = {"fp64": 8, "fp32": 4, "fp16": 2}

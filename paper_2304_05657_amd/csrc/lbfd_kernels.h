@@ -1695,14 +1695,15 @@ __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int
 // (104 -> 99 us; 9 species spill: 117 -> 147), three (168) with more.
 // Otherwise the allocator is left free (1): for the other launches with
 // diagnostics or fields (MODE != kModeStep), which run once per check or read,
-// and for the curved-wall and
-// mixture-transport instantiations (CW, LE).  The 2-D FP64 fields launch
+// and for the curved-wall and mixture-transport instantiations (CW, LE) but the
+// 2-D mixed steps with up to 4 species, which take 128 registers for 129 and no
+// spill (1021 x 386, single, both: 34.4 -> 31.5 us).  The 2-D FP64 fields launch
 // with curved walls and mixture-averaged transport once returned wrong
 // velocities at the three-wave budget (spilling) and exact ones without it;
 // the assembly check of the build finds no one-sided copy in it, so the
 // budget stays off on those paths.
 template <int Q, int NSP, int PREC, int MODE = kModeStep, bool CWLE = false> struct StepWaves {
-    static constexpr int value = CWLE                                   ? 1
+    static constexpr int value = CWLE ? (Q == 9 && NSP <= 4 && PREC != LBFD_FP64 && MODE == kModeStep ? 4 : 1)
                                  : (Q == 9 && NSP <= 4 && PREC != LBFD_FP64 && MODE == kModeStepDiag) ? 4
                                  : (Q == 27 && PREC == LBFD_FP64 && MODE == kModeStepDiag) ? 2
                                  : (Q == 27 && NSP <= 4 && PREC != LBFD_FP64 && MODE == kModeFields) ? 4
