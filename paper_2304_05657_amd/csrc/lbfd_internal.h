@@ -72,6 +72,12 @@ __host__ __device__ inline long long cell_at(int x, int y, int z, int dx, int dy
 
 __host__ __device__ inline int decode_pull_kind(unsigned long long pc, int I) { return (int)(pc >> (2 * I)) & 3; }
 
+// Some direction is pulled from an outlet (both bits of its kind set).
+__host__ __device__ inline bool pulls_outlet(unsigned long long pc)
+{
+    return (pc & (pc >> 1) & 0x5555555555555555ull) != 0;
+}
+
 __host__ __device__ inline int decode_kind(unsigned long long sc, int d, int j)
 {
     return (int)(sc >> (5 * (4 * d + j))) & 7;

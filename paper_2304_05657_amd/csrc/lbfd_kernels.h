@@ -1247,13 +1247,15 @@ __device__ __forceinline__ void tile_stencil(const KParams &P, int d, int x, int
 // 2-D: the populations entering through outflow face f at face cell idx
 // (Eq. 32): g_i(r) <- g_i(r-n)(cs - u.n) + g_i(r)(1 - cs + u.n) with the
 // post-streaming values and velocity of this level; pc: the cell's pull code
-// (whose outlet kinds imply a fluid inner neighbour).
+// (whose outlet kinds imply a fluid inner neighbour; without one there may be
+// no inner cell at all: a box of one cell in x).
 template <int Q, int PREC>
 __device__ __forceinline__ void outlet_2d(const KParams &P, int f, int x, int y, long long idx, unsigned long long pc,
                                           typename Prec<PREC>::calc ux, const typename Prec<PREC>::calc (&g)[Q])
 {
     using L = Lat<Q>;
     using C = typename Prec<PREC>::calc;
+    if (!pulls_outlet(pc)) return;
     const int sign = f ? 1 : -1;
     const long long in = idx - sign;
     const unsigned long long pci = P.code[in] == kCodeBoundary ? P.cell_code[in].x : 0;
@@ -1987,8 +1989,7 @@ __global__ void __launch_bounds__(kBlock) outlet_kernel(const KParams P)
     const long long idx = ((long long)z * P.ny + y) * P.nx + x;
     if (P.code[idx] != kCodeBoundary) return;  // (a fluid cell next to this face is a boundary cell)
     const unsigned long long pc = P.cell_code[idx].x;
-    // some population is the outlet's, hence the inner neighbour fluid
-    if ((pc & (pc >> 1) & 0x5555555555555555ull) == 0) return;
+    if (!pulls_outlet(pc)) return;  // (else the inner neighbour is fluid)
     const long long in = idx - sign;
     const unsigned long long pci = P.code[in] == kCodeBoundary ? P.cell_code[in].x : 0;
     const C cs = (C)0.57735026918962576451;
