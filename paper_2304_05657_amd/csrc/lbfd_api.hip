@@ -876,18 +876,25 @@ static KParams level_params(const lbfd_ctx *c)
     return k;
 }
 
-// A caller's buffer that the fields kernel can write itself: aligned device
-// memory of the context's GPU (other memory the copy engine can reach is
-// filled from the context's own buffer).
-static bool writable_here(const lbfd_ctx *c, const double *p)
+// How a caller's device buffer of n doubles is filled: by the fields kernel
+// itself (aligned memory of the context's GPU), or by a copy out of the
+// context's own buffer (other memory that the copy engine can reach).  A copy
+// past the end of an allocation is refused by the runtime, a store is not, so
+// the end is looked at here.
+enum FieldBuffer { kFieldDirect, kFieldCopied, kFieldTooSmall };
+static FieldBuffer field_buffer(const lbfd_ctx *c, const double *p, size_t n)
 {
-    if (!p) return true;
     hipPointerAttribute_t a;
-    if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipPointerGetAttributes(&a, p) != hipSuccess || a.type != hipMemoryTypeDevice || a.device != c->device ||
+        hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) != hipSuccess) {
         (void)hipGetLastError();
-        return false;
+        return kFieldCopied;
     }
-    return a.type == hipMemoryTypeDevice && a.device == c->device && ((uintptr_t)p & 7) == 0;
+    const size_t at = (uintptr_t)p - (uintptr_t)base;
+    if (at > size || n * sizeof(double) > size - at) return kFieldTooSmall;
+    return ((uintptr_t)p & 7) == 0 ? kFieldDirect : kFieldCopied;
 }
 
 // Fields of the current level into host (dev = false) or device buffers.
@@ -898,8 +905,20 @@ static int read_fields(lbfd_ctx *c, double *rho, double *u, double *T, double *Y
 {
     if (!c) return fail(LBFD_EINVAL, "null context");
     const long long N = c->N;
-    const bool direct = dev && writable_here(c, rho) && writable_here(c, u) && writable_here(c, T) &&
-                        writable_here(c, Y) && writable_here(c, Ph);
+    double *const out[5] = {rho, u, T, Y, Ph};
+    const size_t len[5] = {(size_t)N, (size_t)c->D * N, (size_t)N, (size_t)c->nsp * N, (size_t)N};
+    bool direct = dev;
+    for (int i = 0; dev && i < 5; ++i) {
+        if (!out[i]) continue;
+        const FieldBuffer b = field_buffer(c, out[i], len[i]);
+        direct &= b == kFieldDirect;
+        // (where two buffers overlap the copies leave the last one's values)
+        for (int j = 0; j < i; ++j)
+            direct &= !(out[j] && out[i] < out[j] + len[j] && out[j] < out[i] + len[i]);
+        const bool widened = (i == 2 || i == 3) && c->prec != LBFD_FP64;  // by a kernel, not by a copy
+        if (b == kFieldTooSmall && !widened)
+            return fail(LBFD_EDEVICE, "a field buffer is smaller than the %zu bytes of its field", len[i] * sizeof(double));
+    }
     KParams k = level_params(c);
     if (direct) {
         k.f_rho = rho;
