@@ -135,7 +135,7 @@ struct lbfd_ctx {
     int2 *img_rng = nullptr;            //   Shepard list ranges
     int *img_idx = nullptr;             //   their fluid nodes
     double *img_w = nullptr;            //   and weights
-    double *img_val = nullptr;          //   reconstructed values of the current level
+    void *img_val = nullptr;            //   reconstructed values of the current level
     long long n_sup = 0;                //   distinct nodes of the Shepard lists
     int *sup_idx = nullptr;             //   their cells
     double *sup_val = nullptr;          //   and their packed (T, rho, Y_k) of the current level
@@ -1249,7 +1249,7 @@ int lbfd_set_image_points(lbfd_ctx *c, int64_t n, const int64_t *cell, const int
         hipMalloc((void **)&c->img_rng, range.size() * sizeof(int2)) != hipSuccess ||
         hipMalloc((void **)&c->img_idx, nodes.size() * sizeof(int)) != hipSuccess ||
         hipMalloc((void **)&c->img_w, wts.size() * sizeof(double)) != hipSuccess ||
-        hipMalloc((void **)&c->img_val, (size_t)(2 + c->nsp) * n * sizeof(double)) != hipSuccess) {
+        hipMalloc(&c->img_val, (size_t)(2 + c->nsp) * n * sc_elem_size(c->prec)) != hipSuccess) {
         clear_image_points(c);
         return fail(LBFD_ENOMEM, "hipMalloc of the image-point tables failed");
     }

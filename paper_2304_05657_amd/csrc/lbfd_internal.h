@@ -148,7 +148,8 @@ struct KParams {
     long long n_sup;            // support: the distinct fluid nodes of the lists,
     const int *sup_idx;         //   [n_sup] their cells
     double *sup_val;            //   [n_sup][2 + n_species] T, rho, Y_k (this level)
-    double *img_val;            //   [2 + n_species][n_img] T, rho, Y_k at the image points (this level)
+    void *img_val;              //   [2 + n_species][n_img] T, Y_k, rho at the image points (this level), in the
+                                //     type of the arithmetic
     long long nblocks;     // blocks of a step launch: the tiles
     int tiles_x, tiles_y, tiles_z;
     int tile_band;        // D3Q27: tiles in y of a band of the tile order

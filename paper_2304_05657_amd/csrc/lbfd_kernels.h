@@ -350,15 +350,16 @@ __device__ __forceinline__ typename Prec<PREC>::calc pop_load_pair(const void *b
     }
 }
 
-// Values (T, rho, Y_k) at a listed image point, reconstructed for this
+// Values (T, Y_k, rho) at a listed image point, reconstructed for this
 // level by image_kernel.
 template <int NSP, class C>
 __device__ __forceinline__ void image_value(const KParams &P, int li, Pt<NSP, C> &o)
 {
-    o.T = (C)P.img_val[li];
-    o.rho = (C)P.img_val[P.n_img + li];
+    const C *v = (const C *)P.img_val + li;
+    o.T = v[0];
 #pragma unroll
-    for (int k = 0; k < NSP; ++k) o.Y[k] = (C)P.img_val[(2 + k) * P.n_img + li];
+    for (int k = 0; k < NSP; ++k) o.Y[k] = v[(1 + k) * P.n_img];
+    o.rho = v[(1 + NSP) * P.n_img];
 }
 
 // fourth-order central first and second derivatives (Sec. II.D)
@@ -928,7 +929,7 @@ __device__ __forceinline__ void tile_pull(const KParams &P, int x, int y, int z,
     using C = typename Prec<PREC>::calc;
     using T = typename Prec<PREC>::pop;
     using L = Lat<Q>;
-    constexpr bool kStream = pop_stream<Q, PREC>();
+    constexpr bool kStream = pop_stream<Q, PREC>() && !CW;  // (curved walls read them again)
     using R = std::conditional_t<PREC == LBFD_MIXED_FP16, unsigned short, T>;  // as loaded
     // wrapped neighbour coordinates (a wrapped source beyond a face that is
     // not periodic is never read: its code is not kPullFluid), as byte offsets
@@ -1048,36 +1049,66 @@ __device__ __forceinline__ void tile_pull(const KParams &P, int x, int y, int z,
     }
     if constexpr (CW) {
         // linearly interpolated bounce-back (post-collision form) for a
-        // wall met at the fraction q of the link toward it (direction OPP)
-        if (P.bq != nullptr) {
-            PlanePtr<const R> pl(P.pop_in, 0, P.N), po(P.pop_in, Q - 1, P.N);
-            PlanePtr<const float> pq(P.bq, 0, P.n_boundary);
+        // wall met at the fraction q of the link toward it (direction OPP).
+        // Bound by the latency of its loads, which depend on one another:
+        // hence every direction's q first, then the populations of nine
+        // directions, in flight together.  (One direction after the other
+        // the pass waited 26 times for a q and then for the populations: 160 x
+        // 128 x 96 packing, FP64 / single / half, 683 / 545 / 511 us a step;
+        // now 479 / 434 / 408.)
+        if (P.bq != nullptr && __any((pcode & ~(pcode >> 1) & 0x5555555555555555ull) != 0)) {
             const uint32_t tq = (uint32_t)tb * (uint32_t)sizeof(float);
-            sfor<0, Q>([&](auto I) {
-                constexpr int i = decltype(I)::value;
-                constexpr int opp = Q - 1 - i;
-                if constexpr (i != opp) {
-                    const float qraw = *pq.at(tq);
-                    const float qs = decode_pull_kind(pcode, i) == kPullBounce ? qraw : __builtin_nanf("");
-                    const bool interp = qs == qs;
-                    if (__any(interp)) {
-                        const C q2 = (C)2 * (C)qs;  // weights in the arithmetic precision
-                        // q < 1/2: the far node r + c_I is the pull source of
-                        // direction OPP (when it is a fluid cell)
-                        const bool near_half = qs < 0.5f;
-                        const bool use_far = interp && near_half && decode_pull_kind(pcode, opp) == kPullFluid;
-                        const uint32_t far = off(L::cx(i), L::cy(i), L::cz(i));
-                        const C gfar = widen(*po.at(use_far ? far : own), I);
-                        const C gown = widen(*pl.at(own), I);
-                        const C lo = q2 * g[i] + ((C)1 - q2) * gfar;
-                        const C iq = (C)1 / (interp && !near_half ? q2 : (C)1);
-                        const C hi = g[i] * iq + (q2 - (C)1) * iq * gown;
-                        g[i] = use_far ? lo : (interp && !near_half) ? hi : g[i];
+            float qs[Q];
+            {
+                PlanePtr<const float> pq(P.bq, 0, P.n_boundary);
+                sfor<0, Q>([&](auto I) {
+                    constexpr int i = decltype(I)::value;
+                    qs[i] = __builtin_nanf("");
+                    if constexpr (i != (Q - 1) / 2) qs[i] = *pq.at(tq);
+                    pq.step(P.n_boundary);
+                });
+            }
+            PlanePtr<const R> pl(P.pop_in, 0, P.N), po(P.pop_in, Q - 1, P.N);
+            sfor<0, Q / 9>([&](auto B) {
+                constexpr int b = 9 * decltype(B)::value;
+                R vfar[9], vown[9];
+                // q < 1/2: the far node r + c_I is the pull source of
+                // direction OPP (when it is a fluid cell)
+                auto interp = [&](auto I) -> bool {
+                    constexpr int i = decltype(I)::value;
+                    return decode_pull_kind(pcode, i) == kPullBounce && qs[i] == qs[i];
+                };
+                auto use_far = [&](auto I) -> bool {
+                    constexpr int i = decltype(I)::value;
+                    return interp(I) && qs[i] < 0.5f && decode_pull_kind(pcode, Q - 1 - i) == kPullFluid;
+                };
+                sfor<b, b + 9>([&](auto I) {
+                    constexpr int i = decltype(I)::value;
+                    vfar[i - b] = vown[i - b] = R();
+                    if constexpr (i != (Q - 1) / 2) {
+                        if (__any(interp(I))) {
+                            vfar[i - b] = *po.at(use_far(I) ? off(L::cx(i), L::cy(i), L::cz(i)) : own);
+                            vown[i - b] = *pl.at(own);
+                        }
                     }
-                }
-                pl.step(P.N);
-                po.step(-P.N);
-                pq.step(P.n_boundary);
+                    pl.step(P.N);
+                    po.step(-P.N);
+                });
+                sfor<b, b + 9>([&](auto I) {
+                    constexpr int i = decltype(I)::value;
+                    if constexpr (i != (Q - 1) / 2) {
+                        asm("" : "+v"(qs[i]));  // (the lane masks formed again, not kept in scalars)
+                        if (__any(interp(I))) {
+                            const C q2 = (C)2 * (C)qs[i];  // weights in the arithmetic precision
+                            const bool far_half = use_far(I), near_wall = interp(I) && !(qs[i] < 0.5f);
+                            const C gfar = widen(vfar[i - b], I), gown = widen(vown[i - b], I);
+                            const C lo = q2 * g[i] + ((C)1 - q2) * gfar;
+                            const C iq = (C)1 / (near_wall ? q2 : (C)1);
+                            const C hi = g[i] * iq + (q2 - (C)1) * iq * gown;
+                            g[i] = far_half ? lo : near_wall ? hi : g[i];
+                        }
+                    }
+                });
             });
         }
     }
@@ -1182,8 +1213,51 @@ __device__ __forceinline__ void tile_stencil(const KParams &P, int d, int x, int
             at[j] = b1 ? hi : lo;
         }
     }
-    {
-        using S = typename Prec<PREC>::scal;
+    using S = typename Prec<PREC>::scal;
+    static_assert(std::is_same_v<S, C>, "image points and cells hold the same type");
+    const unsigned kinds = s20 & 0x39ce7u;  // the kinds of the four slots
+    near = kinds != 0;
+    // ghosts with an image point of their own take its values in place of the
+    // mirror cell's: the lane's address and plane stride are selected, so that
+    // the points' loads stay in flight together (with a pass of loads a slot,
+    // one after the other, the images of 160 x 128 x 96 added 133 us in FP64 and
+    // 120 in half beside their reconstruction; now 25 and 15)
+    int li[4] = {-1, -1, -1, -1};
+    bool images = false;
+    if constexpr (CW) {
+        if (P.bimg != nullptr && __any(near)) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) li[j] = near ? P.bimg[(d * 4 + j) * P.n_boundary + tb] : -1;
+            images = __any(li[0] >= 0 || li[1] >= 0 || li[2] >= 0 || li[3] >= 0);
+        }
+    }
+    if (images) {
+        const S *img = (const S *)P.img_val;
+        const S *q[4];
+        uint32_t step[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            q[j] = li[j] >= 0 ? img + li[j] : (const S *)P.sc_in + (idx + at[j]);
+            step[j] = (uint32_t)((li[j] >= 0 ? P.n_img : P.N) * sizeof(S));
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) pv[j].T = *q[j];
+#pragma unroll
+        for (int k = 0; k < NSP; ++k)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                q[j] = (const S *)((const char *)q[j] + step[j]);
+                pv[j].Y[k] = *q[j];
+            }
+        C ri[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) ri[j] = img[(1 + NSP) * P.n_img + (li[j] >= 0 ? li[j] : 0)];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const C r = density<NSP>(P, pv[j].T, pv[j].Y);
+            pv[j].rho = li[j] >= 0 ? ri[j] : r;
+        }
+    } else {
         uint32_t bo[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) bo[j] = (uint32_t)((int)idx + at[j]) * (uint32_t)sizeof(S);
@@ -1200,25 +1274,7 @@ __device__ __forceinline__ void tile_stencil(const KParams &P, int d, int x, int
         for (int j = 0; j < 4; ++j) pv[j].rho = density<NSP>(P, pv[j].T, pv[j].Y);
     }
     const C r0 = density_rcp<NSP>(P, pv[0].T, pv[0].Y);
-    const unsigned kinds = s20 & 0x39ce7u;  // the kinds of the four slots
-    near = kinds != 0;
     if (__any(near)) {
-        if constexpr (CW) {
-            if (P.bimg != nullptr) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int li = near ? P.bimg[(d * 4 + j) * P.n_boundary + tb] : -1;
-                    if (__any(li >= 0)) {
-                        Pt<NSP, C> iv;
-                        image_value<NSP>(P, li >= 0 ? li : 0, iv);
-                        pv[j].T = li >= 0 ? iv.T : pv[j].T;
-                        pv[j].rho = li >= 0 ? iv.rho : pv[j].rho;
-#pragma unroll
-                        for (int k = 0; k < NSP; ++k) pv[j].Y[k] = li >= 0 ? iv.Y[k] : pv[j].Y[k];
-                    }
-                }
-            }
-        }
         iso_ghosts<DIAG, C>(
             P, d, c, n, idx, off, s20, [&](int j) -> C & { return pv[j].T; }, [&](int j) -> C & { return pv[j].rho; },
             [&](int j, C Tw) -> C { return density<NSP>(P, Tw, pv[j].Y); },
@@ -1573,16 +1629,20 @@ __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int
                 if (__any(near)) {
                     if constexpr (CW) {
                         if (P.bimg != nullptr) {
+                            int im[4];
+#pragma unroll
+                            for (int j = 0; j < 4; ++j)
+                                im[j] = near ? P.bimg[(d * 4 + j) * P.n_boundary + tb] : -1;
 #pragma unroll
                             for (int j = 0; j < 4; ++j) {
-                                const int im = near ? P.bimg[(d * 4 + j) * P.n_boundary + tb] : -1;
-                                if (__any(im >= 0)) {
+                                asm volatile("" ::: "memory");  // (a slot's values at a time: registers)
+                                if (__any(im[j] >= 0)) {
                                     Pt<NSP, C> iv;
-                                    image_value<NSP>(P, im >= 0 ? im : 0, iv);
-                                    Tv[j] = im >= 0 ? iv.T : Tv[j];
-                                    rv[j] = im >= 0 ? iv.rho : rv[j];
+                                    image_value<NSP>(P, im[j] >= 0 ? im[j] : 0, iv);
+                                    Tv[j] = im[j] >= 0 ? iv.T : Tv[j];
+                                    rv[j] = im[j] >= 0 ? iv.rho : rv[j];
 #pragma unroll
-                                    for (int k = 0; k < NSP; ++k) Yv[j][k] = im >= 0 ? iv.Y[k] : Yv[j][k];
+                                    for (int k = 0; k < NSP; ++k) Yv[j][k] = im[j] >= 0 ? iv.Y[k] : Yv[j][k];
                                 }
                             }
                         }
@@ -1695,17 +1755,20 @@ __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int
 // sum, which had kept it at one wave; 9 species, spilling 37: 1402 free, 1223).
 // 3-D mixed: four waves (128) with up to 4 species, there also for the fields
 // (104 -> 99 us; 9 species spill: 117 -> 147), three (168) with more.
-// Otherwise the allocator is left free (1): for the other launches with
-// diagnostics or fields (MODE != kModeStep), which run once per check or read,
-// and for the curved-wall and mixture-transport instantiations (CW, LE) but the
-// 2-D mixed steps with up to 4 species, which take 128 registers for 129 and no
-// spill (1021 x 386, single, both: 34.4 -> 31.5 us).  The 2-D FP64 fields launch
-// with curved walls and mixture-averaged transport once returned wrong
-// velocities at the three-wave budget (spilling) and exact ones without it;
-// the assembly check of the build finds no one-sided copy in it, so the
-// budget stays off on those paths.
+// Curved walls and mixture-averaged transport (CW, LE): the 2-D steps with up
+// to 4 species, with and without the diagnostics, take the same budgets (at
+// most two registers spill; 1024 x 512 burner with links, image points and
+// mixture transport, step with the diagnostics, free / budget: FP64 87 / 82 us,
+// single 69 / 67, half 70 / 66).  Otherwise the allocator is left free (1): for
+// the other launches with diagnostics or fields (MODE != kModeStep), which run
+// once per check or read, and for CW and LE in 3-D, with 9 species and in the
+// launches that only evaluate a level.  Of those the 2-D FP64 fields launch with
+// both once returned wrong velocities at the three-wave budget (spilling) and
+// exact ones without it; the assembly check of the build finds no one-sided
+// copy in it, so they stay without.  (test_gpu_modes.py runs every
+// instantiation of this table against the oracle.)
 template <int Q, int NSP, int PREC, int MODE = kModeStep, bool CWLE = false> struct StepWaves {
-    static constexpr int value = CWLE ? (Q == 9 && NSP <= 4 && PREC != LBFD_FP64 && MODE == kModeStep ? 4 : 1)
+    static constexpr int value = CWLE ? (Q == 9 && NSP <= 4 && mode_advances(MODE) ? (PREC == LBFD_FP64 ? 3 : 4) : 1)
                                  : (Q == 9 && NSP <= 4 && PREC != LBFD_FP64 && MODE == kModeStepDiag) ? 4
                                  : (Q == 27 && PREC == LBFD_FP64 && MODE == kModeStepDiag) ? 2
                                  : (Q == 27 && NSP <= 4 && PREC != LBFD_FP64 && MODE == kModeFields) ? 4
@@ -1797,7 +1860,9 @@ __global__ void __launch_bounds__(kBlock) image_kernel(const KParams P)
         C v = acc[f];
 #pragma unroll
         for (int o = LPP / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-        if (live && lane == 0) P.img_val[(size_t)f * P.n_img + k] = (double)v;
+        // (T, Y_k, rho: the order of the scalars' planes)
+        const int o = f == 0 ? 0 : f == 1 ? 1 + NSP : f - 1;
+        if (live && lane == 0) ((C *)P.img_val)[(size_t)o * P.n_img + k] = v;
     }
 }
 
