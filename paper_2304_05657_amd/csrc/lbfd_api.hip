@@ -151,7 +151,6 @@ struct lbfd_ctx {
     ChemRx *rxk_dev = nullptr;
     unsigned char *scratch = nullptr;   // this device's static scratch (lbfd_objective_static)
     int64_t level = 0;
-    dim3 grid, block;
     KParams base;
 };
 
@@ -475,6 +474,61 @@ static int build_descriptors(lbfd_ctx *c, bool upload)
     return upload_codes(c, pcode, scode);
 }
 
+// The tiles of a step launch.
+struct TilePlan {
+    int x, y, z;  // tiles along each axis
+    bool thin;
+    long long count() const { return (long long)x * y * z; }
+};
+static TilePlan tile_plan(int D, int nx, int ny, int nz, bool thin)
+{
+    const int tx = D == 2 ? (thin ? kThinX2 : kTileX2) : (thin ? kThinX3 : kTileX3);
+    const int ty = D == 2 ? (thin ? kThinY2 : kTileY2) : (thin ? kThinY3 : kTileY3);
+    const int tz = D == 2 ? 1 : (thin ? kThinZ3 : kTileZ3);
+    return {(int)((nx + tx - 1LL) / tx), (int)((ny + ty - 1LL) / ty), (int)((nz + tz - 1LL) / tz), thin};
+}
+
+// Whether a box takes the tiles of thin boxes: where they cover it with fewer
+// lanes.  2-D, from more tiles than the chip holds at once (three a CU) and a
+// saving of 15 % on: 2^20 x 1 (FP64) 344 us a step in ordinary tiles, 103 in thin
+// ones; 65536 x 17 116 and 72; 16384 x 66 70 and 64; below either line the square
+// halo and the shorter near-wall passes of ordinary tiles are worth as much or
+// more (4096 x 36 15.2 and 16.2, 512 x 20 9.1 and 9.8).  3-D, from a quarter of
+// the lanes on, or from half of them in boxes of many tiles: 4 x 256 x 256 646
+// and 95 us, 24 x 128 x 128 162 and 100; but 20 x 20 x 20 21.0 and 22.7, 33 x 96 x
+// 96 101 and 122.
+static bool thin_box(int D, int nx, int ny, int nz)
+{
+    const long long n = tile_plan(D, nx, ny, nz, false).count(), m = tile_plan(D, nx, ny, nz, true).count();
+    const bool many = n > 768;
+    return D == 2 ? many && 100 * n >= 115 * m : n >= (many ? 2 : 4) * m;
+}
+
+// Choose the context's tiles (curved walls keep the ordinary ones: their
+// kernels are built for those alone).
+static void plan_tiles(lbfd_ctx *c)
+{
+    const lbfd_params &p = c->p;
+    const bool thin = !c->base.bq && !c->base.bimg && thin_box(c->D, p.nx, p.ny, p.nz);
+    const TilePlan t = tile_plan(c->D, p.nx, p.ny, p.nz, thin);
+    KParams &k = c->base;
+    c->nblocks = (int)t.count();
+    k.nblocks = c->nblocks;
+    k.tiles_x = t.x;
+    k.tiles_y = t.y;
+    k.tiles_z = t.z;
+    k.thin = t.thin;
+    // The tile order of a 3-D step: a band's scalars over the planes that the
+    // tiles in flight and their stencils span (seven, thin nine) take at most
+    // 2 MB, half an XCD's L2 (two rows a tile, thin eight).  Measured on 256 x
+    // 256 x 128 (FP64, 4 species; plane order 1961 us a step) bands of 4 / 8 /
+    // 16 tiles 1859 / 1888 / 1879 us, on 256 x 128 x 128 (FP64, 9 species; 1481
+    // us) 1449 / 1404 / 1430 us.
+    const long long band_row = (t.thin ? 9LL * kThinY3 : 7LL * kTileY3) * p.nx * (1 + c->nsp) *
+                               (long long)sc_elem_size(c->prec);
+    k.tile_band = (int)std::min<long long>({16, t.y, std::max<long long>(1, (2LL << 20) / band_row)});
+}
+
 static KParams make_kparams(const lbfd_ctx *c)
 {
     const lbfd_params &p = c->p;
@@ -496,18 +550,6 @@ static KParams make_kparams(const lbfd_ctx *c)
     k.chem_order = c->chem_order;
     k.chem_heavy = c->chem_heavy;
     k.chem_count = c->chem_count;
-    k.nblocks = c->nblocks;
-    k.tiles_x = (int)c->grid.x;
-    k.tiles_y = (int)c->grid.y;
-    k.tiles_z = (int)c->grid.z;
-    // The tile order of a 3-D step: a band's scalars over the seven planes
-    // that the tiles in flight and their stencils span take at most 2 MB, half
-    // an XCD's L2 (two rows a tile).  Measured on 256 x 256 x 128 (FP64, 4
-    // species; plane order 1961 us a step) bands of 4 / 8 / 16 tiles 1859 /
-    // 1888 / 1879 us, on 256 x 128 x 128 (FP64, 9 species; 1481 us) 1449 /
-    // 1404 / 1430 us.
-    const long long band_row = 7LL * 2 * p.nx * (1 + c->nsp) * (long long)sc_elem_size(c->prec);
-    k.tile_band = (int)std::min<long long>(16, std::max<long long>(1, (2LL << 20) / band_row));
     k.face_Td = c->face_Td;
     k.cell_code = c->cell_code;
     k.bslot = c->bslot;
@@ -653,13 +695,6 @@ int lbfd_init(const lbfd_params *p, const uint8_t *mask, const double *wall_T, c
     const size_t pop_bytes = (size_t)c->Q * N * pop_elem_size(c->prec);
     const size_t sc_bytes = (size_t)(1 + c->nsp) * N * sc_elem_size(c->prec);
     c->outlet_n = (size_t)2 * c->Q * p->ny * p->nz;
-    if (c->D == 2) {
-        c->block = dim3(16, 16, 1);
-    } else {
-        c->block = dim3(64, 2, 2);
-    }
-    c->grid = dim3((p->nx + c->block.x - 1) / c->block.x, (p->ny + c->block.y - 1) / c->block.y,
-                   (p->nz + c->block.z - 1) / c->block.z);
     if (c->N >= (1LL << 29)) {
         delete c;
         return fail(LBFD_EINVAL, "box too large (at most 2^29 cells: 32-bit byte offsets per field)");
@@ -669,7 +704,10 @@ int lbfd_init(const lbfd_params *p, const uint8_t *mask, const double *wall_T, c
     classify_cells(*p, mask, code, boundary);
     c->n_boundary = (long long)boundary.size();
     for (long long i = 0; i < c->N; ++i) c->n_fluid += mask[i] == LBFD_FLUID;
-    c->nblocks = c->grid.x * c->grid.y * c->grid.z;
+    // (as many rows as the most tiles that plan_tiles may choose)
+    const size_t rows = (size_t)std::max(tile_plan(c->D, p->nx, p->ny, p->nz, false).count(),
+                                         thin_box(c->D, p->nx, p->ny, p->nz)
+                                             ? tile_plan(c->D, p->nx, p->ny, p->nz, true).count() : 0);
 
 #define ALLOC(ptr, bytes)                                                                   \
     do {                                                                                    \
@@ -693,7 +731,7 @@ int lbfd_init(const lbfd_params *p, const uint8_t *mask, const double *wall_T, c
     ALLOC(c->outlet_un, (size_t)2 * p->ny * p->nz * sizeof(double));
     ALLOC(c->inflow_u, (size_t)6 * p->ny * p->nz * sizeof(double));
     ALLOC(c->inflow_du, (size_t)3 * p->ny * p->nz * sizeof(double));
-    ALLOC(c->partials, (size_t)c->nblocks * kNDiag * sizeof(double));
+    ALLOC(c->partials, rows * kNDiag * sizeof(double));
     ALLOC(c->diag_dev, kNDiag * sizeof(double));
     ALLOC(c->bad_dev, sizeof(long long));
     ALLOC(c->rx_dev, sizeof(lbfd_reaction) * LBFD_MAX_REACTIONS);
@@ -762,6 +800,7 @@ int lbfd_init(const lbfd_params *p, const uint8_t *mask, const double *wall_T, c
     HIP_OR_FREE(hipGetDevice(&c->device));
     c->streams.main = c->stream;
     c->base = make_kparams(c);
+    plan_tiles(c);
     TRY_OR_FREE(upload_reactions(c));
     {
         void *sp = nullptr;
@@ -780,7 +819,9 @@ int lbfd_init(const lbfd_params *p, const uint8_t *mask, const double *wall_T, c
     KParams k = c->base;
     k.sc_in = c->sc[0];
     k.pop_out = c->pop[0];
-    hipError_t e = launch_init(c->Q, c->nsp, c->prec, k, u0_dev, Ph0_dev, c->grid, c->block, c->stream);
+    const dim3 block = c->D == 2 ? dim3(kTileX2, kTileY2, 1) : dim3(kTileX3, kTileY3, kTileZ3);
+    const dim3 grid((p->nx + block.x - 1) / block.x, (p->ny + block.y - 1) / block.y, (p->nz + block.z - 1) / block.z);
+    hipError_t e = launch_init(c->Q, c->nsp, c->prec, k, u0_dev, Ph0_dev, grid, block, c->stream);
     hipError_t e2 = hipStreamSynchronize(c->stream);
     if (u0_dev) (void)hipFree(u0_dev);
     if (Ph0_dev) (void)hipFree(Ph0_dev);
@@ -1032,6 +1073,7 @@ int lbfd_set_wall_links(lbfd_ctx *c, int64_t n, const int64_t *cell, const int32
         if (c->bq) (void)hipFree(c->bq);
         c->bq = nullptr;
         c->base.bq = nullptr;
+        plan_tiles(c);
         return LBFD_OK;
     }
     const long long nb = c->n_boundary, N = c->N;
@@ -1061,6 +1103,7 @@ int lbfd_set_wall_links(lbfd_ctx *c, int64_t n, const int64_t *cell, const int32
     }
     HIP_TRY(hipMemcpy(c->bq, h.data(), h.size() * sizeof(float), hipMemcpyHostToDevice));
     c->base.bq = c->bq;
+    plan_tiles(c);
     return LBFD_OK;
 }
 
@@ -1087,6 +1130,7 @@ static void clear_image_points(lbfd_ctx *c)
     c->base.img_idx = nullptr;
     c->base.img_w = nullptr;
     c->base.img_val = nullptr;
+    plan_tiles(c);
 }
 
 int lbfd_set_image_points(lbfd_ctx *c, int64_t n, const int64_t *cell, const int32_t *slot, const double *image)
@@ -1277,6 +1321,7 @@ int lbfd_set_image_points(lbfd_ctx *c, int64_t n, const int64_t *cell, const int
     c->base.img_idx = c->img_idx;
     c->base.img_w = c->img_w;
     c->base.img_val = c->img_val;
+    plan_tiles(c);
     return LBFD_OK;
 }
 
@@ -1626,8 +1671,8 @@ int lbfd_objective_static(lbfd_ctx *c, int64_t nsteps, double *J)
     if (!c || !J || nsteps < 0) return fail(LBFD_EINVAL, "bad arguments");
     // The limit counts blocks of 64 x 4 (64 x 2 x 2) cells and the boundary cells
     // in blocks of 256, by eights, whatever the step's own blocks are; a box
-    // within it whose tiles are more than the array's rows (a long one a few
-    // cells thin) keeps its partials in the context's buffer.
+    // within it whose tiles are more than the array's rows keeps its partials in
+    // the context's buffer.
     const long long by = c->D == 2 ? 4 : 2, bz = c->D == 2 ? 1 : 2;
     const long long rows = (c->p.nx + 63LL) / 64 * ((c->p.ny + by - 1) / by) * ((c->p.nz + bz - 1) / bz) +
                            ((c->n_boundary + kBlock - 1) / kBlock + 7) / 8 * 8;

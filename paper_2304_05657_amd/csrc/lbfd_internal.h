@@ -152,6 +152,7 @@ struct KParams {
                                 //     type of the arithmetic
     long long nblocks;     // blocks of a step launch: the tiles
     int tiles_x, tiles_y, tiles_z;
+    int thin;             // the tiles are those of thin boxes
     int tile_band;        // D3Q27: tiles in y of a band of the tile order
     const double *wall_T;
     const void *pop_in;   // post-collision populations of the previous level
@@ -183,6 +184,10 @@ struct KParams {
     double dk[kMaxSp];   // D_k / alpha = 1 / Le_k (mixture-averaged transport)
     double cpk[kMaxSp];  // c_pk / c_p,ref (mixture-averaged transport)
 };
+
+// Tiles of the step, 256 cells: D2Q9 and D3Q27, and those of thin boxes.
+constexpr int kTileX2 = 16, kTileY2 = 16, kTileX3 = 64, kTileY3 = 2, kTileZ3 = 2;
+constexpr int kThinX2 = 64, kThinY2 = 4, kThinX3 = 8, kThinY3 = 8, kThinZ3 = 4;
 
 // Launch modes: the step; the step with the reductions of the level; the
 // reductions of the current level; the fields of the current level (neither

@@ -1336,9 +1336,13 @@ __device__ __forceinline__ void outlet_2d(const KParams &P, int f, int x, int y,
 }
 
 // Tile of one 256-thread block: 16 x 16 cells in 2-D (a wave 16 x 4), 64 x 2 x 2
-// in 3-D (a wave one row).
-template <int D> struct TileShape {
-    static constexpr int X = D == 2 ? 16 : 64, Y = D == 2 ? 16 : 2, Z = D == 2 ? 1 : 2;
+// in 3-D (a wave one row); THIN, for boxes that would leave most of such a
+// tile's lanes outside: 64 x 4, and 8 x 8 x 4 (a wave 8 x 8).
+template <int D, bool THIN> struct TileShape {
+    static constexpr int X = D == 2 ? (THIN ? kThinX2 : kTileX2) : (THIN ? kThinX3 : kTileX3),
+                         Y = D == 2 ? (THIN ? kThinY2 : kTileY2) : (THIN ? kThinY3 : kTileY3),
+                         Z = D == 2 ? 1 : (THIN ? kThinZ3 : kTileZ3);
+    static_assert(X * Y * Z == kBlock, "a thread a cell");
 };
 
 // One tile (bx, by, bz) of the step: its threads work on every fluid cell.  A
@@ -1362,13 +1366,13 @@ template <int D> struct TileShape {
 // 211 MB in FP64 (273 MB before), 3.4 TB/s; in half precision it is bound by
 // its instructions.
 // (tx, ty, tz): the thread's place in the tile, in 3-D ty and tz the same for
-// a wave;
+// a wave (THIN: tz);
 // slot: the block's row of the diagnostics partials.
 // CW: boundary cells apply the curved-wall treatments when listed: the
 // interpolated bounce-back of P.bq and the Shepard image points of P.bimg (a
 // separate instantiation, so that contexts without them keep the registers
 // of plain bounce-back and axis-mirror ghosts).
-template <int Q, int NSP, int PREC, int MODE, bool CW = false, bool LE = false>
+template <int Q, int NSP, int PREC, int MODE, bool CW = false, bool LE = false, bool THIN = false>
 __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int bz, int tx, int ty, int tz,
                                            long long slot)
 {
@@ -1377,7 +1381,7 @@ __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int
     using S = typename Prec<PREC>::scal;
     constexpr int D = L::D;
     constexpr bool DIAG = mode_reduces(MODE);
-    using TS = TileShape<D>;
+    using TS = TileShape<D, THIN>;
     const int x = bx * TS::X + tx, y = by * TS::Y + ty, z = bz * TS::Z + tz;
     const bool inbox = x < P.nx && y < P.ny && z < P.nz;
     const long long idx = inbox ? ((long long)z * P.ny + y) * P.nx + x : 0;
@@ -1387,7 +1391,7 @@ __device__ __forceinline__ void step_block(const KParams &P, int bx, int by, int
     if constexpr (DIAG) diag_identity(acc);
 
     // 2-D: T, Y_k and rho of the tile's cells and a 2-cell halo staged
-    // once in LDS (field-major planes of 20 x 20 points); every finite-
+    // once in LDS (field-major planes of 20 x 20 points, THIN 68 x 8); every finite-
     // difference point and ghost image is then an LDS read.  Points across a
     // periodic face wrap; a point beyond an inflow face holds the ghost itself
     // (Dirichlet T, Y_k, rho), which depends on the point alone; others beyond
@@ -1780,11 +1784,11 @@ template <int Q, int NSP, int PREC, int MODE = kModeStep, bool CWLE = false> str
 
 // The step, a tile a block.  Consecutive blocks go to the 8 XCDs in turn, so
 // the tiles are renumbered to give each XCD one contiguous band of the box.
-template <int Q, int NSP, int PREC, int MODE, bool CW = false, bool LE = false>
+template <int Q, int NSP, int PREC, int MODE, bool CW = false, bool LE = false, bool THIN = false>
 __global__ void __launch_bounds__(kBlock)
 __attribute__((amdgpu_waves_per_eu(StepWaves<Q, NSP, PREC, MODE, CW || LE>::value))) step_kernel(const KParams P)
 {
-    using TS = TileShape<Lat<Q>::D>;
+    using TS = TileShape<Lat<Q>::D, THIN>;
     const long long t = (long long)blockIdx.x;
     const long long n = P.nblocks, q = n >> 3;
     const int xcd = (int)(t & 7), r = (int)(n & 7);
@@ -1806,9 +1810,16 @@ __attribute__((amdgpu_waves_per_eu(StepWaves<Q, NSP, PREC, MODE, CW || LE>::valu
         bz = 0;
     }
     const int tx = (int)threadIdx.x % TS::X;
-    // 3-D: a wave is one row of the tile, its y and z are scalars
-    const int trow = (int)threadIdx.x / TS::X, row = Lat<Q>::D == 3 ? __builtin_amdgcn_readfirstlane(trow) : trow;
-    step_block<Q, NSP, PREC, MODE, CW, LE>(P, bx, by, bz, tx, row % TS::Y, row / TS::Y, tile);
+    // 3-D: a wave is one row of the tile, its y and z are scalars (THIN: its z)
+    const int trow = (int)threadIdx.x / TS::X;
+    if constexpr (Lat<Q>::D == 2) {
+        step_block<Q, NSP, PREC, MODE, CW, LE, THIN>(P, bx, by, bz, tx, trow, 0, tile);
+    } else {
+        const int row = THIN ? trow : __builtin_amdgcn_readfirstlane(trow);
+        step_block<Q, NSP, PREC, MODE, CW, LE, THIN>(P, bx, by, bz, tx, row % TS::Y,
+                                                     THIN ? __builtin_amdgcn_readfirstlane(row / TS::Y) : row / TS::Y,
+                                                     tile);
+    }
 }
 
 // ------------------------------------------------------------ image points
@@ -2154,6 +2165,8 @@ hipError_t launch_tiles_t(const KParams &kp, hipStream_t s)
     const dim3 grid((unsigned)kp.nblocks), block(kBlock);
     if (kp.bq != nullptr || kp.bimg != nullptr)
         step_kernel<Q, NSP, PREC, MODE, true, LE><<<grid, block, 0, s>>>(kp);
+    else if (kp.thin)
+        step_kernel<Q, NSP, PREC, MODE, false, LE, true><<<grid, block, 0, s>>>(kp);
     else
         step_kernel<Q, NSP, PREC, MODE, false, LE><<<grid, block, 0, s>>>(kp);
     return hipGetLastError();
