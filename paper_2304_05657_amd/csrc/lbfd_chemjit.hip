@@ -62,7 +62,7 @@ std::string num(double v)
 // reactions whose exponentials are formed together
 constexpr int kGroup = 4;
 
-std::string generate(const ChemRx *rx, int n_rx, int nsp, bool fp64)
+std::string generate(const ChemRx *rx, int n_rx, int nsp, bool fp64, int waves)
 {
     const char *S = fp64 ? "double" : "float";
     std::string o;
@@ -81,8 +81,9 @@ std::string generate(const ChemRx *rx, int n_rx, int nsp, bool fp64)
     // text takes 116 to 118 -- 168 and spills while the fields were addressed by
     // 64-bit offsets and the limiter stood in the update's way).  256 x 128 x
     // 128: 2187 -> 2001 us with the limiter behind one comparison a species and
-    // 32-bit offsets; 133 x 97 x 75, single: 521 -> 505.
-    w("extern \"C\" __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))");
+    // 32-bit offsets; 133 x 97 x 75, single: 521 -> 505.  A larger mechanism's
+    // text takes more (chem_jit_build).
+    f("extern \"C\" __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(%d)))", waves);
     // (named for its storage type, so that profiles tell the launches apart)
     f("lbfd_chem_jit_%s(const ChemJitArgs a)", fp64 ? "f64" : "f32");
     w("{");
@@ -116,8 +117,8 @@ std::string generate(const ChemRx *rx, int n_rx, int nsp, bool fp64)
     w("        const double Tc = T + dT;");
     // Y_k is read again at every sub-step (from the cache) instead of being
     // held in registers for the whole loop: the offset passes through an
-    // empty asm so that the loads stay in the loop.  Nine fewer register
-    // pairs live across the loop cut the spills at three waves per SIMD.
+    // empty asm so that the loads stay in the loop: nine register pairs fewer
+    // live across it.
     w("        unsigned offv = off;");
     w("        asm volatile(\"\" : \"+v\"(offv));");
     for (int k = 0; k < nsp; ++k)
@@ -186,24 +187,15 @@ std::map<std::string, hipFunction_t> g_cache;  // (device, source) -> kernel, ke
 
 }  // namespace
 
-std::string chem_jit_source(const ChemRx *rx, int n_rx, int nsp, bool fp64) { return generate(rx, n_rx, nsp, fp64); }
-
-int chem_jit_build(const ChemRx *rx, int n_rx, int nsp, bool fp64, const void **fn, std::string &err)
+std::string chem_jit_source(const ChemRx *rx, int n_rx, int nsp, bool fp64, int waves)
 {
-    *fn = nullptr;
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) {
-        err = "hipGetDevice failed";
-        return -1;
-    }
-    const std::string src = generate(rx, n_rx, nsp, fp64);
-    const std::string key = std::to_string(dev) + "\n" + src;
-    std::lock_guard<std::mutex> lock(g_mu);
-    auto it = g_cache.find(key);
-    if (it != g_cache.end()) {
-        *fn = (const void *)it->second;
-        return 0;
-    }
+    return generate(rx, n_rx, nsp, fp64, waves);
+}
+
+// The source compiled for the device and loaded; scratch: bytes of private
+// memory a thread of the kernel takes (registers that did not fit).
+static int compile(const std::string &src, bool fp64, hipFunction_t *f, int *scratch, std::string &err)
+{
     hiprtcProgram prog;
     const char *hdr[] = {kMathText};
     const char *hdr_name[] = {"lbfd_math.h"};
@@ -230,11 +222,48 @@ int chem_jit_build(const ChemRx *rx, int n_rx, int nsp, bool fp64, const void **
     hiprtcGetCode(prog, code.data());
     hiprtcDestroyProgram(&prog);
     hipModule_t mod;
-    hipFunction_t f;
     if (hipModuleLoadData(&mod, code.data()) != hipSuccess ||
-        hipModuleGetFunction(&f, mod, fp64 ? "lbfd_chem_jit_f64" : "lbfd_chem_jit_f32") != hipSuccess) {
+        hipModuleGetFunction(f, mod, fp64 ? "lbfd_chem_jit_f64" : "lbfd_chem_jit_f32") != hipSuccess) {
         err = "loading the compiled chemistry kernel failed";
         return -1;
+    }
+    if (hipFuncGetAttribute(scratch, HIP_FUNC_ATTRIBUTE_LOCAL_SIZE_BYTES, *f) != hipSuccess) {
+        (void)hipGetLastError();
+        *scratch = 0;
+    }
+    return 0;
+}
+
+int chem_jit_build(const ChemRx *rx, int n_rx, int nsp, bool fp64, const void **fn, std::string &err)
+{
+    *fn = nullptr;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) {
+        err = "hipGetDevice failed";
+        return -1;
+    }
+    const std::string src = generate(rx, n_rx, nsp, fp64, kJitWaves);
+    const std::string key = std::to_string(dev) + "\n" + src;
+    std::lock_guard<std::mutex> lock(g_mu);
+    auto it = g_cache.find(key);
+    if (it != g_cache.end()) {
+        *fn = (const void *)it->second;
+        return 0;
+    }
+    hipFunction_t f;
+    int scratch = 0;
+    if (compile(src, fp64, &f, &scratch, err) != 0) return -1;
+    // A text that spills at four waves per SIMD is compiled again for three
+    // (168 registers): 32 reactions, 21 registers spilled in FP64 and 15 in
+    // single, 128 x 96 x 96: 956 -> 830 us a launch, single 850 -> 834.  (26
+    // reactions still fit.)
+    if (scratch > 0) {
+        hipFunction_t f3;
+        std::string err3;
+        int scratch3 = 0;
+        if (compile(generate(rx, n_rx, nsp, fp64, kJitWaves - 1), fp64, &f3, &scratch3, err3) == 0 &&
+            scratch3 < scratch)
+            f = f3;
     }
     g_cache[key] = f;
     *fn = (const void *)f;

@@ -257,11 +257,12 @@ hipError_t launch_widen(const float *src, double *dst, size_t n, hipStream_t s);
 hipError_t launch_fill(double *dst, int n, double v, hipStream_t s);
 
 // The chemistry kernel specialised to a mechanism's structure
-// (lbfd_chemjit.hip): its HIP source, its compile for the current device
+// (lbfd_chemjit.hip): its HIP source for a number of waves per SIMD, its compile for the current device
 // (cached per device and source for the process; *fn the kernel handle, or
 // an error text), and its launch over kp's chemistry list (blocks of 256,
 // scalars of scal_bytes).
-std::string chem_jit_source(const ChemRx *rx, int n_rx, int nsp, bool fp64);
+constexpr int kJitWaves = 4;
+std::string chem_jit_source(const ChemRx *rx, int n_rx, int nsp, bool fp64, int waves = kJitWaves);
 int chem_jit_build(const ChemRx *rx, int n_rx, int nsp, bool fp64, const void **fn, std::string &err);
 hipError_t launch_chem_jit(const KParams &kp, unsigned blocks, size_t scal_bytes, hipStream_t s);
 
