@@ -107,8 +107,9 @@ def build(force: bool = False, jobs: int | None = None, verbose: bool = True) ->
     if failed:
         raise RuntimeError("hipcc failed for: " + ", ".join(failed))
     # every kernel's assembly is checked for copies that only some lanes of
-    # a divergent branch receive (a miscompilation of the register
-    # allocator; see isa_check.py); a library holding one is not linked
+    # a divergent branch receive and for scalar pairs spilled with one half
+    # overwritten (miscompilations of the register allocator; see
+    # isa_check.py); a library holding one is not linked
     from . import isa_check
     missing = [s for s in sources() if not os.path.exists(_asm(s))]
     if missing:
@@ -117,10 +118,11 @@ def build(force: bool = False, jobs: int | None = None, verbose: bool = True) ->
     if bad:
         for path, name, ins in bad[:20]:
             print("[lbfd build] %s: %s: %s" % (os.path.basename(path), name, ins), flush=True)
-        raise RuntimeError("%d one-sided register copies in divergent code (isa_check.py); the library is not "
-                           "linked" % len(bad))
+        raise RuntimeError("%d one-sided register copies or half-overwritten scalar pairs (isa_check.py); the "
+                           "library is not linked" % len(bad))
     if verbose:
-        print("[lbfd build] assembly of %d units checked: no one-sided copies" % len(sources()), flush=True)
+        print("[lbfd build] assembly of %d units checked: no one-sided copies, no half-overwritten pairs"
+              % len(sources()), flush=True)
     objs = [_obj(s) for s in sources()]
     if force or todo or not os.path.exists(LIB) or os.path.getmtime(LIB) < max(os.path.getmtime(o) for o in objs):
         tmp = LIB + ".tmp%d" % os.getpid()

@@ -38,7 +38,22 @@ compute, leaves the other lanes' destination unwritten (seen after a rare
 store in the middle of a large step kernel: every lane outside the rare case
 read registers that no instruction had written).
 
-check(paths) scans assembly files and returns the offending copies;
+A third form is a scalar pair spilled half new, half old.  Under extreme scalar
+pressure the allocator gave one register of a loaded 64-bit value to another
+value and then spilled both registers as the pair:
+
+    s_load_dwordx4 s[64:67], ...        ; s[64:65]: a table's address
+    s_mul_i32 s64, s4, 12               ; another value, in its low word
+    v_writelane_b32 v212, s64, 62       ; "the pair", into two lanes
+    v_writelane_b32 v212, s65, 63
+    ...
+    v_readlane_b32 s8, v212, 62         ; read back, used as an address
+    v_readlane_b32 s9, v212, 63
+
+(seen in a 3-D step kernel that held some eighty 64-bit bases; every load of
+the table went to a wild address).
+
+check(paths) scans assembly files and returns the offending instructions;
 main() exits non-zero when there are any.  The scan is linear over each
 kernel's text and recognises the patterns above; it is a guard against that
 miscompilation, not a general verifier.
@@ -183,7 +198,7 @@ def check_kernel(L: list) -> list:
                 continue  # the else part writes it too
             if _read_after(L, k, dest):
                 found.append((p, L[p]))
-    return found + _check_joins(L)
+    return found + _check_joins(L) + _check_scalar_pairs(L)
 
 
 def _check_joins(L: list) -> list:
@@ -221,6 +236,87 @@ def _check_joins(L: list) -> list:
     return found
 
 
+def _sregs(tok: str) -> set:
+    m = re.match(r'^s(?:\[(\d+):(\d+)\]|(\d+))$', tok.strip())
+    if not m:
+        return set()
+    lo = int(m.group(1) or m.group(3))
+    return set(range(lo, int(m.group(2) or lo) + 1))
+
+
+_NO_SDEST = ('s_cmp', 's_bitcmp', 's_cbranch', 's_branch', 's_waitcnt', 's_nop', 's_barrier', 's_endpgm', 's_sleep',
+             's_set', 's_trap')
+
+
+def _sdests(t: str) -> set:
+    """Scalar registers an instruction writes."""
+    if not _is_code(t):
+        return set()
+    op = t.split()[0]
+    args = t[len(op):].split(';')[0].split(',')
+    if op.startswith('s_'):
+        return set() if op.startswith(_NO_SDEST) else _sregs(args[0])
+    if op.startswith(('v_readlane', 'v_readfirstlane', 'v_cmp')):
+        return _sregs(args[0])
+    if ('_co_' in op or op.startswith('v_div_scale')) and len(args) > 1:
+        return _sregs(args[1])
+    return set()
+
+
+def _used_as_pair(L: list, dests: list, at: int, b: int) -> bool:
+    """Is s[b:b+1] an operand after line at before either half is written?"""
+    pair = 's[%d:%d]' % (b, b + 1)
+    for q in range(at + 1, len(L)):
+        if pair in L[q] and _is_code(L[q]):
+            args = L[q].split(None, 1)[1].split(';')[0].split(',')
+            if any(pair in x for x in (args[1:] if dests[q] else args)):
+                return True
+        if dests[q] & {b, b + 1} or L[q].startswith('s_endpgm'):
+            return False
+    return False
+
+
+def _check_scalar_pairs(L: list) -> list:
+    """Loaded scalar pairs of which one half was overwritten (by an instruction
+    that reads neither half) before both were spilled as a pair."""
+    stores, reloads = {}, {}
+    for i, t in enumerate(L):
+        m = re.match(r'v_writelane_b32 (v\d+), s(\d+), (\d+)$', t)
+        if m:
+            stores.setdefault((m.group(1), m.group(3)), []).append((i, int(m.group(2))))
+        m = re.match(r'v_readlane_b32 s(\d+), (v\d+), (\d+)$', t)
+        if m:
+            reloads[i] = (int(m.group(1)), (m.group(2), m.group(3)))
+
+    if not reloads:
+        return []
+    dests = [_sdests(t) for t in L]
+
+    def definition(reg, at):
+        return next((x for x in range(at - 1, -1, -1) if reg in dests[x]), -1)
+
+    found = []
+    for i, (b, lo) in reloads.items():
+        if b % 2:
+            continue
+        j = next((q for q in range(i - 6, i + 7) if reloads.get(q, (0, 0))[0] == b + 1), None)
+        if j is None or not _used_as_pair(L, dests, max(i, j), b):
+            continue
+        for p, ra in stores.get(lo, []):
+            for q, rb in stores.get(reloads[j][1], []):
+                if ra % 2 or rb != ra + 1:
+                    continue
+                da, db = definition(ra, p), definition(rb, q)
+                x, y = max(da, db), min(da, db)  # x: the later of the two halves' writers
+                if y < 0 or x == y or not L[y].startswith('s_load') or not {ra, rb} <= dests[y] or \
+                        {ra, rb} <= dests[x] or L[x].startswith('v_readlane'):
+                    continue
+                op = L[x].split()[0]
+                if not any(_sregs(z) & {ra, rb} for z in L[x][len(op):].split(',')[1:]):
+                    found.append((x, L[x]))
+    return sorted(set(found))
+
+
 def check(paths) -> list:
     bad = []
     for path in paths:
@@ -236,8 +332,8 @@ def main(argv=None) -> int:
     paths = (argv if argv is not None else sys.argv[1:])
     bad = check(paths)
     for path, name, ins in bad:
-        print('%s: %s: one-sided copy in a divergent flow block: %s' % (path, name, ins))
-    print('%d kernel file(s) checked, %d one-sided copies' % (len(paths), len(bad)))
+        print('%s: %s: one-sided copy or half-overwritten pair: %s' % (path, name, ins))
+    print('%d kernel file(s) checked, %d one-sided copies or half-overwritten pairs' % (len(paths), len(bad)))
     return 1 if bad else 0
 
 
