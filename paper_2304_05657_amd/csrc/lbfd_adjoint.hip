@@ -4,23 +4,26 @@
 // chosen window of levels, with q either the wall heat flux (the sum over
 // fluid cells and axis sides whose first neighbour is an isothermal wall of
 // 2 alpha rho(T_w, Y)(T - T_w)) or the flame position
-// nx - sum_cells (T - T_u)/(T_b - T_u) nx / n_fluid, and the state s^n = (post-collision populations read by step n, T^n, Y^n).
+// nx - sum_cells (T - T_u)/(T_b - T_u) nx / n_fluid, and the state
+// s^n = (post-collision populations read by step n, T^n, Y^n).
 // With s^{n+1} = F(s^n; theta), theta = (wall temperatures, A_j, Ta_j), the
 // adjoint recursion is lambda^N = 0,
 //   lambda^n = (dF/ds^n)^T lambda^{n+1} + (dq/ds^n)^T,
 //   dJ/dtheta = sum_n (dF/dtheta)^T lambda^{n+1} + dq^n/dtheta.
-// One thread per fluid cell c gathers the cell's inputs (pull sources,
-// the finite-difference stencil's scalars, ghost wall temperatures; at
-// interior cells plain offsets, elsewhere from the cell's codes) and runs the cell's update forward in FP64, then backward: the reverse of
-// every operation, hand-derived, from the adjoint of the cell's outputs to
-// those of its inputs, in two kernels (cell_vjp_collision,
-// cell_vjp_stencil).  The sub-stepped Arrhenius source is reversed sub-step
-// by sub-step, each sub-step's state recomputed from the cell's (chem_vjp).
+// One thread per fluid cell c gathers the cell's inputs (pull sources, the
+// finite-difference stencil's scalars, ghost wall temperatures; at interior
+// cells plain offsets, elsewhere from the cell's codes) and runs the cell's
+// update forward in FP64, then backward: the reverse of every operation,
+// hand-derived, from the adjoint of the cell's outputs to those of its inputs,
+// in two kernels (cell_vjp_collision, cell_vjp_stencil).  The Arrhenius source
+// is reversed sub-step by sub-step, each sub-step's state recomputed from the
+// cell's (chem_vjp): a single step in the first of the two, sub-steps in a
+// kernel between them (cell_vjp_chem).
 // Each pulled population is read by exactly one cell, so its adjoint is
 // stored; each stencil slot's share of a scalar's adjoint is stored per slot
-// and gathered by the slot's cell in a third kernel; the wall temperatures'
-// adjoints are added atomically.  Steps are recomputed from checkpoints taken every K steps
-// (host side, lbfd_api.hip).
+// and gathered by the slot's cell in a last kernel; the wall temperatures'
+// adjoints are added atomically.  Steps are recomputed from checkpoints taken
+// every K steps (host side, lbfd_api.hip).
 //
 // tangent_kernel evaluates the same update in dual numbers with a given
 // tangent of every input (the Jacobian-vector product of one step); the
@@ -928,7 +931,8 @@ __device__ __forceinline__ void load_axis(const KParams &P, const AdjCell &c, in
 // hxs (D3Q27): [Q][kBlock] doubles of LDS for the moments' input between the
 // forward and the reverse half, which together with the relaxed moments, the
 // adjoints and a transform's passes would not fit the registers.
-template <int Q, int NSP>
+// SUB: the source is sub-stepped and reversed by adjoint_chem_kernel.
+template <int Q, int NSP, bool SUB>
 __device__ __forceinline__ void cell_vjp_collision(const KParams &P, const AdjCell &c, double wT0, const double *tab,
                                                    const AdjOut &out, double *hxs)
 {
@@ -1240,8 +1244,8 @@ __device__ __forceinline__ void cell_vjp_collision(const KParams &P, const AdjCe
         asm volatile("" : "+v"(c2.idx));
         pull_entries<Q>(P, c2, out.lam_pop, [&](auto I, double &v) { v = ag[decltype(I)::value]; });
     }
-    // the source, reversed
-    {
+    // the source, reversed (with sub-steps by adjoint_chem_kernel)
+    if constexpr (!SUB) {
         double ls[NS];
         ls[0] = lDtT;
 #pragma unroll
@@ -1261,6 +1265,30 @@ __device__ __forceinline__ void cell_vjp_collision(const KParams &P, const AdjCe
 #pragma unroll
     for (int k = 0; k < NSP; ++k) mid(M::aY0 + k) = aY0[k];
     mid(M::lR0) = lrho;
+}
+
+// The source's reverse where it is sub-stepped, from the cell's AdjMid and into
+// its aT0, aY0.
+template <int Q, int NSP>
+__device__ __forceinline__ void cell_vjp_chem(const KParams &P, const AdjCell &c, const double *tab, const AdjOut &out)
+{
+    using M = AdjMid<Lat<Q>::D, NSP>;
+    const uint32_t self = (uint32_t)c.idx * 8u;
+    const double *sc = (const double *)P.sc_in;
+    auto mid = [&](int k) -> double & { return plane_at(out.mid, P.N, k, self); };
+    double Y0[NSP], ls[1 + NSP], aT0 = mid(M::aT0), aY0[NSP];
+    const double T0 = plane_at(sc, P.N, 0, self);
+#pragma unroll
+    for (int k = 0; k < NSP; ++k) {
+        Y0[k] = plane_at(sc, P.N, 1 + k, self);
+        aY0[k] = mid(M::aY0 + k);
+    }
+#pragma unroll
+    for (int k = 0; k < 1 + NSP; ++k) ls[k] = mid(M::ls + k);
+    chem_vjp<NSP>(P, tab, T0, Y0, ls, aT0, aY0, out.lam_param);
+    mid(M::aT0) = aT0;
+#pragma unroll
+    for (int k = 0; k < NSP; ++k) mid(M::aY0 + k) = aY0[k];
 }
 
 // Second half: the reverse of the finite-difference stencils (diffusion,
@@ -1447,28 +1475,62 @@ struct AdjParams {
     double obj_w;           // weight of this level's q (flame position: times dq/dT of a cell)
 };
 
-template <int Q, int NSP>
+// The block's sums of dJ/d(A, Ta), summed over their copies, onto the result.
+__device__ __forceinline__ void add_params(const KParams &P, const double *red, double *dparam)
+{
+    for (int j = threadIdx.x; j < 2 * P.n_rx; j += blockDim.x) {
+        double v = 0.0;
+        for (int q = 0; q < kParamCopies; ++q) v += red[j * kParamCopies + q];
+        if (v != 0.0) atomicAdd(&dparam[j], v);
+    }
+}
+
+template <int Q, int NSP, bool SUB>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(Q == 27 ? 1 : 2))) adjoint_collision_kernel(const AdjParams AP)
 {
     const KParams &P = AP.k;
-    __shared__ double red[2 * LBFD_MAX_REACTIONS * kParamCopies];
+    __shared__ double red[SUB ? 1 : 2 * LBFD_MAX_REACTIONS * kParamCopies];
     __shared__ double tab[kExpTabN];
     __shared__ double hxs[Q == 27 ? Q * kBlock : 1];
-    for (int j = threadIdx.x; j < 2 * P.n_rx * kParamCopies; j += blockDim.x) red[j] = 0.0;
+    if constexpr (!SUB)
+        for (int j = threadIdx.x; j < 2 * P.n_rx * kParamCopies; j += blockDim.x) red[j] = 0.0;
     for (int j = threadIdx.x; j < kExpTabN; j += blockDim.x) tab[j] = kExp2Tab[j];
     __syncthreads();
     AdjCell c;
     if (adj_cell(P, c)) {
         const double wT0 = AP.obj_kind == LBFD_OBJ_FLAME_POSITION ? AP.obj_w : 0.0;
         AdjOut o{AP.lam_pop_next, AP.lam_sc_next, AP.lam_pop, AP.lam_sc, AP.dwallT, red, AP.mid, AP.nb};
-        cell_vjp_collision<Q, NSP>(P, c, wT0, tab, o, hxs);
+        cell_vjp_collision<Q, NSP, SUB>(P, c, wT0, tab, o, hxs);
+    }
+    if constexpr (!SUB) {
+        __syncthreads();
+        add_params(P, red, AP.dparam);
+    }
+}
+
+// The sub-stepped source's reverse is a serial chain a cell that grows with the
+// square of its sub-steps and needs few registers: a kernel of its own runs it
+// at four waves a SIMD (126 registers), where the collision kernel's one or two
+// left its latency open.  Four levels of 72 x 56 x 40, up to 64 sub-steps: 27.7
+// ms with it in the collision kernel, 15.0; ten of 512 x 128 22.7 and 18.8.  A
+// single sub-step stays there (its reads and writes of the cell's state would
+// cost more than it).
+template <int Q, int NSP>
+__global__ void __launch_bounds__(kBlock) adjoint_chem_kernel(const AdjParams AP)
+{
+    const KParams &P = AP.k;
+    __shared__ double red[2 * LBFD_MAX_REACTIONS * kParamCopies];
+    __shared__ double tab[kExpTabN];
+    for (int j = threadIdx.x; j < 2 * P.n_rx * kParamCopies; j += blockDim.x) red[j] = 0.0;
+    for (int j = threadIdx.x; j < kExpTabN; j += blockDim.x) tab[j] = kExp2Tab[j];
+    __syncthreads();
+    AdjCell c;
+    if (adj_cell(P, c)) {
+        AdjOut o{AP.lam_pop_next, AP.lam_sc_next, AP.lam_pop, AP.lam_sc, AP.dwallT, red, AP.mid, AP.nb};
+        cell_vjp_chem<Q, NSP>(P, c, tab, o);
     }
     __syncthreads();
-    for (int j = threadIdx.x; j < 2 * P.n_rx; j += blockDim.x) {
-        double v = 0.0;
-        for (int q = 0; q < kParamCopies; ++q) v += red[j * kParamCopies + q];
-        if (v != 0.0) atomicAdd(&AP.dparam[j], v);
-    }
+    add_params(P, red, AP.dparam);
 }
 
 template <int Q, int NSP>
@@ -1562,6 +1624,17 @@ __global__ void __launch_bounds__(kBlock) tangent_kernel(const TanParams TP)
     if (dq != 0.0) atomicAdd(TP.dq, dq);
 }
 
+template <int Q, int NSP>
+void launch_collision(const AdjParams &ap, unsigned nb, hipStream_t s)
+{
+    if (ap.k.chem_substeps_max > 1 && ap.k.n_rx > 0) {
+        adjoint_collision_kernel<Q, NSP, true><<<nb, kBlock, 0, s>>>(ap);
+        adjoint_chem_kernel<Q, NSP><<<nb, kBlock, 0, s>>>(ap);
+    } else {
+        adjoint_collision_kernel<Q, NSP, false><<<nb, kBlock, 0, s>>>(ap);
+    }
+}
+
 bool adjoint_supported(int Q, int nsp) { return (Q == 9 && nsp == 4) || (Q == 27 && nsp == 4); }
 
 int adjoint_mid_fields(int Q, int nsp)
@@ -1590,11 +1663,11 @@ hipError_t launch_adjoint(int Q, int nsp, const KParams &kp, const double *lam_p
     ap.obj_w = obj_w;
     const unsigned nb = (unsigned)((kp.N + kBlock - 1) / kBlock);
     if (Q == 9 && nsp == 4) {
-        adjoint_collision_kernel<9, 4><<<nb, kBlock, 0, s>>>(ap);
+        launch_collision<9, 4>(ap, nb, s);
         adjoint_stencil_kernel<9, 4><<<nb, kBlock, 0, s>>>(ap);
         adjoint_gather_kernel<9, 4><<<nb, kBlock, 0, s>>>(ap);
     } else if (Q == 27 && nsp == 4) {
-        adjoint_collision_kernel<27, 4><<<nb, kBlock, 0, s>>>(ap);
+        launch_collision<27, 4>(ap, nb, s);
         adjoint_stencil_kernel<27, 4><<<nb, kBlock, 0, s>>>(ap);
         adjoint_gather_kernel<27, 4><<<nb, kBlock, 0, s>>>(ap);
     } else {
