@@ -923,18 +923,26 @@ static KParams level_params(const lbfd_ctx *c)
 // past the end of an allocation is refused by the runtime, a store is not, so
 // the end is looked at here.
 enum FieldBuffer { kFieldDirect, kFieldCopied, kFieldTooSmall };
-static FieldBuffer field_buffer(const lbfd_ctx *c, const double *p, size_t n)
-{
-    hipPointerAttribute_t a;
-    hipDeviceptr_t base = nullptr;
+// The last allocation looked at in one call: buffers often share theirs.
+struct Allocation {
+    uintptr_t base = 0;
     size_t size = 0;
-    if (hipPointerGetAttributes(&a, p) != hipSuccess || a.type != hipMemoryTypeDevice || a.device != c->device ||
-        hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) != hipSuccess) {
-        (void)hipGetLastError();
-        return kFieldCopied;
+};
+static FieldBuffer field_buffer(const lbfd_ctx *c, const double *p, size_t n, Allocation &last)
+{
+    if ((uintptr_t)p - last.base >= last.size) {
+        hipPointerAttribute_t a;
+        hipDeviceptr_t base = nullptr;
+        size_t size = 0;
+        if (hipPointerGetAttributes(&a, p) != hipSuccess || a.type != hipMemoryTypeDevice || a.device != c->device ||
+            hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) != hipSuccess) {
+            (void)hipGetLastError();
+            return kFieldCopied;
+        }
+        last = {(uintptr_t)base, size};
     }
-    const size_t at = (uintptr_t)p - (uintptr_t)base;
-    if (at > size || n * sizeof(double) > size - at) return kFieldTooSmall;
+    const size_t at = (uintptr_t)p - last.base;
+    if (at > last.size || n * sizeof(double) > last.size - at) return kFieldTooSmall;
     return ((uintptr_t)p & 7) == 0 ? kFieldDirect : kFieldCopied;
 }
 
@@ -949,9 +957,10 @@ static int read_fields(lbfd_ctx *c, double *rho, double *u, double *T, double *Y
     double *const out[5] = {rho, u, T, Y, Ph};
     const size_t len[5] = {(size_t)N, (size_t)c->D * N, (size_t)N, (size_t)c->nsp * N, (size_t)N};
     bool direct = dev;
+    Allocation last;
     for (int i = 0; dev && i < 5; ++i) {
         if (!out[i]) continue;
-        const FieldBuffer b = field_buffer(c, out[i], len[i]);
+        const FieldBuffer b = field_buffer(c, out[i], len[i], last);
         direct &= b == kFieldDirect;
         // (where two buffers overlap the copies leave the last one's values)
         for (int j = 0; j < i; ++j)
