@@ -1311,9 +1311,8 @@ __device__ __forceinline__ void outlet_2d(const KParams &P, int f, int x, int y,
 {
     using L = Lat<Q>;
     using C = typename Prec<PREC>::calc;
-    if (!pulls_outlet(pc)) return;
     const int sign = f ? 1 : -1;
-    const long long in = idx - sign;
+    const long long in = pulls_outlet(pc) ? idx - sign : idx;
     const unsigned long long pci = P.code[in] == kCodeBoundary ? P.cell_code[in].x : 0;
     const C cs = (C)0.57735026918962576451;
     const C un = (C)sign * ux;
