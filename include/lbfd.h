@@ -222,7 +222,8 @@ int lbfd_read_fields(lbfd_ctx *c, double *rho, double *u, double *T,
 
 /* lbfd_read_fields into caller-owned device buffers of the same layouts
  * (double; mixed-precision T, Y are widened on the device), queued on the
- * context stream.  Synchronous. */
+ * context stream.  Synchronous.  LBFD_EDEVICE, with nothing written, for a
+ * buffer whose allocation on the context's GPU ends before its field does. */
 int lbfd_read_fields_dev(lbfd_ctx *c, double *rho, double *u, double *T,
                          double *Y, double *Ph);
 
@@ -370,17 +371,18 @@ int lbfd_objective_static(lbfd_ctx *c, int64_t nsteps, double *J);
  * has no differentiation; this entry point serves gradient-based uses of
  * the step (sensitivities of wall heat flux and flame position with respect
  * to wall temperatures and Arrhenius parameters).  Starting from the
- * current level L, runs nsteps steps and
- * computes the objective J selected by lbfd_set_objective and its exact
- * derivatives with respect to the
- * wall temperature of every isothermal solid cell (dJ_dwallT [N], host, may
- * be NULL; zero at other cells) and the Arrhenius A and Ta of every reaction
+ * current level L, runs nsteps steps and computes the objective J selected by
+ * lbfd_set_objective and its exact derivatives with respect to the wall
+ * temperature of every isothermal solid cell (dJ_dwallT [N], host, may be
+ * NULL; zero at other cells) and the Arrhenius A and Ta of every reaction
  * (dJ_dA, dJ_dTa [n_reactions], host, may be NULL).  Checkpoints are taken
  * every K steps and each segment is recomputed once during the backward
- * sweep (device memory: about (nsteps/K + K + 8) states).  On return the
- * context is at level L + nsteps, as after lbfd_step(nsteps).  Requires FP64
- * precision, no OUTFLOW face, and a lattice/species combination with an
- * adjoint kernel (D2Q9 or D3Q27 with 4 species); LBFD_EINVAL otherwise.
+ * sweep.  Device memory: one allocation of about (nsteps/K + K + 5) states,
+ * which the context keeps for its next call, until lbfd_destroy, when it is at
+ * most 1 GiB, and gives back at the end of the call when it is larger.  On
+ * return the context is at level L + nsteps, as after lbfd_step(nsteps).
+ * Requires FP64 precision, no OUTFLOW face, and a lattice/species combination
+ * with an adjoint kernel (D2Q9 or D3Q27 with 4 species); LBFD_EINVAL otherwise.
  * The wall-temperature and Arrhenius derivatives are accumulated with
  * atomic adds, so they may differ in the last bits between runs. */
 int lbfd_adjoint(lbfd_ctx *c, int64_t nsteps, int K, double *J, double *dJ_dwallT, double *dJ_dA,
@@ -430,8 +432,8 @@ int lbfd_time_kernels(lbfd_ctx *c, int64_t nsteps, double *ms_interior, double *
                       double *ms_chemistry);
 
 /* Cell counts of the context's geometry: fluid cells, and the fluid cells
- * that are boundary cells (every other fluid cell is interior: all of its pull sources and finite-difference points are fluid cells inside
- * the box). */
+ * that are boundary cells (every other fluid cell is interior: all of its
+ * pull sources and finite-difference points are fluid cells inside the box). */
 int lbfd_cell_counts(const lbfd_ctx *c, int64_t *n_fluid, int64_t *n_boundary);
 
 /* Kernel launches queued by one lbfd_step level without diagnostics: 1 for

@@ -1486,7 +1486,8 @@ __device__ __forceinline__ void add_params(const KParams &P, const double *red, 
 }
 
 template <int Q, int NSP, bool SUB>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(Q == 27 ? 1 : 2))) adjoint_collision_kernel(const AdjParams AP)
+__global__ void __launch_bounds__(kBlock)
+__attribute__((amdgpu_waves_per_eu(Q == 27 ? 1 : 2))) adjoint_collision_kernel(const AdjParams AP)
 {
     const KParams &P = AP.k;
     __shared__ double red[SUB ? 1 : 2 * LBFD_MAX_REACTIONS * kParamCopies];
@@ -1534,7 +1535,8 @@ __global__ void __launch_bounds__(kBlock) adjoint_chem_kernel(const AdjParams AP
 }
 
 template <int Q, int NSP>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) adjoint_stencil_kernel(const AdjParams AP)
+__global__ void __launch_bounds__(kBlock)
+__attribute__((amdgpu_waves_per_eu(2))) adjoint_stencil_kernel(const AdjParams AP)
 {
     const KParams &P = AP.k;
     AdjCell c;

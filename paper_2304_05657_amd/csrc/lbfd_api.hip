@@ -158,7 +158,8 @@ static void free_ctx(lbfd_ctx *c)
 {
     if (!c) return;
     void *ptrs[] = {c->pop[0], c->pop[1], c->sc[0], c->sc[1], c->mask, c->code, c->wall_T, c->outlet, c->outlet_un,
-                    c->inflow_u, c->inflow_du, c->bq, c->bimg, c->img_rng, c->img_idx, c->img_w, c->img_val, c->sup_idx, c->sup_val,
+                    c->inflow_u, c->inflow_du, c->bq, c->bimg, c->img_rng, c->img_idx, c->img_w, c->img_val,
+                    c->sup_idx, c->sup_val,
                     c->fields, c->partials, c->diag_dev, c->bad_dev, c->rx_dev, c->rxk_dev, c->fluid,
                     c->chem_order, c->chem_heavy, c->chem_count, c->face_Td, c->cell_code, c->bslot,
                     c->adj_ws};
@@ -364,10 +365,12 @@ static int upload_codes(lbfd_ctx *c, const std::vector<unsigned long long> &pull
         (void)hipFree(tmp);
     else if (e == hipSuccess)
         e = hipMemset(tmp, 0, need);  // (as it was)
-    return e == hipSuccess ? LBFD_OK : fail(LBFD_EDEVICE, "upload of the boundary codes failed: %s", hipGetErrorString(e));
+    return e == hipSuccess ? LBFD_OK
+                           : fail(LBFD_EDEVICE, "upload of the boundary codes failed: %s", hipGetErrorString(e));
 }
 
-// upload = false: the check alone (new wall temperatures; the codes hold none).
+// upload = false: the check alone (new wall temperatures: the codes hold none,
+// but one that is not a number is refused by it).
 static int build_descriptors(lbfd_ctx *c, bool upload)
 {
     const lbfd_params &p = c->p;
@@ -967,7 +970,8 @@ static int read_fields(lbfd_ctx *c, double *rho, double *u, double *T, double *Y
             direct &= !(out[j] && out[i] < out[j] + len[j] && out[j] < out[i] + len[i]);
         const bool widened = (i == 2 || i == 3) && c->prec != LBFD_FP64;  // by a kernel, not by a copy
         if (b == kFieldTooSmall && !widened)
-            return fail(LBFD_EDEVICE, "a field buffer is smaller than the %zu bytes of its field", len[i] * sizeof(double));
+            return fail(LBFD_EDEVICE, "a field buffer is smaller than the %zu bytes of its field",
+                        len[i] * sizeof(double));
     }
     KParams k = level_params(c);
     if (direct) {
@@ -1574,9 +1578,8 @@ struct AdjBuffers {
 
 // The workspace of one adjoint call: the context's, when it is large enough,
 // else a new one.  At the end the context keeps it if it is at most kAdjKeep
-// bytes, so that an optimisation
-// loop's calls allocate once, and a larger one is given back, whose allocation
-// is a small part of its call.
+// bytes, so that an optimisation loop's calls allocate once, and a larger one
+// is given back, whose allocation is a small part of its call.
 constexpr size_t kAdjKeep = (size_t)1 << 30;
 namespace {
 struct AdjWorkspace {

@@ -260,34 +260,6 @@ __device__ __forceinline__ double inflow_cu(const KParams &P, int x, int y, int 
     return inflow_cu_c(P, L::cx(I), L::cy(I), L::cz(I), x, y, z);
 }
 
-// Post-streaming population i of fluid cell (x, y, z) at the current level
-// from the post-collision buffer: pull from r - c_i; half-way bounce-back
-// from a solid or wall; velocity inlet (Eq. 31 in g units:
-// g*_opp + 2 w_i rho_in c_i.u_in); outlet value kept in the outlet buffer.
-template <int Q, int PREC, int I>
-__device__ __forceinline__ typename Prec<PREC>::calc gather(const KParams &P, int x, int y, int z, long long idx)
-{
-    using C = typename Prec<PREC>::calc;
-    using L = Lat<Q>;
-    constexpr int OPP = Q - 1 - I;
-    if constexpr (I == (Q - 1) / 2) {
-        return pop_load<Q, PREC, I>(P.pop_in, P.N, idx);  // rest population
-    } else {
-        Nb s = classify(P, x - L::cx(I), y - L::cy(I), z - L::cz(I));
-        if (s.kind == kFluid) return pop_load<Q, PREC, I>(P.pop_in, P.N, s.idx);
-        if (s.kind == kInflow) {
-            const double cu = inflow_cu<Q, I>(P, x, y, z);
-            return pop_load<Q, PREC, OPP>(P.pop_in, P.N, idx) + (C)(2.0 * L::w(I) * P.rho_in * cu);
-        }
-        if (s.kind == kOutflow) {
-            int sign = (s.face & 1) ? 1 : -1;
-            Nb in = classify(P, x - sign, y, z);
-            if (in.kind == kFluid) return (C)P.outlet[outlet_index(P, s.face, I, Q, y, z)];
-        }
-        return pop_load<Q, PREC, OPP>(P.pop_in, P.N, idx);
-    }
-}
-
 // ------------------------------------------------------------ scalars
 template <int NSP, class C>
 struct Pt {
