@@ -1,7 +1,7 @@
-"""2-D tiles of the step (64 x 4 cells, every fluid cell in its tile, scalars
+"""2-D tiles of the step (16 x 16 cells, every fluid cell in its tile, scalars
 staged with a 2-cell halo) at the sizes where their indexing can go wrong:
-boxes one cell short of, at and past a tile in each axis, boxes thinner than
-the halo, every face kind next to ragged tiles, single-cell solids against
+boxes one cell short of, at and past a tile in x (test_gpu_tile_seams.py: in
+y), boxes thinner than the halo, every face kind next to ragged tiles, single-cell solids against
 faces and behind an inlet's first cell.  Against the oracle.
 
 Tolerance: in FP64 the two sides differ by rounding order only (see
