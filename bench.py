@@ -60,8 +60,8 @@ KERNEL_SOURCES = [os.path.join(ROOT, "paper_2304_05657_amd", "csrc", f)
 # (profiles/traffic_porous_mech_512x256x256_and_porous_256.md)
 TRAFFIC = {
     ("porous3d_mech_512x256x256", "fp64", "lbfd_chem_jit_f64"): {
-        "bytes_per_launch": 6504.9e6,
-        "kernel_sha256": "85e1f64e01cc23371eb346d23d97157e75765e960080d5f822f0d281fea9e85c",
+        "bytes_per_launch": 6493.5e6,
+        "kernel_sha256": "68f91ddc1a69ee66c16904b930cb96146545ea2b68f127538b2038081f045c83",
     },
 }
 POP_BYTES = {"fp64": 8, "fp32": 4, "fp16": 2}
