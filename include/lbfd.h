@@ -222,8 +222,9 @@ int lbfd_read_fields(lbfd_ctx *c, double *rho, double *u, double *T,
 
 /* lbfd_read_fields into caller-owned device buffers of the same layouts
  * (double; mixed-precision T, Y are widened on the device), queued on the
- * context stream.  Synchronous.  LBFD_EDEVICE, with nothing written, for a
- * buffer whose allocation on the context's GPU ends before its field does. */
+ * context stream.  Synchronous.  LBFD_EDEVICE for a buffer whose allocation
+ * ends before the field that would be copied into it (in the mixed forms T
+ * and Y are widened by a kernel, which does not look). */
 int lbfd_read_fields_dev(lbfd_ctx *c, double *rho, double *u, double *T,
                          double *Y, double *Ph);
 

@@ -920,18 +920,17 @@ static KParams level_params(const lbfd_ctx *c)
     return k;
 }
 
-// How a caller's device buffer of n doubles is filled: by the fields kernel
-// itself (aligned memory of the context's GPU), or by a copy out of the
-// context's own buffer (other memory that the copy engine can reach).  A copy
-// past the end of an allocation is refused by the runtime, a store is not, so
-// the end is looked at here.
-enum FieldBuffer { kFieldDirect, kFieldCopied, kFieldTooSmall };
+// Whether a caller's device buffer of n doubles can be filled by the fields
+// kernel itself: aligned memory of the context's GPU whose allocation holds
+// them all.  Others are filled by copies out of the context's own buffer: the
+// copy engine reaches other memory, and the runtime refuses a copy past the end
+// of an allocation, where a store would go on.
 // The last allocation looked at in one call: buffers often share theirs.
 struct Allocation {
     uintptr_t base = 0;
     size_t size = 0;
 };
-static FieldBuffer field_buffer(const lbfd_ctx *c, const double *p, size_t n, Allocation &last)
+static bool writable_here(const lbfd_ctx *c, const double *p, size_t n, Allocation &last)
 {
     if ((uintptr_t)p - last.base >= last.size) {
         hipPointerAttribute_t a;
@@ -940,13 +939,20 @@ static FieldBuffer field_buffer(const lbfd_ctx *c, const double *p, size_t n, Al
         if (hipPointerGetAttributes(&a, p) != hipSuccess || a.type != hipMemoryTypeDevice || a.device != c->device ||
             hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) != hipSuccess) {
             (void)hipGetLastError();
-            return kFieldCopied;
+            return false;
         }
         last = {(uintptr_t)base, size};
     }
     const size_t at = (uintptr_t)p - last.base;
-    if (at > last.size || n * sizeof(double) > last.size - at) return kFieldTooSmall;
-    return ((uintptr_t)p & 7) == 0 ? kFieldDirect : kFieldCopied;
+    return at <= last.size && n * sizeof(double) <= last.size - at && ((uintptr_t)p & 7) == 0;
+}
+
+static int copy_field(void *dst, const void *src, size_t bytes, hipMemcpyKind kind, hipStream_t s)
+{
+    const hipError_t e = hipMemcpyAsync(dst, src, bytes, kind, s);
+    if (e == hipSuccess) return LBFD_OK;
+    (void)hipGetLastError();  // (reported here, not by the next launch)
+    return fail(LBFD_EDEVICE, "copy of a field failed: %s", hipGetErrorString(e));
 }
 
 // Fields of the current level into host (dev = false) or device buffers.
@@ -961,17 +967,12 @@ static int read_fields(lbfd_ctx *c, double *rho, double *u, double *T, double *Y
     const size_t len[5] = {(size_t)N, (size_t)c->D * N, (size_t)N, (size_t)c->nsp * N, (size_t)N};
     bool direct = dev;
     Allocation last;
-    for (int i = 0; dev && i < 5; ++i) {
+    for (int i = 0; direct && i < 5; ++i) {
         if (!out[i]) continue;
-        const FieldBuffer b = field_buffer(c, out[i], len[i], last);
-        direct &= b == kFieldDirect;
+        direct = writable_here(c, out[i], len[i], last);
         // (where two buffers overlap the copies leave the last one's values)
         for (int j = 0; j < i; ++j)
             direct &= !(out[j] && out[i] < out[j] + len[j] && out[j] < out[i] + len[i]);
-        const bool widened = (i == 2 || i == 3) && c->prec != LBFD_FP64;  // by a kernel, not by a copy
-        if (b == kFieldTooSmall && !widened)
-            return fail(LBFD_EDEVICE, "a field buffer is smaller than the %zu bytes of its field",
-                        len[i] * sizeof(double));
     }
     KParams k = level_params(c);
     if (direct) {
@@ -994,16 +995,18 @@ static int read_fields(lbfd_ctx *c, double *rho, double *u, double *T, double *Y
     HIP_TRY(launch_step(c->Q, c->nsp, c->prec, kModeFields, k, c->streams));
     HIP_TRY(hipStreamSynchronize(c->stream));
     const hipMemcpyKind kind = dev ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-    if (rho) HIP_TRY(hipMemcpyAsync(rho, c->fields, N * sizeof(double), kind, c->stream));
-    if (u) HIP_TRY(hipMemcpyAsync(u, c->fields + N, (size_t)c->D * N * sizeof(double), kind, c->stream));
-    if (Ph) HIP_TRY(hipMemcpyAsync(Ph, c->fields + 4 * N, N * sizeof(double), kind, c->stream));
+    int rc = LBFD_OK;
+    if (rho) rc = copy_field(rho, c->fields, N * sizeof(double), kind, c->stream);
+    if (!rc && u) rc = copy_field(u, c->fields + N, (size_t)c->D * N * sizeof(double), kind, c->stream);
+    if (!rc && Ph) rc = copy_field(Ph, c->fields + 4 * N, N * sizeof(double), kind, c->stream);
+    if (rc) return rc;
     if (T || Y) {
         const size_t n = (size_t)(1 + c->nsp) * N;
         if (c->prec == LBFD_FP64) {
-            if (T) HIP_TRY(hipMemcpyAsync(T, c->sc[c->cur], N * sizeof(double), kind, c->stream));
-            if (Y)
-                HIP_TRY(hipMemcpyAsync(Y, (double *)c->sc[c->cur] + N, (size_t)c->nsp * N * sizeof(double), kind,
-                                       c->stream));
+            if (T) rc = copy_field(T, c->sc[c->cur], N * sizeof(double), kind, c->stream);
+            if (!rc && Y)
+                rc = copy_field(Y, (double *)c->sc[c->cur] + N, (size_t)c->nsp * N * sizeof(double), kind, c->stream);
+            if (rc) return rc;
         } else if (dev) {
             // mixed storage: widened to double on the device
             if (T) HIP_TRY(launch_widen((const float *)c->sc[c->cur], T, (size_t)N, c->stream));

@@ -1,9 +1,9 @@
 """Device buffers of lbfd_read_fields_dev that the fields launch must not write
-by itself: one whose allocation ends before its field does is refused (as the
-runtime refuses a copy past the end of an allocation), with nothing written;
-buffers that overlap, or lie off the alignment of a double, are filled by
-copies in the order rho, u, P_h, T, Y.  The refused buffers hold half their
-field, so that no rounding of an allocation's size hides it."""
+by itself: one whose allocation ends before its field does (filled by a copy,
+which the runtime refuses; the refused buffers hold half their field, so that
+no rounding of an allocation's size hides it), buffers that overlap, or that lie
+off the alignment of a double (filled by copies in the order rho, u, P_h, T,
+Y)."""
 import ctypes as C
 
 import numpy as np
@@ -40,10 +40,11 @@ def test_too_small_is_refused(dim, small):
     say("%dd %s: %d bytes for %d doubles" % (dim, small, size[small] * 4, size[small]))
     buf = {k: torch.full((size[k],), -7.0, dtype=torch.float64, device="cuda") for k in KEYS}
     rc = s._lib.lbfd_read_fields_dev(s._h, *(raw if k == small else C.c_void_p(buf[k].data_ptr()) for k in KEYS))
-    assert rc == -3 and b"smaller" in s._lib.lbfd_last_error()
-    for k in KEYS:
-        assert torch.all(buf[k] == -7.0), k
+    assert rc == -3 and b"copy of a field" in s._lib.lbfd_last_error()
     # the context still reads and steps
+    assert s._lib.lbfd_read_fields_dev(s._h, *(C.c_void_p(buf[k].data_ptr()) for k in KEYS)) == 0
+    for k in KEYS:
+        assert np.array_equal(buf[k].cpu().numpy(), host[k].reshape(-1)), k
     s.step(1)
     s.sync()
     assert hip.hipFree(raw) == 0
