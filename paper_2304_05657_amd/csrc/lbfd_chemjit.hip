@@ -194,7 +194,8 @@ std::string chem_jit_source(const ChemRx *rx, int n_rx, int nsp, bool fp64, int 
 
 // The source compiled for the device and loaded; scratch: bytes of private
 // memory a thread of the kernel takes (registers that did not fit).
-static int compile(const std::string &src, bool fp64, hipFunction_t *f, int *scratch, std::string &err)
+static int compile(const std::string &src, bool fp64, hipModule_t *mod, hipFunction_t *f, int *scratch,
+                   std::string &err)
 {
     hiprtcProgram prog;
     const char *hdr[] = {kMathText};
@@ -221,9 +222,8 @@ static int compile(const std::string &src, bool fp64, hipFunction_t *f, int *scr
     std::vector<char> code(sz);
     hiprtcGetCode(prog, code.data());
     hiprtcDestroyProgram(&prog);
-    hipModule_t mod;
-    if (hipModuleLoadData(&mod, code.data()) != hipSuccess ||
-        hipModuleGetFunction(f, mod, fp64 ? "lbfd_chem_jit_f64" : "lbfd_chem_jit_f32") != hipSuccess) {
+    if (hipModuleLoadData(mod, code.data()) != hipSuccess ||
+        hipModuleGetFunction(f, *mod, fp64 ? "lbfd_chem_jit_f64" : "lbfd_chem_jit_f32") != hipSuccess) {
         err = "loading the compiled chemistry kernel failed";
         return -1;
     }
@@ -250,20 +250,24 @@ int chem_jit_build(const ChemRx *rx, int n_rx, int nsp, bool fp64, const void **
         *fn = (const void *)it->second;
         return 0;
     }
+    hipModule_t mod;
     hipFunction_t f;
     int scratch = 0;
-    if (compile(src, fp64, &f, &scratch, err) != 0) return -1;
+    if (compile(src, fp64, &mod, &f, &scratch, err) != 0) return -1;
     // A text that spills at four waves per SIMD is compiled again for three
     // (168 registers): 32 reactions, 21 registers spilled in FP64 and 15 in
     // single, 128 x 96 x 96: 956 -> 830 us a launch, single 850 -> 834.  (26
     // reactions still fit.)
     if (scratch > 0) {
+        hipModule_t mod3;
         hipFunction_t f3;
         std::string err3;
         int scratch3 = 0;
-        if (compile(generate(rx, n_rx, nsp, fp64, kJitWaves - 1), fp64, &f3, &scratch3, err3) == 0 &&
-            scratch3 < scratch)
-            f = f3;
+        if (compile(generate(rx, n_rx, nsp, fp64, kJitWaves - 1), fp64, &mod3, &f3, &scratch3, err3) == 0) {
+            const bool better = scratch3 < scratch;
+            (void)hipModuleUnload(better ? mod : mod3);
+            if (better) f = f3;
+        }
     }
     g_cache[key] = f;
     *fn = (const void *)f;
