@@ -1193,7 +1193,7 @@ __device__ __forceinline__ void tile_stencil(const KParams &P, int d, int x, int
     // mirror cell's: the lane's address and plane stride are selected, so that
     // the points' loads stay in flight together (with a pass of loads a slot,
     // one after the other, the images of 160 x 128 x 96 added 133 us in FP64 and
-    // 120 in half beside their reconstruction; now 25 and 15)
+    // 120 in half beside their reconstruction; now some 30)
     int li[4] = {-1, -1, -1, -1};
     bool images = false;
     if constexpr (CW) {
@@ -1206,11 +1206,11 @@ __device__ __forceinline__ void tile_stencil(const KParams &P, int d, int x, int
     if (images) {
         const S *img = (const S *)P.img_val;
         const S *q[4];
-        uint32_t step[4];
+        uint32_t step[4];  // in elements (n_img < 2^31)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             q[j] = li[j] >= 0 ? img + li[j] : (const S *)P.sc_in + (idx + at[j]);
-            step[j] = (uint32_t)((li[j] >= 0 ? P.n_img : P.N) * sizeof(S));
+            step[j] = (uint32_t)(li[j] >= 0 ? P.n_img : P.N);
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) pv[j].T = *q[j];
@@ -1218,7 +1218,7 @@ __device__ __forceinline__ void tile_stencil(const KParams &P, int d, int x, int
         for (int k = 0; k < NSP; ++k)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                q[j] = (const S *)((const char *)q[j] + step[j]);
+                q[j] += step[j];
                 pv[j].Y[k] = *q[j];
             }
         C ri[4];
