@@ -302,18 +302,22 @@ def _check_scalar_pairs(L: list) -> list:
         j = next((q for q in range(i - 6, i + 7) if reloads.get(q, (0, 0))[0] == b + 1), None)
         if j is None or not _used_as_pair(L, dests, max(i, j), b):
             continue
-        for p, ra in stores.get(lo, []):
-            for q, rb in stores.get(reloads[j][1], []):
-                if ra % 2 or rb != ra + 1:
-                    continue
-                da, db = definition(ra, p), definition(rb, q)
-                x, y = max(da, db), min(da, db)  # x: the later of the two halves' writers
-                if y < 0 or x == y or not L[y].startswith('s_load') or not {ra, rb} <= dests[y] or \
-                        {ra, rb} <= dests[x] or L[x].startswith('v_readlane'):
-                    continue
-                op = L[x].split()[0]
-                if not any(_sregs(z) & {ra, rb} for z in L[x][len(op):].split(',')[1:]):
-                    found.append((x, L[x]))
+        # the store before each half's reload, in layout order
+        sp = [st for st in stores.get(lo, []) if st[0] < i]
+        sq = [st for st in stores.get(reloads[j][1], []) if st[0] < j]
+        if not sp or not sq:
+            continue
+        (p, ra), (q, rb) = sp[-1], sq[-1]
+        if ra % 2 or rb != ra + 1:
+            continue
+        da, db = definition(ra, p), definition(rb, q)
+        x, y = max(da, db), min(da, db)  # x: the later of the two halves' writers
+        if y < 0 or x == y or not L[y].startswith('s_load') or not {ra, rb} <= dests[y] or \
+                {ra, rb} <= dests[x] or L[x].startswith('v_readlane'):
+            continue
+        op = L[x].split()[0]
+        if not any(_sregs(z) & {ra, rb} for z in L[x][len(op):].split(',')[1:]):
+            found.append((x, L[x]))
     return sorted(set(found))
 
 

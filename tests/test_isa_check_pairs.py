@@ -22,3 +22,10 @@ USE = ["global_load_dword v1, v2, s[8:9]", "s_endpgm"]
 ])
 def test_half_overwritten_pair(body, bad):
     assert bool(check_kernel(body)) == bad
+
+
+def test_lanes_stored_again():
+    """A later store of the same lanes (a tuple whose halves are dead by then)
+    is not what an earlier reload reads."""
+    again = ["s_mul_i32 s64, s4, 12"] + SPILL + ["s_endpgm"]
+    assert not check_kernel([LOAD] + SPILL + BACK + USE[:1] + again)
