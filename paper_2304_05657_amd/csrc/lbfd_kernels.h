@@ -1283,6 +1283,10 @@ __device__ __forceinline__ void outlet_2d(const KParams &P, int f, int x, int y,
 {
     using L = Lat<Q>;
     using C = typename Prec<PREC>::calc;
+    // (in half precision by selection: 2048 x 512 burner 36.5 us a step, behind
+    // the branch 36.9; in FP64 the branch is the faster, 256 x 64 8.0 and 8.4)
+    if constexpr (PREC != LBFD_MIXED_FP16)
+        if (!pulls_outlet(pc)) return;
     const int sign = f ? 1 : -1;
     const long long in = pulls_outlet(pc) ? idx - sign : idx;
     const unsigned long long pci = P.code[in] == kCodeBoundary ? P.cell_code[in].x : 0;
