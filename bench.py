@@ -60,8 +60,8 @@ KERNEL_SOURCES = [os.path.join(ROOT, "paper_2304_05657_amd", "csrc", f)
 # (profiles/traffic_porous_mech_512x256x256_and_porous_256.md)
 TRAFFIC = {
     ("porous3d_mech_512x256x256", "fp64", "lbfd_chem_jit_f64"): {
-        "bytes_per_launch": 6493.5e6,
-        "kernel_sha256": "68f91ddc1a69ee66c16904b930cb96146545ea2b68f127538b2038081f045c83",
+        "bytes_per_launch": 6500.1e6,
+        "kernel_sha256": "eb64ce47b49290d998356037578946ec2a79984c5bf836729f486a254a04354d",
     },
 }
 POP_BYTES = {"fp64": 8, "fp32": 4, "fp16": 2}
